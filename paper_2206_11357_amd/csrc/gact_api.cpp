@@ -39,6 +39,7 @@ gact::Geometry make_geometry(int group_size) {
     geo.groups_per_tile = geo.lanes_used / geo.lpg;
     geo.group_size = group_size;
     geo.group_shift = geo.lpg_shift + 5;
+    geo.lpg_magic = 65536 / geo.lpg + 1;
     geo.lds_wave_dwords = 0;      // set per launch from the dtypes in it
     return geo;
 }

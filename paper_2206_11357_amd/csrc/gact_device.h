@@ -46,6 +46,7 @@ struct Geometry {
     int32_t groups_per_tile;
     int32_t group_size;
     int32_t group_shift;   // log2(group_size) when pow2
+    int32_t lpg_magic;     // floor(65536 / lpg) + 1: lane / lpg = lane * lpg_magic >> 16 for lane < 64
     int32_t lds_wave_dwords;   // compress: LDS dwords per wavefront (lds_dwords_per_wave of the widest dtype launched)
 };
 
