@@ -47,6 +47,7 @@ struct Geometry {
     int32_t group_size;
     int32_t group_shift;   // log2(group_size) when pow2
     int32_t lpg_magic;     // floor(65536 / lpg) + 1: lane / lpg = lane * lpg_magic >> 16 for lane < 64
+    int32_t run_shift;     // log2 of the neighbouring blocks one XCD takes in a run (run_shift_for), 0: plain order
     int32_t lds_wave_dwords;   // compress: LDS dwords per wavefront (lds_dwords_per_wave of the widest dtype launched)
 };
 
@@ -100,22 +101,39 @@ constexpr int64_t reduce_chunk_elems(int dtype) { return dtype == GACT_DT_F32 ? 
 // wavefront store covers (256 fp32 or 512 bf16 elements); a block of four
 // wavefronts takes 4 * units consecutive units.  Units per wavefront trade the
 // load latency a wavefront hides against the length of its store burst; the
-// best value depends on dtype and code width and was chosen by sweep on MI355X
-// (% of HBM peak, decompress, 32 tensors of 13 / 26 M elements):
-//            units  1     2     3     4     6
-//   bf16 b=1      59.4  66.9  71.7  65.8  64.0
-//   bf16 b=2      61.2  75.2  74.7  75.4  68.0   (2 units: 68.8 in a second run)
-//   bf16 b=4      63.3  79.5  76.2  72.8  74.1
-//   bf16 b=8      72.8  80.6  74.3  75.4  75.0
-//   fp32 b=1      56.8  75.0  78.8  73.6  66.1
-//   fp32 b=2      56.9  68.4  76.9  77.1  62.2
-//   fp32 b=4      57.5  75.8  72.2  69.6  63.5
-//   fp32 b=8      63.9  79.2  66.2  66.7  62.6
-constexpr int dec_units_per_wave(int /*dtype*/, int bits) {
-    return bits == 1 ? 3 : bits == 2 ? 4 : 2;
+// best value depends on the code width and was chosen by sweep on MI355X, with
+// the block order of run_shift_for (us, decompress, every tensor at that width:
+// 96 bf16 tensors of 1.4 G elements, 400 bf16 ones of 1.0 G, 53 fp32 ones of 0.7 G,
+// 3 fp32 ones of 87 M):
+//            units    1                     2                     3                     4
+//   b=1      669 524 672  93       532 437 533  76       532 415 471  70       542 424 484  68
+//   b=2      691 535 706  97       533 439 536  77       532 415 496  72       537 444 496  71
+//   b=4      716 539 702  98       554 431 524  76       638 422 559  73       584 445 571  78
+//   b=8      694  -  665   -       665  -  556   -       724  -  664   -       700  -  645   -
+// A launch of 53 fp32 tensors of mixed widths around 2 bits, 89 M elements: 65.3 us
+// with four units at 2 bits, 66.7 with three.
+constexpr int dec_units_per_wave(int dtype, int bits) {
+    return bits == 1 ? 3 : bits == 2 ? (dtype == GACT_DT_F32 ? 4 : 3) : 2;
 }
 constexpr int dec_block_elems(int dtype, int bits) {
     return 4 * dec_units_per_wave(dtype, bits) * (dtype == GACT_DT_F32 ? 256 : 512);
+}
+
+// Length of the runs of neighbouring blocks that go to one XCD, as a power of two
+// (us on MI355X, plain order and runs of 2^s blocks):
+//                                              plain   s=4    s=5    s=6    s=7    s=8    s=9
+//   decompress 96 bf16 tensors, 1.2M blocks    2378   2428   2336   2350   2343   2329   2340
+//   decompress 53 fp32 tensors, 230k blocks     492    493    490    492    495    503    510
+//   decompress 400 bf16 tensors, 49k blocks     133    129    128    127    127    130    129
+//   decompress 3 fp32 tensors, 32k blocks      76.2   73.7   73.5   73.8   74.5   75.3   77.9
+//   decompress 1 bf16 tensor, 1.8k blocks      4.85    --    5.35
+// Decompress: runs of 32 (runs of 4 to 16 cost up to 10 % on bf16 output at 4 bits, and lengths that are
+// no power of two are worse than 32 throughout).  Launches of few windows keep plain order: the XCDs that
+// get the runs of a last, partial window finish late.
+inline int run_shift_for(bool compress, uint64_t blocks) {
+    int log2 = 0;
+    while ((blocks >> log2) > 1) ++log2;
+    return compress || log2 < 14 ? 0 : 5;
 }
 
 }  // namespace gact

@@ -708,6 +708,22 @@ __device__ __forceinline__ void decompress_units(const TensorArgs& t, const Geom
         default: break;                                                              \
     }
 
+// The block of work this workgroup takes.  Workgroups go to the eight XCDs in
+// turn, each XCD with an L2 of its own, so that in plain order neighbouring
+// blocks never share one: a line of packed codes, minima or steps that two
+// blocks write parts of (every line at a block's edge where the caller's buffers
+// are not aligned to 128 bytes, as in one buffer per kind cut at multiples of 16)
+// leaves two caches as two partial writes, and one that two blocks read is
+// fetched twice.  Within a window of 8 * 2^s workgroups, XCD x therefore takes
+// the 2^s neighbouring blocks x * 2^s ...; what does not fill a window keeps
+// plain order.  s is geo.run_shift, chosen by the launcher.
+__device__ __forceinline__ uint32_t work_block(const Geometry& geo) {
+    const uint32_t b = blockIdx.x, s = (uint32_t)geo.run_shift;
+    const uint32_t window = b >> (3 + s) << (3 + s);
+    if (s == 0u || window + (8u << s) > gridDim.x) return b;
+    return window | ((b & 7u) << s) | ((b - window) >> 3);
+}
+
 template <bool SUM>
 __device__ __forceinline__ void compress_block(const TensorArgs& t, const Geometry& geo,
                                                int64_t block_in_tensor, double* __restrict__ tile_sum) {
@@ -760,13 +776,13 @@ __device__ __forceinline__ void run_block(const TensorArgs& t, const Geometry& g
 // bf16 compressor, which is bound by instruction issue, needs all of them.
 template <bool COMPRESS>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void single_kernel(TensorArgs t, Geometry geo) {
-    run_block<COMPRESS>(t, geo, (int64_t)blockIdx.x);
+    run_block<COMPRESS>(t, geo, (int64_t)work_block(geo));
 }
 
 // One tensor, compressed, with the sum of every tile as a by-product.
 __global__ __launch_bounds__(kBlockThreads) void compress_sum_kernel(TensorArgs t, Geometry geo,
                                                                      double* __restrict__ tile_sum) {
-    compress_block<true>(t, geo, (int64_t)blockIdx.x, tile_sum);
+    compress_block<true>(t, geo, (int64_t)work_block(geo), tile_sum);
 }
 
 // Multi-tensor: block b belongs to the tensor l with first_block[l] <= b <
@@ -791,7 +807,7 @@ template <bool COMPRESS>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void multi_kernel(
     const TensorArgs* __restrict__ table, const uint32_t* __restrict__ first_block,
     const uint32_t* __restrict__ hint, uint32_t hint_shift, Geometry geo) {
-    const uint32_t b = blockIdx.x;
+    const uint32_t b = work_block(geo);
     const int l = find_tensor<false>(first_block, hint, hint_shift, b);
     const TensorArgs t = table[l];
     run_block<COMPRESS>(t, geo, (int64_t)(b - first_block[l]));
@@ -802,7 +818,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(8
 template <bool COMPRESS>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void multi_inline_kernel(
     InlineTable tab, Geometry geo) {
-    const uint32_t b = blockIdx.x;
+    const uint32_t b = work_block(geo);
     const int l = find_tensor<true>(tab.first_block, tab.hint, tab.hint_shift, b);
     run_block<COMPRESS>(tab.t[l], geo, (int64_t)(b - tab.first_block[l]));
 }

@@ -2,6 +2,7 @@
 Every output byte is compared.  Quantizer: arXiv 2206.11357 App. A.4, per group (Sec. 5)."""
 import numpy as np
 import pytest
+import torch
 
 import synthetic_inputs as syn
 from test_gpu_parity import run_case
@@ -24,3 +25,25 @@ def test_full_tiles_of_group_sizes_that_are_no_power_of_two(gact, dtype, lanes):
         x = as_dtype(syn.draw_numpy(syn.OUTLIER, n, 40 * lanes + k), dtype)
         for bits in (1, 2, 4, 8)[(k + lanes) % 2::2]:
             run_case(gact, x, G, bits, seed=lanes + k)
+
+
+@pytest.mark.parametrize("dtype,bits,blocks", [("bf16", 4, 8192 + 37), ("f32", 2, 8192), ("f32", 1, 16384 + 300)])
+def test_runs_of_neighbouring_blocks_per_xcd(gact, dtype, bits, blocks):
+    """Launches that are long enough for another block order, with and without a last partial window,
+    against the same tensor in pieces that are not."""
+    G, seed, n = 256, 9, blocks * 8192 - 1234
+    gen = torch.Generator(device="cuda").manual_seed(blocks)
+    x = torch.randn(n, device="cuda", generator=gen).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    whole = gact.gact_compress(x, G, bits, seed)
+    y = gact.gact_decompress(*whole, n, G, bits, dtype=x.dtype)
+    step = 500 * 8192
+    ws = torch.empty(gact.gact_multi_workspace_bytes(1), dtype=torch.uint8, device="cuda")
+    for a in range(0, n, step):
+        m = min(step, n - a)
+        p, mn, sc = gact.alloc_compressed(m, G, bits, "cuda")
+        descs = gact.make_descs([x[a:a + m]], [p], [mn], [sc], [None], [m], [bits], [seed], [x.dtype], index_bases=[a])
+        gact.gact_compress_multi(descs, 1, G, ws)
+        assert torch.equal(p, whole[0][a * bits // 8:a * bits // 8 + p.numel()]), a
+        assert torch.equal(mn, whole[1][a // G:a // G + mn.numel()]) and torch.equal(sc, whole[2][a // G:a // G + sc.numel()]), a
+        assert torch.equal(gact.gact_decompress(p, mn, sc, m, G, bits, dtype=x.dtype).view(torch.uint8),
+                           y[a:a + m].view(torch.uint8)), a
