@@ -122,18 +122,24 @@ constexpr int dec_block_elems(int dtype, int bits) {
 // Length of the runs of neighbouring blocks that go to one XCD, as a power of two
 // (us on MI355X, plain order and runs of 2^s blocks):
 //                                              plain   s=4    s=5    s=6    s=7    s=8    s=9
+//   compress  400 bf16 tensors, 253k blocks     922    901    887    882    871    859    863
+//   compress  96 bf16 tensors, 688k blocks     2386   2389   2363   2357   2352   2352   2352
+//   compress  53 fp32 tensors, 87k blocks       498    486    481    481    481    483    483
+//   compress  400 bf16 tensors, 32k blocks      121    116    115    114    115    117    120
+//   compress  3 fp32 tensors, 16k blocks       69.4   68.3   68.2   68.6   69.4   70.0   70.3
 //   decompress 96 bf16 tensors, 1.2M blocks    2378   2428   2336   2350   2343   2329   2340
 //   decompress 53 fp32 tensors, 230k blocks     492    493    490    492    495    503    510
 //   decompress 400 bf16 tensors, 49k blocks     133    129    128    127    127    130    129
 //   decompress 3 fp32 tensors, 32k blocks      76.2   73.7   73.5   73.8   74.5   75.3   77.9
 //   decompress 1 bf16 tensor, 1.8k blocks      4.85    --    5.35
-// Decompress: runs of 32 (runs of 4 to 16 cost up to 10 % on bf16 output at 4 bits, and lengths that are
+// Compress: runs as long as leave 64 windows, at most 256 blocks.  Decompress: runs of 32 (runs of 4 to 16 cost up to 10 % on bf16 output at 4 bits, and lengths that are
 // no power of two are worse than 32 throughout).  Launches of few windows keep plain order: the XCDs that
 // get the runs of a last, partial window finish late.
 inline int run_shift_for(bool compress, uint64_t blocks) {
     int log2 = 0;
     while ((blocks >> log2) > 1) ++log2;
-    return compress || log2 < 14 ? 0 : 5;
+    if (compress) return log2 < 13 ? 0 : (log2 - 9 < 8 ? log2 - 9 : 8);
+    return log2 < 14 ? 0 : 5;
 }
 
 }  // namespace gact

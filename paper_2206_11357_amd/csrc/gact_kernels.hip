@@ -416,6 +416,28 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
     RawTile<DT> raw;
     load_tile<DT, KIND>(t.io, e0, ne, lane, raw);
 
+    // Noise of the lane's 32 elements, while the loads are in flight: block numbers
+    // tile_blk + 4 lane + (0..3).  The guarded instantiation draws it block by block further down.
+    const uint64_t tile_blk = t.blk_base() + ((uint64_t)e0 >> 3);
+    // The key passes through an empty statement: otherwise the twenty round keys are computed once,
+    // ahead of the switch over the instantiations, and spill to vector registers from there.
+    uint32_t k0 = t.seed_lo, k1 = t.seed_hi;
+    asm volatile("" : "+s"(k0), "+s"(k1));
+    // All four blocks for fp32; two for bf16, whose 64 registers hold no more without spilling.
+    constexpr int kEarly = DT == GACT_DT_F32 ? 4 : 2;
+    uint32_t noise[4][4];
+    const PhiloxUniform pu((uint32_t)(tile_blk >> 32), k0, k1);
+    const uint32_t lane_c0 = (uint32_t)tile_blk + 4u * (uint32_t)lane;
+    if (KIND != kEdge) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 4 - kEarly; c < 4; ++c) {
+            philox_head_uniform(lane_c0 + (uint32_t)c, pu, k0, k1, noise[c]);
+            philox_rounds<3>(noise[c][0], noise[c][1], noise[c][2], noise[c][3], k0, k1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
     // layout switch: coalesced rows in, 32 consecutive elements per lane out
     float v[kPerLane];
     stage_tile<DT>(raw, lds, lane);
@@ -502,18 +524,22 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
 #pragma unroll
     for (int w = 0; w < BITS; ++w) acc[w] = 0u;
     const float ninv17 = -(inv * 0x1p17f);
-    // block numbers of this lane: tile_blk + 4 lane + (0..3); the high word is the
-    // same for the whole tile unless the low word wraps inside it
-    const uint64_t tile_blk = t.blk_base() + ((uint64_t)e0 >> 3);
-    const bool hi_uniform = (uint32_t)tile_blk <= 0xFFFFFEFFu;
-    const PhiloxUniform pu((uint32_t)(tile_blk >> 32), t.seed_lo, t.seed_hi);
-    const uint32_t lane_c0 = (uint32_t)tile_blk + 4u * (uint32_t)lane;
 #pragma unroll
     for (int c = 3; c >= 0; --c) {
+        // valid elements from this lane's first on.  Opaque, so that the masks of the 32 comparisons
+        // are not kept from the statistics above (they would fill the scalar registers and spill).
+        int left = ne - my0;
+        if (KIND == kEdge) asm volatile("" : "+v"(left));
         uint32_t r[4];
-        if (hi_uniform) philox_head_uniform(lane_c0 + (uint32_t)c, pu, t.seed_lo, t.seed_hi, r);
-        else philox_head_any(tile_blk + (uint64_t)(4 * lane + c), t.seed_lo, t.seed_hi, r);
-        philox_rounds<3>(r[0], r[1], r[2], r[3], t.seed_lo, t.seed_hi);
+        if (KIND == kEdge) {
+            philox_head_any(tile_blk + (uint64_t)(4 * lane + c), k0, k1, r);
+            philox_rounds<3>(r[0], r[1], r[2], r[3], k0, k1);
+        } else if (c < 4 - kEarly) {
+            philox_head_uniform(lane_c0 + (uint32_t)c, pu, k0, k1, r);
+            philox_rounds<3>(r[0], r[1], r[2], r[3], k0, k1);
+        } else {
+            r[0] = noise[c][0]; r[1] = noise[c][1]; r[2] = noise[c][2]; r[3] = noise[c][3];
+        }
         float tn[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) tn[j] = (v[c * 8 + j] - mn) * ninv17;   // -T, T in [0, 2^25)
@@ -529,7 +555,7 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
             // noise value 2^-17 unless B = 255, so only 8-bit codes can round
             // past the top level
             if (BITS == 8) nq = nq > -(int32_t)B ? nq : -(int32_t)B;
-            if (KIND == kEdge && my0 + e >= ne) nq = (int32_t)kBias;
+            if (KIND == kEdge && e >= left) nq = (int32_t)kBias;
             const int w = (e * BITS) >> 5;
             acc[w] = (acc[w] << BITS) + (uint32_t)nq;
         }
@@ -695,12 +721,12 @@ __device__ __forceinline__ void decompress_units(const TensorArgs& t, const Geom
 
 // ------------------------------------------------------------------ kernels
 // uniform dispatch over (dtype, bits)
-#define GACT_DISPATCH(t, CALL)                                                       \
+#define GACT_DISPATCH(t, WITH_F32, CALL)                                             \
     switch ((t).dtype() * 16 + (t).bits()) {                                             \
-        case GACT_DT_F32 * 16 + 1:  { CALL(GACT_DT_F32, 1) } break;                  \
-        case GACT_DT_F32 * 16 + 2:  { CALL(GACT_DT_F32, 2) } break;                  \
-        case GACT_DT_F32 * 16 + 4:  { CALL(GACT_DT_F32, 4) } break;                  \
-        case GACT_DT_F32 * 16 + 8:  { CALL(GACT_DT_F32, 8) } break;                  \
+        case GACT_DT_F32 * 16 + 1:  if constexpr (WITH_F32) { CALL(GACT_DT_F32, 1) } break;  \
+        case GACT_DT_F32 * 16 + 2:  if constexpr (WITH_F32) { CALL(GACT_DT_F32, 2) } break;  \
+        case GACT_DT_F32 * 16 + 4:  if constexpr (WITH_F32) { CALL(GACT_DT_F32, 4) } break;  \
+        case GACT_DT_F32 * 16 + 8:  if constexpr (WITH_F32) { CALL(GACT_DT_F32, 8) } break;  \
         case GACT_DT_BF16 * 16 + 1: { CALL(GACT_DT_BF16, 1) } break;                 \
         case GACT_DT_BF16 * 16 + 2: { CALL(GACT_DT_BF16, 2) } break;                 \
         case GACT_DT_BF16 * 16 + 4: { CALL(GACT_DT_BF16, 4) } break;                 \
@@ -724,7 +750,7 @@ __device__ __forceinline__ uint32_t work_block(const Geometry& geo) {
     return window | ((b & 7u) << s) | ((b - window) >> 3);
 }
 
-template <bool SUM>
+template <bool WITH_F32, bool SUM>
 __device__ __forceinline__ void compress_block(const TensorArgs& t, const Geometry& geo,
                                                int64_t block_in_tensor, double* __restrict__ tile_sum) {
     // sized by the launcher: geo.lds_wave_dwords per wavefront
@@ -740,10 +766,12 @@ __device__ __forceinline__ void compress_block(const TensorArgs& t, const Geomet
 #define GACT_C_FULL(DT, BITS) compress_tile<DT, BITS, kFull, SUM>(t, geo, tile, lds, lane, tile_sum);
 #define GACT_C_ANY(DT, BITS)  compress_tile<DT, BITS, kFullAny, SUM>(t, geo, tile, lds, lane, tile_sum);
 #define GACT_C_EDGE(DT, BITS) compress_tile<DT, BITS, kEdge, SUM>(t, geo, tile, lds, lane, tile_sum);
-    if (geo.pow2 ? end <= t.n : end < t.n) {
-        if (geo.pow2) { GACT_DISPATCH(t, GACT_C_FULL) } else { GACT_DISPATCH(t, GACT_C_ANY) }
+    // A tile in which the low word of the Philox block number wraps is not either (PhiloxUniform).
+    const uint32_t blk = (uint32_t)(t.blk_base() + ((uint64_t)tile * (uint32_t)(geo.lanes_used * kPerLane) >> 3));
+    if ((geo.pow2 ? end <= t.n : end < t.n) && blk <= 0xFFFFFEFFu) {
+        if (geo.pow2) { GACT_DISPATCH(t, WITH_F32, GACT_C_FULL) } else { GACT_DISPATCH(t, WITH_F32, GACT_C_ANY) }
     } else {
-        GACT_DISPATCH(t, GACT_C_EDGE)
+        GACT_DISPATCH(t, WITH_F32, GACT_C_EDGE)
     }
 #undef GACT_C_FULL
 #undef GACT_C_ANY
@@ -760,29 +788,37 @@ __device__ __forceinline__ void decompress_block(const TensorArgs& t, const Geom
     decompress_units<DT, BITS, false, dec_units_per_wave(DT, BITS)>(t, geo, block_in_tensor, wave, lane);
 #define GACT_D_EDGE(DT, BITS) \
     decompress_units<DT, BITS, true, dec_units_per_wave(DT, BITS)>(t, geo, block_in_tensor, wave, lane);
-    if (full) { GACT_DISPATCH(t, GACT_D_FULL) } else { GACT_DISPATCH(t, GACT_D_EDGE) }
+    if (full) { GACT_DISPATCH(t, true, GACT_D_FULL) } else { GACT_DISPATCH(t, true, GACT_D_EDGE) }
 #undef GACT_D_FULL
 #undef GACT_D_EDGE
 }
 
-template <bool COMPRESS>
+// What a launch does.  A compressing launch is one of two kernels:
+//   kBf16  every tensor is bf16: 4 KB of LDS per wavefront, so eight wavefronts per
+//          SIMD are resident if they keep to 64 VGPRs;
+//   kAny   fp32 among them: 8 KB of LDS per wavefront, four per SIMD, 128 VGPRs each.
+enum Work { kDecompress, kCompressBf16, kCompressAny };
+constexpr int waves_per_simd(Work w) { return w == kCompressAny ? 4 : 8; }
+
+template <Work W>
 __device__ __forceinline__ void run_block(const TensorArgs& t, const Geometry& geo,
                                           int64_t block_in_tensor) {
-    if (COMPRESS) compress_block<false>(t, geo, block_in_tensor, nullptr);
-    else decompress_block(t, geo, block_in_tensor);
+    if constexpr (W == kDecompress) decompress_block(t, geo, block_in_tensor);
+    else compress_block<W == kCompressAny, false>(t, geo, block_in_tensor, nullptr);
 }
 
-// Eight resident wavefronts per SIMD (at most 64 VGPRs) for every kernel: the
-// bf16 compressor, which is bound by instruction issue, needs all of them.
-template <bool COMPRESS>
-__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void single_kernel(TensorArgs t, Geometry geo) {
-    run_block<COMPRESS>(t, geo, (int64_t)work_block(geo));
+#define GACT_KERNEL(W) \
+    __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(waves_per_simd(W), waves_per_simd(W)))) void
+
+template <Work W>
+GACT_KERNEL(W) single_kernel(TensorArgs t, Geometry geo) {
+    run_block<W>(t, geo, (int64_t)work_block(geo));
 }
 
 // One tensor, compressed, with the sum of every tile as a by-product.
 __global__ __launch_bounds__(kBlockThreads) void compress_sum_kernel(TensorArgs t, Geometry geo,
                                                                      double* __restrict__ tile_sum) {
-    compress_block<true>(t, geo, (int64_t)work_block(geo), tile_sum);
+    compress_block<true, true>(t, geo, (int64_t)work_block(geo), tile_sum);
 }
 
 // Multi-tensor: block b belongs to the tensor l with first_block[l] <= b <
@@ -803,38 +839,53 @@ __device__ __forceinline__ int find_tensor(const uint32_t* first_block, const ui
 }
 
 // Table in device memory (the caller's workspace): any number of tensors.
-template <bool COMPRESS>
-__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void multi_kernel(
+template <Work W>
+GACT_KERNEL(W) multi_kernel(
     const TensorArgs* __restrict__ table, const uint32_t* __restrict__ first_block,
     const uint32_t* __restrict__ hint, uint32_t hint_shift, Geometry geo) {
     const uint32_t b = work_block(geo);
     const int l = find_tensor<false>(first_block, hint, hint_shift, b);
     const TensorArgs t = table[l];
-    run_block<COMPRESS>(t, geo, (int64_t)(b - first_block[l]));
+    run_block<W>(t, geo, (int64_t)(b - first_block[l]));
 }
 
 // Table passed by value in the kernel arguments: up to kInlineTensors tensors,
 // no upload and no host synchronisation before the launch.
-template <bool COMPRESS>
-__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void multi_inline_kernel(
+template <Work W>
+GACT_KERNEL(W) multi_inline_kernel(
     InlineTable tab, Geometry geo) {
     const uint32_t b = work_block(geo);
     const int l = find_tensor<true>(tab.first_block, tab.hint, tab.hint_shift, b);
-    run_block<COMPRESS>(tab.t[l], geo, (int64_t)(b - tab.first_block[l]));
+    run_block<W>(tab.t[l], geo, (int64_t)(b - tab.first_block[l]));
 }
 
 }  // namespace gact
 
 // ------------------------------------------------------------ host launchers
+namespace {
+gact::Work work_of(int compress, const gact::Geometry* geo) {
+    if (!compress) return gact::kDecompress;
+    return geo->lds_wave_dwords == gact::lds_dwords_per_wave(GACT_DT_BF16) ? gact::kCompressBf16 : gact::kCompressAny;
+}
+}  // namespace
+
+// KERNEL<work>, launched on `blocks` blocks with the LDS its work needs
+#define GACT_LAUNCH(KERNEL, ...)                                                                            \
+    do {                                                                                                    \
+        const dim3 grid(blocks), block(gact::kBlockThreads);                                                \
+        const unsigned lds = compress ? 4u * gact::kWavesPerBlk * (unsigned)geo->lds_wave_dwords : 0u;      \
+        hipStream_t s = (hipStream_t)stream;                                                                \
+        switch (work_of(compress, geo)) {                                                                   \
+            case gact::kDecompress:   hipLaunchKernelGGL(KERNEL<gact::kDecompress>, grid, block, lds, s, __VA_ARGS__); break;   \
+            case gact::kCompressBf16: hipLaunchKernelGGL(KERNEL<gact::kCompressBf16>, grid, block, lds, s, __VA_ARGS__); break; \
+            case gact::kCompressAny:  hipLaunchKernelGGL(KERNEL<gact::kCompressAny>, grid, block, lds, s, __VA_ARGS__); break;  \
+        }                                                                                                   \
+        return hipGetLastError() == hipSuccess ? 0 : -1;                                                    \
+    } while (0)
+
 extern "C" int gact_launch_single(int compress, const gact::TensorArgs* t, const gact::Geometry* geo,
                                   unsigned blocks, void* stream) {
-    hipStream_t s = (hipStream_t)stream;
-    const unsigned lds = compress ? 4u * gact::kWavesPerBlk * (unsigned)geo->lds_wave_dwords : 0u;
-    if (compress)
-        hipLaunchKernelGGL(gact::single_kernel<true>, dim3(blocks), dim3(gact::kBlockThreads), lds, s, *t, *geo);
-    else
-        hipLaunchKernelGGL(gact::single_kernel<false>, dim3(blocks), dim3(gact::kBlockThreads), lds, s, *t, *geo);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    GACT_LAUNCH(gact::single_kernel, *t, *geo);
 }
 
 extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::Geometry* geo,
@@ -847,28 +898,12 @@ extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::G
 
 extern "C" int gact_launch_multi_inline(int compress, const gact::InlineTable* tab,
                                         const gact::Geometry* geo, unsigned blocks, void* stream) {
-    hipStream_t s = (hipStream_t)stream;
-    const unsigned lds = compress ? 4u * gact::kWavesPerBlk * (unsigned)geo->lds_wave_dwords : 0u;
-    if (compress)
-        hipLaunchKernelGGL(gact::multi_inline_kernel<true>, dim3(blocks), dim3(gact::kBlockThreads), lds, s,
-                           *tab, *geo);
-    else
-        hipLaunchKernelGGL(gact::multi_inline_kernel<false>, dim3(blocks), dim3(gact::kBlockThreads), lds, s,
-                           *tab, *geo);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    GACT_LAUNCH(gact::multi_inline_kernel, *tab, *geo);
 }
 
 extern "C" int gact_launch_multi(int compress, const gact::TensorArgs* d_table,
                                  const uint32_t* d_first_block, const uint32_t* d_hint,
                                  unsigned hint_shift, const gact::Geometry* geo, unsigned blocks,
                                  void* stream) {
-    hipStream_t s = (hipStream_t)stream;
-    const unsigned lds = compress ? 4u * gact::kWavesPerBlk * (unsigned)geo->lds_wave_dwords : 0u;
-    if (compress)
-        hipLaunchKernelGGL(gact::multi_kernel<true>, dim3(blocks), dim3(gact::kBlockThreads), lds, s,
-                           d_table, d_first_block, d_hint, hint_shift, *geo);
-    else
-        hipLaunchKernelGGL(gact::multi_kernel<false>, dim3(blocks), dim3(gact::kBlockThreads), lds, s,
-                           d_table, d_first_block, d_hint, hint_shift, *geo);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    GACT_LAUNCH(gact::multi_kernel, d_table, d_first_block, d_hint, hint_shift, *geo);
 }

@@ -4,8 +4,10 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
+
 import synthetic_inputs as syn
-from test_gpu_parity import run_case
+from test_gpu_parity import run_case, to_device, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -47,3 +49,40 @@ def test_runs_of_neighbouring_blocks_per_xcd(gact, dtype, bits, blocks):
         assert torch.equal(mn, whole[1][a // G:a // G + mn.numel()]) and torch.equal(sc, whole[2][a // G:a // G + sc.numel()]), a
         assert torch.equal(gact.gact_decompress(p, mn, sc, m, G, bits, dtype=x.dtype).view(torch.uint8),
                            y[a:a + m].view(torch.uint8)), a
+
+
+@pytest.mark.parametrize("dtype", ("f32", "bf16"))
+def test_noise_across_a_wrap_of_the_low_counter_word(gact, dtype):
+    """Tiles before, at and after the point where the low word of the Philox block number wraps."""
+    G, bits, seed, n = 32, 4, 5, 9 * 2048 + 31
+    x = as_dtype(syn.draw_numpy(syn.NORMAL, n, 3), dtype)
+    xd = to_device(x)
+    for blocks_before in (256, 252, 260, 1024, 4, 508):
+        base = 8 * (2**32 - blocks_before)
+        p, mn, sc = gact.alloc_compressed(n, G, bits, "cuda")
+        descs = gact.make_descs([xd], [p], [mn], [sc], [None], [n], [bits], [seed], [xd.dtype], index_bases=[base])
+        gact.gact_compress_multi(descs, 1, G, torch.empty(gact.gact_multi_workspace_bytes(1), dtype=torch.uint8, device="cuda"))
+        p_ref, mn_ref, _ = oracle.compress_slice(x, G, bits, seed, base)
+        assert np.array_equal(to_host(p), p_ref), blocks_before
+        assert np.array_equal(to_host(mn).view(np.uint32), mn_ref.view(np.uint32)), blocks_before
+
+
+def test_one_launch_of_both_types_and_one_of_each(gact):
+    """A launch with fp32 tensors in it and one of bf16 alone are two kernels: the same bytes from both."""
+    G, seed = 128, 11
+    xs = [to_device(as_dtype(syn.draw_numpy(syn.RELU, n, n), d)) for n, d in
+          ((6000, "bf16"), (8192 + 7, "f32"), (4096, "bf16"), (2048 * 5, "f32"), (1, "bf16"))]
+    ws = torch.empty(gact.gact_multi_workspace_bytes(len(xs)), dtype=torch.uint8, device="cuda")
+
+    def launch(which, bits):
+        out = [gact.alloc_compressed(x.numel(), G, bits, "cuda") for x in which]
+        L = len(which)
+        descs = gact.make_descs(which, [o[0] for o in out], [o[1] for o in out], [o[2] for o in out], [None] * L,
+                                [x.numel() for x in which], [bits] * L, [seed] * L, [x.dtype for x in which])
+        gact.gact_compress_multi(descs, L, G, ws)
+        return {x.data_ptr(): o for x, o in zip(which, out)}
+    for bits in (1, 2, 4, 8):
+        both = launch(xs, bits)
+        for dt in (torch.float32, torch.bfloat16):
+            for ptr, out in launch([x for x in xs if x.dtype == dt], bits).items():
+                assert all(torch.equal(a, b) for a, b in zip(out, both[ptr])), (bits, dt)
