@@ -219,25 +219,25 @@ __device__ __forceinline__ float fmax3(float a, float b, float c) {
     return r;
 }
 
-// x[j] <- x[j] + b for eight values, rounded toward minus infinity.  The
+// x[j] <- x[j] + b[j % 4] for eight values, rounded toward minus infinity.  The
 // wavefront's binary32 rounding mode (MODE bits 1:0) is switched to round-down
 // for exactly these eight additions and back to nearest-even; the block is one
 // volatile statement, so no other floating-point instruction can be scheduled
 // into it and everything outside keeps the nearest-even contract.
-__device__ __forceinline__ void add8_round_down(float (&x)[8], float b) {
+__device__ __forceinline__ void add8_round_down(float (&x)[8], float b0, float b1, float b2, float b3) {
     asm volatile(
         "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 2\n\t"
-        "v_add_f32 %0, %0, %8\n\t"
-        "v_add_f32 %1, %1, %8\n\t"
-        "v_add_f32 %2, %2, %8\n\t"
-        "v_add_f32 %3, %3, %8\n\t"
-        "v_add_f32 %4, %4, %8\n\t"
-        "v_add_f32 %5, %5, %8\n\t"
-        "v_add_f32 %6, %6, %8\n\t"
-        "v_add_f32 %7, %7, %8\n\t"
+        "v_add_f32 %0, %8, %0\n\t"
+        "v_add_f32 %1, %9, %1\n\t"
+        "v_add_f32 %2, %10, %2\n\t"
+        "v_add_f32 %3, %11, %3\n\t"
+        "v_add_f32 %4, %8, %4\n\t"
+        "v_add_f32 %5, %9, %5\n\t"
+        "v_add_f32 %6, %10, %6\n\t"
+        "v_add_f32 %7, %11, %7\n\t"
         "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 0"
         : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7])
-        : "v"(b));
+        : "s"(b0), "s"(b1), "s"(b2), "s"(b3));
 }
 
 // Instructions the compiler does not select on its own.
@@ -247,16 +247,22 @@ __device__ __forceinline__ int32_t cvt_floor_i32(float x) {
     asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(x));
     return r;
 }
-// 2 * (low / high 16 bits of w) + c
-__device__ __forceinline__ uint32_t mad2_lo16(uint32_t w, uint32_t c) {
+// M * (low / high 16 bits of w) + c
+template <int M>
+__device__ __forceinline__ uint32_t mad_lo16(uint32_t w, uint32_t c) {
     uint32_t r;
-    asm("v_mad_u32_u16 %0, %1, 2, %2" : "=v"(r) : "v"(w), "v"(c));
+    asm("v_mad_u32_u16 %0, %1, %3, %2" : "=v"(r) : "v"(w), "v"(c), "n"(M));
     return r;
 }
-__device__ __forceinline__ uint32_t mad2_hi16(uint32_t w, uint32_t c) {
+template <int M>
+__device__ __forceinline__ uint32_t mad_hi16(uint32_t w, uint32_t c) {
     uint32_t r;
-    asm("v_mad_u32_u16 %0, %1, 2, %2 op_sel:[1,0,0,0]" : "=v"(r) : "v"(w), "v"(c));
+    asm("v_mad_u32_u16 %0, %1, %3, %2 op_sel:[1,0,0,0]" : "=v"(r) : "v"(w), "v"(c), "n"(M));
     return r;
+}
+// bits of a where m is set, of b elsewhere
+__device__ __forceinline__ uint32_t select_bits(uint32_t m, uint32_t a, uint32_t b) {
+    return __builtin_amdgcn_bitop3_b32(m, a, b, 0xCA);
 }
 
 // ------------------------------------------------------- tile <-> HBM moves
@@ -394,6 +400,39 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// range / (2^BITS - 1), correctly rounded, for range >= 2^-100: a product with the rounded reciprocal
+// and one fused correction (three instructions instead of the eleven of a general division).  Every
+// significand was compared with the division on the host for the divisors 3, 15 and 255; the result does
+// not depend on the exponent as long as the remainder (down to 2^-149) and the quotient are exact.
+template <int BITS>
+__device__ __forceinline__ float div_levels(float range) {
+    constexpr float Bf = (float)((1u << BITS) - 1u), r = 1.0f / Bf;
+    if (BITS == 1) return range;
+    const float q = range * r;
+    return __builtin_fmaf(__builtin_fmaf(-q, Bf, range), r, q);
+}
+
+// Eight 4-bit fields, each in bits 17..20 of its word, to one word: field k in bits 4k..4k+3.
+// Byte 2 of a word holds its field; three byte permutes gather four of them.
+__device__ __forceinline__ uint32_t gather_nibbles(const uint32_t (&n)[8]) {
+    uint32_t d[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        d[h] = __builtin_amdgcn_perm(n[2 + h], n[0 + h], 0x0C0C0602u);
+        d[h] = __builtin_amdgcn_perm(n[4 + h], d[h], 0x0C060100u);
+        d[h] = __builtin_amdgcn_perm(n[6 + h], d[h], 0x06020100u);
+    }
+    return select_bits(0x0F0F0F0Fu, d[0] >> 1, d[1] << 3);
+}
+
+// every BITS-wide field f of w replaced by -f modulo 2^BITS
+template <int BITS>
+__device__ __forceinline__ uint32_t negate_fields(uint32_t w) {
+    if (BITS == 1) return w;
+    constexpr uint32_t one = BITS == 2 ? 0x55555555u : 0x11111111u, top = one << (BITS - 1);
+    return ((~w & ~top) + one) ^ (~w & top);
+}
+
 // ----------------------------------------------------------------- compress
 // One wavefront compresses tile `tile` of tensor `t`.
 //   geo.lpg        lanes per group (G/32)
@@ -478,7 +517,7 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
     const float range = mx - mn;
     const float Bf = (float)B;
     float inv = 0.0f, step = 0.0f;
-    if (range >= 0x1p-100f) { inv = Bf / range; step = range / Bf; }
+    if (range >= 0x1p-100f) { inv = Bf / range; step = div_levels<BITS>(range); }
 
     // Minimum and step of every group of the tile.  All lanes of a group hold the
     // same pair.  Stored from the first lane of each group, the values would leave
@@ -504,26 +543,29 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
     // C = ceil(T) and c = C mod 2^17:  round up  <=>  2 frac 2^16 > 2r + 1
     // <=>  c >= 2r + 2  <=>  2r + 1 - C < -(floor(t) 2^17), hence
     //     -q = (2r + 1 - C) >> 17   (arithmetic shift).
-    // 1 - C = floor(-T) + 1 comes out of one addition rounded toward minus
-    // infinity: for |T| < 2^22 (codes of up to 4 bits: T <= 15 * 2^17 (1 + 2^-23))
-    // the sum -T + (1.5 * 2^23 + 1) lies in [2^23, 2^24), where binary32 has a
-    // spacing of 1, so its round-down value is 1.5 * 2^23 + 1 + floor(-T) exactly
-    // and its bit pattern is 0x4B400001 + floor(-T).  The 16-bit multiply-add
-    // that selects the noise half word adds 2r to that pattern, and because
-    // 0x4B400000 is a multiple of 2^17 the shift gives kBias - q with
-    // kBias = 0x4B400000 >> 17.  8-bit codes (T up to 2^25) use a
-    // convert-with-floor instead (kBias = 0).  The biased negated codes are
-    // accumulated last element first, one shift-add each, and the word is
-    // kBias * (sum of the field weights) - accumulator, all modulo 2^32.
+    // Codes of up to 4 bits: the same with everything scaled by 2^s, s = 0 .. 3:
+    //     -q = ((2r + 1) 2^s - C) >> (17 + s),   C = ceil(2^s T).
+    // 2^s - C = floor(-2^s T) + 2^s comes out of one addition rounded toward
+    // minus infinity: 2^s T < 2^22, so the sum -2^s T + (1.5 * 2^23 + 2^s) lies
+    // in [2^23, 2^24), where binary32 has a spacing of 1, and the bit pattern of
+    // its round-down value is 0x4B400000 + 2^s + floor(-2^s T).  The 16-bit
+    // multiply-add that selects the noise half word adds 2^(s+1) r, and because
+    // 0x4B400000 is a multiple of 2^22, bits 17+s .. 17+s+BITS-1 of the result
+    // hold -q modulo 2^BITS.  s = position in the nibble: the 1, 2 or 4 elements
+    // of a nibble land beside each other in bits 17..20 without a shift and are
+    // merged by bit selects; byte permutes put eight nibbles into a word.  (The
+    // shift and shift-add per element that this replaced issued at 2.5 and 4.1
+    // cycles a wavefront; now 1.4 instructions for a 4-bit element, 1.2 for a
+    // 2-bit one, 1 for a 1-bit one, where there were 2.)
+    // 8-bit codes (T up to 2^25) convert with floor, s = 0, and accumulate the
+    // negated codes last element first, one shift-add each.
     constexpr bool kMagic = BITS <= 4;
-    constexpr uint32_t kBias = kMagic ? (0x4B400000u >> 17) : 0u;
-    constexpr uint32_t kFieldWeights = BITS == 1 ? 0xFFFFFFFFu : BITS == 2 ? 0x55555555u
-                                     : BITS == 4 ? 0x11111111u : 0x01010101u;
-    constexpr uint32_t kBiasWord = kBias * kFieldWeights;          // modulo 2^32
-    uint32_t acc[BITS];
-#pragma unroll
-    for (int w = 0; w < BITS; ++w) acc[w] = 0u;
-    const float ninv17 = -(inv * 0x1p17f);
+    uint32_t out[BITS];
+    uint32_t nib[8];                                  // of the word under construction
+    constexpr int kPerNib = BITS <= 4 ? 4 / BITS : 1; // elements per nibble
+    const float ninv = -(inv * 0x1p17f);
+    const float ninv_s[4] = {ninv, ninv * (kPerNib == 2 ? 4.0f : 2.0f), kPerNib == 4 ? ninv * 4.0f : ninv,
+                             ninv * (kPerNib == 4 ? 8.0f : 4.0f)};
 #pragma unroll
     for (int c = 3; c >= 0; --c) {
         // valid elements from this lane's first on.  Opaque, so that the masks of the 32 comparisons
@@ -542,27 +584,53 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
         }
         float tn[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) tn[j] = (v[c * 8 + j] - mn) * ninv17;   // -T, T in [0, 2^25)
-        if (kMagic) add8_round_down(tn, 12582913.0f);                      // 1.5 * 2^23 + 1
+        for (int j = 0; j < 8; ++j)                                        // -2^s T
+            tn[j] = (v[c * 8 + j] - mn) * ninv_s[kPerNib == 4 ? j & 3 : kPerNib == 2 ? j & 1 : 0];
+        if (kMagic) {
+            constexpr float m = 12582912.0f;                               // 1.5 * 2^23
+            if (kPerNib == 1) add8_round_down(tn, m + 1.0f, m + 1.0f, m + 1.0f, m + 1.0f);
+            if (kPerNib == 2) add8_round_down(tn, m + 1.0f, m + 4.0f, m + 1.0f, m + 4.0f);
+            if (kPerNib == 4) add8_round_down(tn, m + 1.0f, m + 2.0f, m + 4.0f, m + 8.0f);
+            uint32_t y[8];
 #pragma unroll
-        for (int j = 7; j >= 0; --j) {
-            const int e = c * 8 + j;
-            const uint32_t n1 = kMagic ? __builtin_bit_cast(uint32_t, tn[j])
-                                       : (uint32_t)(cvt_floor_i32(tn[j]) + 1);     // (bias +) 1 - C
-            const uint32_t y = (j & 1) ? mad2_hi16(r[j >> 1], n1) : mad2_lo16(r[j >> 1], n1);
-            int32_t nq = (int32_t)y >> 17;                        // kBias - q
-            // t <= B (1 + 2^-23): an overshoot's fraction is below the smallest
-            // noise value 2^-17 unless B = 255, so only 8-bit codes can round
-            // past the top level
-            if (BITS == 8) nq = nq > -(int32_t)B ? nq : -(int32_t)B;
-            if (KIND == kEdge && e >= left) nq = (int32_t)kBias;
-            const int w = (e * BITS) >> 5;
-            acc[w] = (acc[w] << BITS) + (uint32_t)nq;
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t n1 = __builtin_bit_cast(uint32_t, tn[j]), w = r[j >> 1];
+                if (kPerNib == 1) y[j] = (j & 1) ? mad_hi16<2>(w, n1) : mad_lo16<2>(w, n1);
+                if (kPerNib == 2) y[j] = (j & 1) ? mad_hi16<8>(w, n1) : mad_lo16<2>(w, n1);
+                if (kPerNib == 4) y[j] = (j & 1) ? ((j & 2) ? mad_hi16<16>(w, n1) : mad_hi16<4>(w, n1))
+                                                 : ((j & 2) ? mad_lo16<8>(w, n1) : mad_lo16<2>(w, n1));
+                if (KIND == kEdge && c * 8 + j >= left) y[j] = 0u;
+            }
+            // nibbles of this chunk: 8 / kPerNib of them, at the chunk's place in the word
+            constexpr int kNibs = 8 / kPerNib;
+            const int n0 = (c * kNibs) & 7;
+#pragma unroll
+            for (int i = 0; i < kNibs; ++i) {
+                uint32_t a = y[i * kPerNib];
+                if (kPerNib == 2) a = select_bits(3u << 19, y[i * 2 + 1], a);
+                if (kPerNib == 4) {
+                    a = select_bits(1u << 18, y[i * 4 + 1], a);
+                    a = select_bits(1u << 20, y[i * 4 + 3], select_bits(1u << 19, y[i * 4 + 2], a));
+                }
+                nib[n0 + i] = a;
+            }
+            if (n0 == 0) out[c * kNibs / 8] = negate_fields<BITS>(gather_nibbles(nib));
+        } else {
+#pragma unroll
+            for (int j = 7; j >= 0; --j) {
+                const uint32_t n1 = (uint32_t)(cvt_floor_i32(tn[j]) + 1);      // 1 - C
+                const uint32_t y = (j & 1) ? mad_hi16<2>(r[j >> 1], n1) : mad_lo16<2>(r[j >> 1], n1);
+                int32_t nq = (int32_t)y >> 17;                                 // -q
+                // t <= B (1 + 2^-23): an overshoot's fraction is below the smallest noise value
+                // 2^-17 unless B = 255, so only 8-bit codes can round past the top level
+                nq = nq > -(int32_t)B ? nq : -(int32_t)B;
+                if (KIND == kEdge && c * 8 + j >= left) nq = 0;
+                const int w = (c * 8 + j) >> 2;
+                out[w] = ((j & 3) == 3 ? 0u : out[w] << 8) + (uint32_t)nq;
+                if ((j & 3) == 0) out[w] = 0u - out[w];
+            }
         }
     }
-    uint32_t out[BITS];
-#pragma unroll
-    for (int w = 0; w < BITS; ++w) out[w] = kBiasWord - acc[w];
 
     if (lane < geo.groups_per_tile && (KIND != kEdge || lane * geo.lpg * kPerLane < ne)) {
         float* gm = t.gmin + g0;                                   // uniform bases, lane offsets

@@ -86,3 +86,28 @@ def test_one_launch_of_both_types_and_one_of_each(gact):
         for dt in (torch.float32, torch.bfloat16):
             for ptr, out in launch([x for x in xs if x.dtype == dt], bits).items():
                 assert all(torch.equal(a, b) for a, b in zip(out, both[ptr])), (bits, dt)
+
+
+@pytest.mark.parametrize("dtype", ("f32", "bf16"))
+@pytest.mark.parametrize("bits", (1, 2, 4, 8))
+def test_every_code_in_every_place_of_a_word(gact, dtype, bits):
+    """Values on the quantizer's grid: each code at each place of a packed word, and values between
+    them, in full tiles and in a last one that ends inside a word."""
+    B, G = 2**bits - 1, 64
+    rng = np.random.default_rng(bits)
+    codes = rng.integers(0, B + 1, size=(64 * 2048) // G * G + 37).astype(np.float32)
+    codes[::G], codes[1::G] = 0.0, float(B)            # the group's range: a step of one
+    run_case(gact, as_dtype(codes, dtype), G, bits, seed=1)
+    run_case(gact, as_dtype(codes + rng.random(codes.size, dtype=np.float32) * np.float32(0.5), dtype), G, bits, seed=2)
+
+
+def test_steps_are_correctly_rounded(gact):
+    """range / (2^b - 1) for ranges of many significands and exponents, down to the smallest that has a step."""
+    rng = np.random.default_rng(4)
+    G = 32
+    expo = np.concatenate([rng.integers(-99, 126, 4000), np.full(500, -100), np.full(500, 126)])
+    top = np.ldexp(1.0 + rng.random(expo.size), expo).astype(np.float32)
+    x = np.zeros((expo.size, G), dtype=np.float32)
+    x[:, 5] = top
+    for bits in (1, 2, 4, 8):
+        run_case(gact, x.ravel(), G, bits, seed=bits)
