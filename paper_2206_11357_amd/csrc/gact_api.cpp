@@ -279,7 +279,8 @@ int compress_footprint(const void* d_x, gact_dtype dtype, int64_t n, int group_s
     if (rc != GACT_OK) return rc;
     if (n == 0)
         return gact_launch_zero(d_footprint, 1 + n_samples, stream) == 0 ? GACT_OK : GACT_E_HIP;
-    const size_t need = (size_t)tiles_for(n, geo) * sizeof(double);       // one partial sum per tile
+    // The documented size, a sum per tile; one per block of four tiles is used.
+    const size_t need = (size_t)tiles_for(n, geo) * sizeof(double);
     if (!d_workspace || !aligned(d_workspace, 16) || workspace_bytes < need)
         return limited ? GACT_E_SCRATCH : GACT_E_ARG;
     const int64_t blocks = blocks_for(true, t, geo);
@@ -288,7 +289,7 @@ int compress_footprint(const void* d_x, gact_dtype dtype, int64_t n, int group_s
     if (gact_launch_compress_sum(&t, &geo, (unsigned)blocks, (double*)d_workspace, stream) != 0)
         return GACT_E_HIP;
     const gact::ReduceArgs r{d_x, nullptr, n, (int32_t)dtype, 0};
-    return gact_launch_footprint_finish(&r, (unsigned)tiles_for(n, geo), (double*)d_workspace, n_samples,
+    return gact_launch_footprint_finish(&r, (unsigned)blocks, (double*)d_workspace, n_samples,
                                         d_footprint, stream) == 0 ? GACT_OK : GACT_E_HIP;
 }
 

@@ -437,12 +437,12 @@ __device__ __forceinline__ uint32_t negate_fields(uint32_t w) {
 // One wavefront compresses tile `tile` of tensor `t`.
 //   geo.lpg        lanes per group (G/32)
 //   geo.lanes_used lanes that hold data in a full tile (64 for power-of-two G)
-//   SUM            also write the binary64 sum of the tile's elements to tile_sum[tile]
-//                  (the footprint of Sec. 5.2 from the same read)
+//   SUM            also return the binary64 sum of the tile's elements in tile_sum (the
+//                  footprint of Sec. 5.2 from the same read)
 template <int DT, int BITS, TileKind KIND, bool SUM>
 __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometry& geo,
                                               int64_t tile, uint32_t* __restrict__ lds, int lane,
-                                              double* __restrict__ tile_sum) {
+                                              double& tile_sum) {
     constexpr uint32_t B = (1u << BITS) - 1u;
     const int tile_elems = geo.lanes_used * kPerLane;
     const int64_t e0 = tile * (int64_t)tile_elems;       // `tile` is uniform over the wavefront
@@ -486,13 +486,15 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
     const int my0 = lane * kPerLane;                 // first element of this lane in the tile
     if (SUM) {
         // lane: its 32 elements in index order; wavefront: xor butterfly 32, 16, ... 1
+        int left = ne - my0;
+        if (KIND == kEdge) asm volatile("" : "+v"(left));   // see the rounding loop
         double acc = 0.0;
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j)
-            if (KIND == kFull || my0 + j < ne) acc += (double)v[j];
+            if (KIND == kFull || j < left) acc += (double)v[j];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-        if (lane == 0) tile_sum[tile] = acc;
+        tile_sum = acc;
     }
 
     // group statistics
@@ -820,7 +822,7 @@ __device__ __forceinline__ uint32_t work_block(const Geometry& geo) {
 
 template <bool WITH_F32, bool SUM>
 __device__ __forceinline__ void compress_block(const TensorArgs& t, const Geometry& geo,
-                                               int64_t block_in_tensor, double* __restrict__ tile_sum) {
+                                               int64_t block_in_tensor, double& tile_sum) {
     // sized by the launcher: geo.lds_wave_dwords per wavefront
     extern __shared__ __attribute__((aligned(16))) uint32_t lds_all[];
     const int wave = threadIdx.x >> 6;
@@ -872,7 +874,10 @@ template <Work W>
 __device__ __forceinline__ void run_block(const TensorArgs& t, const Geometry& geo,
                                           int64_t block_in_tensor) {
     if constexpr (W == kDecompress) decompress_block(t, geo, block_in_tensor);
-    else compress_block<W == kCompressAny, false>(t, geo, block_in_tensor, nullptr);
+    else {
+        double unused;
+        compress_block<W == kCompressAny, false>(t, geo, block_in_tensor, unused);
+    }
 }
 
 #define GACT_KERNEL(W) \
@@ -883,10 +888,18 @@ GACT_KERNEL(W) single_kernel(TensorArgs t, Geometry geo) {
     run_block<W>(t, geo, (int64_t)work_block(geo));
 }
 
-// One tensor, compressed, with the sum of every tile as a by-product.
+// One tensor, compressed, with the sum of every block's elements as a by-product.  (One sum per block
+// and not per tile: the addition that follows reads a quarter of the terms, and the barrier costs
+// nothing, because a block's LDS is not given back before its last wavefront ends.)
 __global__ __launch_bounds__(kBlockThreads) void compress_sum_kernel(TensorArgs t, Geometry geo,
-                                                                     double* __restrict__ tile_sum) {
-    compress_block<true, true>(t, geo, (int64_t)work_block(geo), tile_sum);
+                                                                     double* __restrict__ block_sum) {
+    __shared__ double part[kWavesPerBlk];
+    const uint32_t b = work_block(geo);
+    double sum = 0.0;                                 // stays so for a wavefront past the end
+    compress_block<true, true>(t, geo, (int64_t)b, sum);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) block_sum[b] = (part[0] + part[1]) + (part[2] + part[3]);
 }
 
 // Multi-tensor: block b belongs to the tensor l with first_block[l] <= b <
@@ -957,10 +970,10 @@ extern "C" int gact_launch_single(int compress, const gact::TensorArgs* t, const
 }
 
 extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::Geometry* geo,
-                                        unsigned blocks, double* d_tile_sum, void* stream) {
+                                        unsigned blocks, double* d_block_sum, void* stream) {
     const unsigned lds = 4u * gact::kWavesPerBlk * (unsigned)geo->lds_wave_dwords;
     hipLaunchKernelGGL(gact::compress_sum_kernel, dim3(blocks), dim3(gact::kBlockThreads), lds,
-                       (hipStream_t)stream, *t, *geo, d_tile_sum);
+                       (hipStream_t)stream, *t, *geo, d_block_sum);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

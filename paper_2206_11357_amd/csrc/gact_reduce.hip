@@ -160,9 +160,7 @@ __global__ __launch_bounds__(kRedThreads) void sum_kernel(ReduceArgs r, double* 
 }
 
 // out[1 + j] = element floor(j * n / n_samples) as binary64
-__global__ void sample_kernel(ReduceArgs r, int n_samples, double* __restrict__ out) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n_samples) return;
+__device__ __forceinline__ void sample(const ReduceArgs& r, int j, int n_samples, double* __restrict__ out) {
     const int64_t i = (int64_t)(((unsigned __int128)(uint64_t)j * (uint64_t)r.n) / (uint64_t)n_samples);
     float v;
     if (r.dtype == GACT_DT_F32) v = ((const float*)r.a)[i];
@@ -249,12 +247,21 @@ __global__ __launch_bounds__(kRedThreads) void grad_stats_kernel(const ReduceArg
 // the terms t, t + 1024, ... eight at a time (eight independent loads in
 // flight), then the block adds the thread sums in a tree.  `stride` is the
 // distance between terms (1, or the chunk length after fold_kernel).
+// Blocks from `nout` on take a footprint's sample points, 1024 a block: they are
+// a few loads, and a kernel of their own took 4.5 us of a footprint's 47 on 51 M
+// fp32 elements.
 constexpr int kFinThreads = 1024;
 __global__ __launch_bounds__(kFinThreads) void finish_kernel(const double* __restrict__ partial,
                                                              uint32_t count, uint32_t stride,
                                                              size_t out_pitch, double scale,
-                                                             double* __restrict__ out) {
+                                                             double* __restrict__ out, uint32_t nout,
+                                                             ReduceArgs r, int n_samples) {
     __shared__ double lds[kFinThreads / 64];
+    if (blockIdx.x >= nout) {
+        const int j = (int)((blockIdx.x - nout) * kFinThreads + threadIdx.x);
+        if (j < n_samples) sample(r, j, n_samples, out);
+        return;
+    }
     const double* p = partial + (size_t)blockIdx.x * out_pitch;
     double acc = 0.0;
     uint32_t i = threadIdx.x;
@@ -290,20 +297,21 @@ __global__ __launch_bounds__(kRedThreads) void fold_kernel(double* __restrict__ 
     if (threadIdx.x == 0) p[0] = s;
 }
 
-// Enqueues the final addition of `count` terms for each of `nout` outputs.
+// Enqueues the final addition of `count` terms for each of `nout` outputs, and the sample points of r.
 static void launch_finish(double* d_partial, unsigned count, int nout, double scale, double* d_out,
-                          hipStream_t s) {
+                          hipStream_t s, const ReduceArgs& r = ReduceArgs{}, int n_samples = 0) {
     constexpr unsigned kFoldBlocks = 128;
+    const dim3 grid(nout + (n_samples + kFinThreads - 1) / kFinThreads);
     if (count <= 32768u) {
-        hipLaunchKernelGGL(finish_kernel, dim3(nout), dim3(kFinThreads), 0, s, d_partial, count, 1u,
-                           (size_t)count, scale, d_out);
+        hipLaunchKernelGGL(finish_kernel, grid, dim3(kFinThreads), 0, s, d_partial, count, 1u,
+                           (size_t)count, scale, d_out, (uint32_t)nout, r, n_samples);
         return;
     }
     const unsigned chunk = (count + kFoldBlocks - 1) / kFoldBlocks;
     const unsigned folded = (count + chunk - 1) / chunk;
     hipLaunchKernelGGL(fold_kernel, dim3(folded, nout), dim3(kRedThreads), 0, s, d_partial, count, chunk);
-    hipLaunchKernelGGL(finish_kernel, dim3(nout), dim3(kFinThreads), 0, s, d_partial, folded, chunk,
-                       (size_t)count, scale, d_out);
+    hipLaunchKernelGGL(finish_kernel, grid, dim3(kFinThreads), 0, s, d_partial, folded, chunk,
+                       (size_t)count, scale, d_out, (uint32_t)nout, r, n_samples);
 }
 
 }  // namespace gact
@@ -331,18 +339,15 @@ extern "C" int gact_launch_grad_stats(const gact::ReduceArgs* d_table, const uin
 // out[0 .. nout) = 0 through a kernel (no memset node, so callers may capture it)
 extern "C" int gact_launch_zero(double* d_out, int nout, void* stream) {
     hipLaunchKernelGGL(gact::finish_kernel, dim3(nout), dim3(gact::kFinThreads), 0, (hipStream_t)stream,
-                       (const double*)d_out, 0u, 1u, (size_t)0, 0.0, d_out);
+                       (const double*)d_out, 0u, 1u, (size_t)0, 0.0, d_out, (uint32_t)nout, gact::ReduceArgs{}, 0);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// The footprint from per-tile sums that a compress launch left in d_partial.
+// The footprint from per-block sums that a compress launch left in d_partial.
 extern "C" int gact_launch_footprint_finish(const gact::ReduceArgs* r, unsigned count, double* d_partial,
                                             int n_samples, double* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
-    gact::launch_finish(d_partial, count, 1, 1.0, d_out, s);
-    if (n_samples > 0)
-        hipLaunchKernelGGL(gact::sample_kernel, dim3((n_samples + 255) / 256), dim3(256), 0, s, *r,
-                           n_samples, d_out);
+    gact::launch_finish(d_partial, count, 1, 1.0, d_out, s, *r, n_samples);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -350,9 +355,6 @@ extern "C" int gact_launch_footprint(const gact::ReduceArgs* r, unsigned blocks,
                                      int n_samples, double* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(gact::sum_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, *r, d_partial);
-    gact::launch_finish(d_partial, blocks, 1, 1.0, d_out, s);
-    if (n_samples > 0)
-        hipLaunchKernelGGL(gact::sample_kernel, dim3((n_samples + 255) / 256), dim3(256), 0, s, *r,
-                           n_samples, d_out);
+    gact::launch_finish(d_partial, blocks, 1, 1.0, d_out, s, *r, n_samples);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }

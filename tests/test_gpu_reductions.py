@@ -1,0 +1,39 @@
+"""The reductions' launch forms at the sizes where one gives way to the next, against the oracle
+(arXiv 2206.11357: Alg. 1, the variance alert of Sec. 4.2, the footprint of Sec. 5.2)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synthetic_inputs as syn
+from test_gpu_sensitivity import REL, buffers, dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ("f32", "bf16"))
+def test_footprint_sums_per_block_and_samples_in_one_kernel(gact, dtype):
+    """Sizes around tiles and blocks of the fused call (wavefronts without a tile, group sizes that are no
+    power of two), no sample points, one, more than a block of them.  The terms are added in binary64 in
+    another order than the oracle's: at most about 60 roundings of 1.1e-16 relative to the sum of magnitudes."""
+    for k, (n, G, ns) in enumerate(((1, 32, 0), (2047, 64, 1), (2049, 96, 3), (8192, 256, 8), (8193, 256, 1024),
+                                    (8192 * 3 - 2048, 1024, 1025), (63 * 32 * 9, 96, 2049), (200001, 224, 5))):
+        x = syn.draw_numpy(syn.NORMAL, n, 900 + k)
+        x = syn.f32_to_bf16_bits(x) if dtype == "bf16" else x
+        p, mn, sc, fp = gact.gact_compress_footprint(dev(x), G, 4, 5 + k, ns)
+        p_ref, mn_ref, sc_ref = oracle.compress(x, G, 4, 5 + k)
+        want, got = oracle.footprint(x, ns), fp.cpu().numpy()
+        mag = float(np.abs(syn.bf16_bits_to_f32(x) if dtype == "bf16" else x).astype(np.float64).sum())
+        assert abs(got[0] - want[0]) <= 60 * 1.2e-16 * mag, n
+        assert np.array_equal(got[1:], want[1:]), n
+        assert np.array_equal(p.cpu().numpy(), p_ref) and np.array_equal(mn.cpu().numpy(), mn_ref), n
+        assert np.array_equal(sc.cpu().numpy(), sc_ref), n
+
+
+def test_footprint_of_more_blocks_than_one_addition_takes(gact):
+    n = 32769 * 4096 + 5
+    x = torch.arange(1024, device="cuda", dtype=torch.float32).repeat(n // 1024 + 1)[:n]
+    full, rest = divmod(n, 1024)
+    got = gact.gact_footprint(x, 7).cpu().numpy()
+    assert got[0] == full * (1023 * 512) + rest * (rest - 1) // 2            # integers: exact in binary64
+    assert np.array_equal(got[1:], [float((j * n // 7) % 1024) for j in range(7)])
