@@ -206,12 +206,22 @@ size_t reduce_table_bytes(int K) {
     return ((size_t)K * sizeof(gact::ReduceArgs) + (size_t)(K + 1) * sizeof(uint32_t) + 15) / 16 * 16;
 }
 
-// Builds and uploads the buffer table of a reduction launch.  On success
-// *blocks_out is the grid size, *d_partial the per-block result area behind
-// the table; returns 1 when there is nothing to reduce.
+// What a reduction launch reads and where it leaves its per-block results.
+struct Reduction {
+    int K = 0;                                    // buffers that are not empty; 0: nothing to reduce
+    unsigned blocks = 0;
+    gact::ReduceTable inline_table{};             // their table, when it fits the kernel arguments
+    bool is_inline = false;
+    const gact::ReduceArgs* d_table = nullptr;    // else uploaded to the workspace
+    const uint32_t* d_first = nullptr;
+    double* d_partial = nullptr;
+    const gact::ReduceTable* table() const { return is_inline ? &inline_table : nullptr; }
+};
+
+// Builds the buffer table of a reduction launch and uploads it unless it is small.  The per-block
+// results lie behind the table's place in the workspace either way.
 int stage_reduction(const std::vector<gact::ReduceArgs>& bufs, void* d_workspace,
-                    size_t workspace_bytes, int nout, void* stream, unsigned* blocks_out,
-                    const gact::ReduceArgs** d_table, const uint32_t** d_first, double** d_partial) {
+                    size_t workspace_bytes, int nout, void* stream, Reduction* red) {
     std::vector<gact::ReduceArgs> live;
     std::vector<uint32_t> first;
     uint64_t blocks = 0;
@@ -225,11 +235,20 @@ int stage_reduction(const std::vector<gact::ReduceArgs>& bufs, void* d_workspace
     }
     first.push_back((uint32_t)blocks);
     const int K = (int)live.size();
-    if (K == 0) return 1;
+    if (K == 0) return GACT_OK;
     const size_t tb = reduce_table_bytes(K);
     const size_t need = tb + (size_t)nout * blocks * sizeof(double);
     if (!d_workspace || !aligned(d_workspace, 16) || workspace_bytes < need) return GACT_E_ARG;
-    if (const int rc = refuse_if_capturing(stream)) return rc;
+    if (const int rc = refuse_if_capturing(stream)) return rc;      // for both kinds of table
+    red->K = K;
+    red->blocks = (unsigned)blocks;
+    red->d_partial = (double*)((unsigned char*)d_workspace + tb);
+    if (K <= gact::kInlineBuffers) {
+        std::memcpy(red->inline_table.t, live.data(), (size_t)K * sizeof(gact::ReduceArgs));
+        std::memcpy(red->inline_table.first_block, first.data(), first.size() * sizeof(uint32_t));
+        red->is_inline = true;
+        return GACT_OK;
+    }
     std::vector<unsigned char> image(tb);
     std::memcpy(image.data(), live.data(), (size_t)K * sizeof(gact::ReduceArgs));
     std::memcpy(image.data() + (size_t)K * sizeof(gact::ReduceArgs), first.data(),
@@ -238,10 +257,8 @@ int stage_reduction(const std::vector<gact::ReduceArgs>& bufs, void* d_workspace
     if (hipMemcpyAsync(d_workspace, image.data(), image.size(), hipMemcpyHostToDevice,
                        (hipStream_t)stream) != hipSuccess)
         return GACT_E_HIP;
-    *blocks_out = (unsigned)blocks;
-    *d_table = (const gact::ReduceArgs*)d_workspace;
-    *d_first = (const uint32_t*)((const unsigned char*)d_workspace + (size_t)K * sizeof(gact::ReduceArgs));
-    *d_partial = (double*)((unsigned char*)d_workspace + tb);
+    red->d_table = (const gact::ReduceArgs*)d_workspace;
+    red->d_first = (const uint32_t*)((const unsigned char*)d_workspace + (size_t)K * sizeof(gact::ReduceArgs));
     return GACT_OK;
 }
 
@@ -357,20 +374,13 @@ int gact_sensitivity(const gact_grad_pair* h_pairs, int K, int bits, double* d_o
         if (p.n > 0 && (!p.g0 || !p.g1 || !aligned(p.g0, 16) || !aligned(p.g1, 16))) return GACT_E_ARG;
         bufs.push_back(gact::ReduceArgs{p.g0, const_cast<void*>(p.g1), p.n, p.dtype, 0});
     }
-    unsigned blocks = 0;
-    const gact::ReduceArgs* d_table = nullptr;
-    const uint32_t* d_first = nullptr;
-    double* d_partial = nullptr;
-    const int rc = stage_reduction(bufs, d_workspace, workspace_bytes, 1, stream, &blocks, &d_table,
-                                   &d_first, &d_partial);
-    if (rc < 0) return rc;
-    if (rc == 1)     // nothing to reduce: the result is zero
+    Reduction red;
+    if (const int rc = stage_reduction(bufs, d_workspace, workspace_bytes, 1, stream, &red)) return rc;
+    if (red.K == 0)     // nothing to reduce: the result is zero
         return gact_launch_zero(d_out, 1, stream) == 0 ? GACT_OK : GACT_E_HIP;
     const double B = (double)((1 << bits) - 1);
-    const int live = (int)(((const unsigned char*)d_first - (const unsigned char*)d_table) /
-                           sizeof(gact::ReduceArgs));
-    return gact_launch_diff_sq(d_table, d_first, live, blocks, d_partial, 0.5 * B * B, d_out,
-                               stream) == 0 ? GACT_OK : GACT_E_HIP;
+    return gact_launch_diff_sq(red.table(), red.d_table, red.d_first, red.K, red.blocks, red.d_partial,
+                               0.5 * B * B, d_out, stream) == 0 ? GACT_OK : GACT_E_HIP;
 }
 
 int gact_grad_stats_update(const gact_grad_stat* h_stats, int K, int64_t t, double* d_out,
@@ -383,19 +393,12 @@ int gact_grad_stats_update(const gact_grad_stat* h_stats, int K, int64_t t, doub
         if (p.n > 0 && (!p.g || !p.mean || !aligned(p.g, 16) || !aligned(p.mean, 16))) return GACT_E_ARG;
         bufs.push_back(gact::ReduceArgs{p.g, p.mean, p.n, p.dtype, 0});
     }
-    unsigned blocks = 0;
-    const gact::ReduceArgs* d_table = nullptr;
-    const uint32_t* d_first = nullptr;
-    double* d_partial = nullptr;
-    const int rc = stage_reduction(bufs, d_workspace, workspace_bytes, 2, stream, &blocks, &d_table,
-                                   &d_first, &d_partial);
-    if (rc < 0) return rc;
-    if (rc == 1) return gact_launch_zero(d_out, 2, stream) == 0 ? GACT_OK : GACT_E_HIP;
-    const int live = (int)(((const unsigned char*)d_first - (const unsigned char*)d_table) /
-                           sizeof(gact::ReduceArgs));
+    Reduction red;
+    if (const int rc = stage_reduction(bufs, d_workspace, workspace_bytes, 2, stream, &red)) return rc;
+    if (red.K == 0) return gact_launch_zero(d_out, 2, stream) == 0 ? GACT_OK : GACT_E_HIP;
     const float rt = (float)(1.0 / (double)t);
-    return gact_launch_grad_stats(d_table, d_first, live, rt, blocks, d_partial, d_out, stream) == 0
-               ? GACT_OK : GACT_E_HIP;
+    return gact_launch_grad_stats(red.table(), red.d_table, red.d_first, red.K, rt, red.blocks,
+                                  red.d_partial, d_out, stream) == 0 ? GACT_OK : GACT_E_HIP;
 }
 
 int gact_footprint(const void* d_x, gact_dtype dtype, int64_t n, int n_samples, double* d_out,

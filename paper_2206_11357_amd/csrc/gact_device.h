@@ -94,6 +94,13 @@ struct ReduceArgs {
     int32_t     dtype;     // of a (and of b for sensitivity)
     int32_t     pad;
 };
+// A buffer table small enough to travel in the kernel arguments (4 KB limit).
+constexpr int kInlineBuffers = 104;
+struct ReduceTable {
+    ReduceArgs t[kInlineBuffers];
+    uint32_t   first_block[kInlineBuffers + 1];
+};
+
 // elements of one buffer a block covers: 256 threads x 4 pieces of 16 bytes
 constexpr int64_t reduce_chunk_elems(int dtype) { return dtype == GACT_DT_F32 ? 4096 : 8192; }
 
@@ -146,8 +153,9 @@ inline int run_shift_for(bool compress, uint64_t blocks) {
 
 extern "C" int gact_launch_single(int compress, const gact::TensorArgs* t,
                                   const gact::Geometry* geo, unsigned blocks, void* stream);
-extern "C" int gact_launch_diff_sq(const gact::ReduceArgs* d_table, const uint32_t* d_first, int K,
-                                   unsigned blocks, double* d_partial, double scale, double* d_out,
+// `inline_table` is used when it is not null, else the table in device memory
+extern "C" int gact_launch_diff_sq(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
+                                   const uint32_t* d_first, int K, unsigned blocks, double* d_partial, double scale, double* d_out,
                                    void* stream);
 extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::Geometry* geo,
                                         unsigned blocks, double* d_block_sum, void* stream);
@@ -156,8 +164,8 @@ extern "C" int gact_launch_footprint_finish(const gact::ReduceArgs* r, unsigned 
 extern "C" int gact_launch_footprint(const gact::ReduceArgs* r, unsigned blocks, double* d_partial,
                                      int n_samples, double* d_out, void* stream);
 extern "C" int gact_launch_zero(double* d_out, int nout, void* stream);
-extern "C" int gact_launch_grad_stats(const gact::ReduceArgs* d_table, const uint32_t* d_first, int K,
-                                      float rt, unsigned blocks, double* d_partial, double* d_out,
+extern "C" int gact_launch_grad_stats(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
+                                      const uint32_t* d_first, int K, float rt, unsigned blocks, double* d_partial, double* d_out,
                                       void* stream);
 extern "C" int gact_launch_copy(void* dst, const void* src, uint64_t nbytes, unsigned workgroups, void* stream);
 extern "C" int gact_launch_multi_inline(int compress, const gact::InlineTable* tab,

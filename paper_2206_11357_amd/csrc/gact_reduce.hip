@@ -107,14 +107,9 @@ __device__ __forceinline__ double diff_sq_chunk(const ReduceArgs& r, int64_t chu
     return acc;
 }
 
-__global__ __launch_bounds__(kRedThreads) void diff_sq_kernel(const ReduceArgs* __restrict__ table,
-                                                              const uint32_t* __restrict__ first_block,
-                                                              int K, double* __restrict__ partial) {
+__device__ __forceinline__ void diff_sq_block(const ReduceArgs& r, int64_t chunk, double* __restrict__ partial) {
     __shared__ double lds[4];
     const uint32_t b = blockIdx.x;
-    const int k = find_buffer(first_block, K, b);
-    const ReduceArgs r = table[k];
-    const int64_t chunk = (int64_t)(b - first_block[k]);
     const bool full = (chunk + 1) * reduce_chunk_elems(r.dtype) <= r.n;
     double acc;
     if (r.dtype == GACT_DT_F32)
@@ -123,6 +118,23 @@ __global__ __launch_bounds__(kRedThreads) void diff_sq_kernel(const ReduceArgs* 
         acc = full ? diff_sq_chunk<GACT_DT_BF16, true>(r, chunk) : diff_sq_chunk<GACT_DT_BF16, false>(r, chunk);
     const double s = block_sum(acc, lds);
     if (threadIdx.x == 0) partial[b] = s;
+}
+
+// Table in device memory (uploaded to the caller's workspace): any number of buffers.
+__global__ __launch_bounds__(kRedThreads) void diff_sq_kernel(const ReduceArgs* __restrict__ table,
+                                                              const uint32_t* __restrict__ first_block,
+                                                              int K, double* __restrict__ partial) {
+    const int k = find_buffer(first_block, K, blockIdx.x);
+    const ReduceArgs r = table[k];
+    diff_sq_block(r, (int64_t)(blockIdx.x - first_block[k]), partial);
+}
+
+// Table by value in the kernel arguments: no upload, which takes the stream 5 us
+// ahead of the kernel (96 bf16 pairs of 101 M elements: 67.8 us with, 65.6 us without).
+__global__ __launch_bounds__(kRedThreads) void diff_sq_inline_kernel(ReduceTable tab, int K,
+                                                                     double* __restrict__ partial) {
+    const int k = find_buffer(tab.first_block, K, blockIdx.x);
+    diff_sq_block(tab.t[k], (int64_t)(blockIdx.x - tab.first_block[k]), partial);
 }
 
 // ---------------------------------------------------------------- footprint
@@ -218,15 +230,10 @@ __device__ __forceinline__ void stats_chunk(const ReduceArgs& r, int64_t chunk, 
     }
 }
 
-__global__ __launch_bounds__(kRedThreads) void grad_stats_kernel(const ReduceArgs* __restrict__ table,
-                                                                 const uint32_t* __restrict__ first_block,
-                                                                 int K, float rt, uint32_t blocks,
-                                                                 double* __restrict__ partial) {
+__device__ __forceinline__ void grad_stats_block(const ReduceArgs& r, int64_t chunk, float rt, uint32_t blocks,
+                                                 double* __restrict__ partial) {
     __shared__ double lds[4];
     const uint32_t b = blockIdx.x;
-    const int k = find_buffer(first_block, K, b);
-    const ReduceArgs r = table[k];
-    const int64_t chunk = (int64_t)(b - first_block[k]);
     double sg2 = 0.0, sm2 = 0.0;
     const bool full = (chunk + 1) * reduce_chunk_elems(r.dtype) <= r.n;
     if (r.dtype == GACT_DT_F32) {
@@ -239,6 +246,22 @@ __global__ __launch_bounds__(kRedThreads) void grad_stats_kernel(const ReduceArg
     const double s0 = block_sum(sg2, lds);
     const double s1 = block_sum(sm2, lds);
     if (threadIdx.x == 0) { partial[b] = s0; partial[blocks + b] = s1; }
+}
+
+__global__ __launch_bounds__(kRedThreads) void grad_stats_kernel(const ReduceArgs* __restrict__ table,
+                                                                 const uint32_t* __restrict__ first_block,
+                                                                 int K, float rt, uint32_t blocks,
+                                                                 double* __restrict__ partial) {
+    const int k = find_buffer(first_block, K, blockIdx.x);
+    const ReduceArgs r = table[k];
+    grad_stats_block(r, (int64_t)(blockIdx.x - first_block[k]), rt, blocks, partial);
+}
+
+__global__ __launch_bounds__(kRedThreads) void grad_stats_inline_kernel(ReduceTable tab, int K, float rt,
+                                                                        uint32_t blocks,
+                                                                        double* __restrict__ partial) {
+    const int k = find_buffer(tab.first_block, K, blockIdx.x);
+    grad_stats_block(tab.t[k], (int64_t)(blockIdx.x - tab.first_block[k]), rt, blocks, partial);
 }
 
 // ------------------------------------------------------------ final addition
@@ -316,22 +339,30 @@ static void launch_finish(double* d_partial, unsigned count, int nout, double sc
 
 }  // namespace gact
 
-extern "C" int gact_launch_diff_sq(const gact::ReduceArgs* d_table, const uint32_t* d_first, int K,
-                                   unsigned blocks, double* d_partial, double scale, double* d_out,
-                                   void* stream) {
+extern "C" int gact_launch_diff_sq(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
+                                   const uint32_t* d_first, int K, unsigned blocks, double* d_partial,
+                                   double scale, double* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(gact::diff_sq_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, d_table, d_first,
-                       K, d_partial);
+    if (inline_table)
+        hipLaunchKernelGGL(gact::diff_sq_inline_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, *inline_table,
+                           K, d_partial);
+    else
+        hipLaunchKernelGGL(gact::diff_sq_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, d_table, d_first,
+                           K, d_partial);
     gact::launch_finish(d_partial, blocks, 1, scale, d_out, s);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-extern "C" int gact_launch_grad_stats(const gact::ReduceArgs* d_table, const uint32_t* d_first, int K,
-                                      float rt, unsigned blocks, double* d_partial, double* d_out,
-                                      void* stream) {
+extern "C" int gact_launch_grad_stats(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
+                                      const uint32_t* d_first, int K, float rt, unsigned blocks,
+                                      double* d_partial, double* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(gact::grad_stats_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, d_table,
-                       d_first, K, rt, blocks, d_partial);
+    if (inline_table)
+        hipLaunchKernelGGL(gact::grad_stats_inline_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s,
+                           *inline_table, K, rt, blocks, d_partial);
+    else
+        hipLaunchKernelGGL(gact::grad_stats_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, d_table,
+                           d_first, K, rt, blocks, d_partial);
     gact::launch_finish(d_partial, blocks, 2, 1.0, d_out, s);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }

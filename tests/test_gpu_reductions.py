@@ -37,3 +37,26 @@ def test_footprint_of_more_blocks_than_one_addition_takes(gact):
     got = gact.gact_footprint(x, 7).cpu().numpy()
     assert got[0] == full * (1023 * 512) + rest * (rest - 1) // 2            # integers: exact in binary64
     assert np.array_equal(got[1:], [float((j * n // 7) % 1024) for j in range(7)])
+
+
+@pytest.mark.parametrize("K", (103, 104, 105, 120))
+def test_tables_in_the_arguments_and_in_the_workspace(gact, K):
+    """The largest buffer list that travels in the kernel arguments, the smallest that is uploaded, and a
+    longer list of which enough are empty; both types in one list."""
+    sizes = [1 + (k * 977) % 9000 for k in range(K)]
+    if K == 120:
+        sizes[3:40:2] = [0] * len(sizes[3:40:2])
+    half = K // 2
+    g0 = buffers(sizes[:half], 10, "f32") + buffers(sizes[half:], 10, "bf16")
+    g1 = buffers(sizes[:half], 500, "f32") + buffers(sizes[half:], 500, "bf16")
+    got = gact.gact_sensitivity([dev(x) for x in g0], [dev(x) for x in g1], 2).item()
+    assert got == pytest.approx(oracle.sensitivity(g0, g1, 2), rel=REL)
+    means = [syn.draw_numpy(syn.NORMAL, n, 70 + k) if n else np.empty(0, np.float32) for k, n in enumerate(sizes)]
+    d_means = [dev(m) for m in means]
+    out = gact.gact_grad_stats_update([dev(x) for x in g0], d_means, 3).cpu().numpy()
+    want = np.zeros(2)
+    for g, m, d in zip(g0, means, d_means):
+        if g.size:
+            want += oracle.grad_stats_update(g, m, 3)
+            assert np.array_equal(d.cpu().numpy().view(np.uint32), m.view(np.uint32))
+    assert out == pytest.approx(want, rel=REL)
