@@ -104,6 +104,21 @@ int refuse_if_capturing(void* stream) {
     return status == hipStreamCaptureStatusNone ? GACT_OK : GACT_E_CAPTURE;
 }
 
+// Enqueues a copy of a launch table to the workspace; `src` may go when this returns (it is pageable
+// memory, of which the runtime takes its own copy first).  The runtime moves up to 16 KB with a small
+// kernel, 4.6 us of the stream, and more with the DMA engine, whose hand-over leaves the stream idle for
+// 18 to 20 us: tables of up to three such pieces (about 700 tensors) go piece by piece.  400 tensors, 28 KB:
+// compress 115 -> 106 us, decompress 131 -> 109 us (0.25 G bf16 elements).
+int upload(void* dst, const unsigned char* src, size_t bytes, void* stream) {
+    constexpr size_t kPiece = 16384;
+    const size_t piece = bytes <= 3 * kPiece ? kPiece : bytes;
+    for (size_t at = 0; at < bytes; at += piece)
+        if (hipMemcpyAsync((unsigned char*)dst + at, src + at, std::min(piece, bytes - at), hipMemcpyHostToDevice,
+                           (hipStream_t)stream) != hipSuccess)
+            return GACT_E_HIP;
+    return GACT_OK;
+}
+
 size_t table_bytes(int L) { return ((size_t)L * sizeof(gact::TensorArgs) + 15) / 16 * 16; }
 size_t first_bytes(int L) { return ((size_t)(L + 1) * sizeof(uint32_t) + 15) / 16 * 16; }
 
@@ -191,10 +206,7 @@ int run_multi(bool compress, const gact_tensor_desc* descs, int L, int group_siz
     std::memcpy(image.data(), table.data(), (size_t)live * sizeof(gact::TensorArgs));
     std::memcpy(image.data() + tb, first.data(), first.size() * sizeof(uint32_t));
     std::memcpy(image.data() + tb + fb, hint.data(), hint.size() * sizeof(uint32_t));
-    // pageable source: the runtime has taken its own copy when this returns
-    if (hipMemcpyAsync(d_workspace, image.data(), image.size(), hipMemcpyHostToDevice,
-                       (hipStream_t)stream) != hipSuccess)
-        return GACT_E_HIP;
+    if (const int rc = upload(d_workspace, image.data(), image.size(), stream)) return rc;
     const unsigned char* base = (const unsigned char*)d_workspace;
     return gact_launch_multi(compress ? 1 : 0, (const gact::TensorArgs*)base, (const uint32_t*)(base + tb),
                              (const uint32_t*)(base + tb + fb), shift, &geo, (unsigned)blocks,
@@ -253,10 +265,7 @@ int stage_reduction(const std::vector<gact::ReduceArgs>& bufs, void* d_workspace
     std::memcpy(image.data(), live.data(), (size_t)K * sizeof(gact::ReduceArgs));
     std::memcpy(image.data() + (size_t)K * sizeof(gact::ReduceArgs), first.data(),
                 first.size() * sizeof(uint32_t));
-    // pageable source: the runtime has taken its own copy when this returns
-    if (hipMemcpyAsync(d_workspace, image.data(), image.size(), hipMemcpyHostToDevice,
-                       (hipStream_t)stream) != hipSuccess)
-        return GACT_E_HIP;
+    if (const int rc = upload(d_workspace, image.data(), image.size(), stream)) return rc;
     red->d_table = (const gact::ReduceArgs*)d_workspace;
     red->d_first = (const uint32_t*)((const unsigned char*)d_workspace + (size_t)K * sizeof(gact::ReduceArgs));
     return GACT_OK;

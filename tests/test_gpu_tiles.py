@@ -111,3 +111,24 @@ def test_steps_are_correctly_rounded(gact):
     x[:, 5] = top
     for bits in (1, 2, 4, 8):
         run_case(gact, x.ravel(), G, bits, seed=bits)
+
+
+@pytest.mark.parametrize("L", (65, 215, 245, 430, 470, 640, 760))
+def test_tables_uploaded_in_one_piece_and_in_several(gact, L):
+    """Launch tables of 6 to 60 KB: one copy of up to 16 KB, two or three of them, one larger copy.  Each
+    tensor's bytes against the call for it alone."""
+    G, seed = 64, 3
+    x = torch.randn(L * 512, device="cuda", generator=torch.Generator("cuda").manual_seed(L)).to(torch.bfloat16)
+    xs = [x[l * 512:l * 512 + 1 + (l * 37) % 512] for l in range(L)]
+    bits = [(1, 2, 4, 8)[l % 4] for l in range(L)]
+    bufs = [gact.alloc_compressed(v.numel(), G, b, "cuda") for v, b in zip(xs, bits)]
+    ys = [torch.empty_like(v) for v in xs]
+    descs = gact.make_descs(xs, [b[0] for b in bufs], [b[1] for b in bufs], [b[2] for b in bufs], ys,
+                            [v.numel() for v in xs], bits, [seed + l for l in range(L)], [v.dtype for v in xs])
+    ws = torch.empty(gact.gact_multi_workspace_bytes(L), dtype=torch.uint8, device="cuda")
+    gact.gact_compress_multi(descs, L, G, ws)
+    gact.gact_decompress_multi(descs, L, G, ws)
+    for l, (v, b) in enumerate(zip(xs, bits)):
+        alone = gact.gact_compress(v, G, b, seed + l)
+        assert all(torch.equal(p, q) for p, q in zip(alone, bufs[l])), l
+        assert torch.equal(gact.gact_decompress(*alone, v.numel(), G, b, dtype=v.dtype), ys[l]), l
