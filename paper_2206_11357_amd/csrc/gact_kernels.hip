@@ -276,56 +276,51 @@ struct RawTile {
 //   kFull     2048 elements, group size a power of two
 //   kFullAny  lanes_used * 32 elements (44 to 63 lanes hold data), any group size;
 //             not the tensor's last tile
-//   kEdge     anything else: element-guarded loads and stores
+//   kEdge     anything else: the end of a tensor, or a tile in which the low word of
+//             the Philox block number wraps
 // Before kFullAny, all tiles of a group size that is no power of two were guarded
 // ones, whose branches per element and scan over the group's lanes made the launch
 // bound by instruction issue: 130 M fp32 elements, G = 96, 2 bits 90.6 -> 71.1 us
 // (4.7 -> 6.0 TB/s), 1.0 G bf16 elements, G = 224, 3 bits 779 -> 511 us.
 enum TileKind { kFull, kFullAny, kEdge };
 
-// Coalesced global loads.  `ne` = number of valid elements of the tile.  kEdge:
-// elements past `ne` are never read from memory and read 0.  kFullAny: the pieces
-// past `ne` (a multiple of 32) repeat the last one, which no HBM traffic follows.
+// element i of x as a 32-bit word (bf16 in the low half)
+template <int DT>
+__device__ __forceinline__ uint32_t load_element(const void* __restrict__ x, int64_t i) {
+    return DT == GACT_DT_F32 ? ((const uint32_t*)x)[i] : (uint32_t)((const uint16_t*)x)[i];
+}
+
+// Coalesced global loads.  `ne` = number of valid elements of the tile.  The pieces
+// that hold none of them repeat the last whole one, which no HBM traffic follows, so
+// that all loads go out without a branch between them; kEdge puts the piece that `ne`
+// cuts together from single elements (never read past `ne`), the same for all lanes.
 template <int DT, TileKind KIND>
 __device__ __forceinline__ void load_tile(const void* __restrict__ x, int64_t e0, int ne, int lane,
                                           RawTile<DT>& raw) {
-    if (DT == GACT_DT_F32) {
-        const uint32_t* p = (const uint32_t*)x + e0;
+    constexpr int P = DT == GACT_DT_F32 ? 4 : 8, kLoads = DT == GACT_DT_F32 ? 8 : 4;
+    const uint8_t* p = (const uint8_t*)x + e0 * (16 / P);
+    const int whole = KIND == kEdge ? ne & ~(P - 1) : ne;      // elements in whole pieces
+    if (KIND != kEdge || whole > 0) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            int e = k * 256 + lane * 4;
-            if (KIND == kFullAny) e = e < ne - 4 ? e : ne - 4;
-            if (KIND != kEdge) {
-                raw.r[k] = __builtin_nontemporal_load((const u4*)(p + e));
-            } else if (e + 4 <= ne) {
-                raw.r[k] = *(const u4*)(p + e);
-            } else {
-                u4 t = {0u, 0u, 0u, 0u};
-                if (e + 0 < ne) t.x = p[e + 0];
-                if (e + 1 < ne) t.y = p[e + 1];
-                if (e + 2 < ne) t.z = p[e + 2];
-                raw.r[k] = t;
-            }
+        for (int k = 0; k < kLoads; ++k) {
+            int e = (k * 64 + lane) * P;
+            if (KIND != kFull) e = e < whole - P ? e : whole - P;
+            raw.r[k] = __builtin_nontemporal_load((const u4*)(p + e * (16 / P)));
         }
     } else {
-        const uint16_t* p = (const uint16_t*)x + e0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            int e = k * 512 + lane * 8;
-            if (KIND == kFullAny) e = e < ne - 8 ? e : ne - 8;
-            if (KIND != kEdge) {
-                raw.r[k] = __builtin_nontemporal_load((const u4*)(p + e));
-            } else if (e + 8 <= ne) {
-                raw.r[k] = *(const u4*)(p + e);
-            } else {
-                uint32_t h[8];
+        for (int k = 0; k < kLoads; ++k) raw.r[k] = u4{0u, 0u, 0u, 0u};
+    }
+    if (KIND == kEdge && whole != ne) {
+        uint32_t h[P];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) h[j] = (e + j < ne) ? (uint32_t)p[e + j] : 0u;
-                u4 t = {h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
-                        h[6] | (h[7] << 16)};
-                raw.r[k] = t;
-            }
-        }
+        for (int j = 0; j < P; ++j) h[j] = load_element<DT>(x, e0 + (whole + j < ne ? whole + j : ne - 1));
+        u4 t;
+        if (DT == GACT_DT_F32) t = u4{h[0], h[1], h[2], h[3]};
+        else t = u4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4 % P] | (h[5 % P] << 16), h[6 % P] | (h[7 % P] << 16)};
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k)
+            if ((k * 64 + lane) * P == whole) raw.r[k] = t;
     }
 }
 
@@ -455,27 +450,30 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
     RawTile<DT> raw;
     load_tile<DT, KIND>(t.io, e0, ne, lane, raw);
 
+    uint32_t last_word = 0u;                         // the tile's last valid element
+    if (KIND == kEdge) last_word = load_element<DT>(t.io, e0 + ne - 1);
+
     // Noise of the lane's 32 elements, while the loads are in flight: block numbers
-    // tile_blk + 4 lane + (0..3).  The guarded instantiation draws it block by block further down.
+    // tile_blk + 4 lane + (0..3).
     const uint64_t tile_blk = t.blk_base() + ((uint64_t)e0 >> 3);
     // The key passes through an empty statement: otherwise the twenty round keys are computed once,
     // ahead of the switch over the instantiations, and spill to vector registers from there.
     uint32_t k0 = t.seed_lo, k1 = t.seed_hi;
     asm volatile("" : "+s"(k0), "+s"(k1));
-    // All four blocks for fp32; two for bf16, whose 64 registers hold no more without spilling.
-    constexpr int kEarly = DT == GACT_DT_F32 ? 4 : 2;
+    // All four blocks for fp32; two (one) for bf16, whose 64 registers hold no more without spilling.
+    constexpr int kEarly = DT == GACT_DT_F32 ? 4 : KIND == kEdge ? 1 : 2;
     uint32_t noise[4][4];
     const PhiloxUniform pu((uint32_t)(tile_blk >> 32), k0, k1);
     const uint32_t lane_c0 = (uint32_t)tile_blk + 4u * (uint32_t)lane;
-    if (KIND != kEdge) {
-        __builtin_amdgcn_sched_barrier(0);
+    const auto draw = [&](int c, uint32_t (&r)[4]) {
+        if (KIND == kEdge) philox_head_any(tile_blk + (uint64_t)(4 * lane + c), k0, k1, r);
+        else philox_head_uniform(lane_c0 + (uint32_t)c, pu, k0, k1, r);
+        philox_rounds<3>(r[0], r[1], r[2], r[3], k0, k1);
+    };
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int c = 4 - kEarly; c < 4; ++c) {
-            philox_head_uniform(lane_c0 + (uint32_t)c, pu, k0, k1, noise[c]);
-            philox_rounds<3>(noise[c][0], noise[c][1], noise[c][2], noise[c][3], k0, k1);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int c = 4 - kEarly; c < 4; ++c) draw(c, noise[c]);
+    __builtin_amdgcn_sched_barrier(0);
 
     // layout switch: coalesced rows in, 32 consecutive elements per lane out
     float v[kPerLane];
@@ -484,37 +482,35 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
     read_row<DT>(lds, lane, v);
 
     const int my0 = lane * kPerLane;                 // first element of this lane in the tile
+    const int left = ne - my0;                       // its valid elements, if fewer than 32
     if (SUM) {
         // lane: its 32 elements in index order; wavefront: xor butterfly 32, 16, ... 1
-        int left = ne - my0;
-        if (KIND == kEdge) asm volatile("" : "+v"(left));   // see the rounding loop
+        int left_here = left;                        // opaque: the 32 masks are not kept, they would spill
+        if (KIND == kEdge) asm volatile("" : "+v"(left_here));
         double acc = 0.0;
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j)
-            if (KIND == kFull || j < left) acc += (double)v[j];
+            if (KIND == kFull || j < left_here) acc += (double)v[j];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
         tile_sum = acc;
     }
 
-    // group statistics
-    float mn, mx;
-    if (KIND != kEdge) {
-        mn = fmin3(v[0], v[1], v[2]); mx = fmax3(v[0], v[1], v[2]);
+    // Places past the end take the last valid element: it belongs to the last group, whose minimum and
+    // maximum a copy does not change.  (Groups with no valid element at all are not stored.)
+    if (KIND == kEdge) {
+        const float last = __builtin_bit_cast(float, DT == GACT_DT_F32 ? last_word : last_word << 16);
 #pragma unroll
-        for (int j = 3; j + 1 < kPerLane; j += 2) { mn = fmin3(mn, v[j], v[j + 1]); mx = fmax3(mx, v[j], v[j + 1]); }
-        mn = fmin3(mn, v[kPerLane - 1], v[kPerLane - 1]); mx = fmax3(mx, v[kPerLane - 1], v[kPerLane - 1]);
-        if (KIND == kFull) group_minmax_pow2(mn, mx, geo.lpg);
-        else group_minmax_any(mn, mx, geo, lane);
-    } else {
-        mn = __builtin_inff(); mx = -__builtin_inff();
-#pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
-            if (my0 + j < ne) { mn = fmin2(mn, v[j]); mx = fmax2(mx, v[j]); }
-        }
-        if (geo.pow2) group_minmax_pow2(mn, mx, geo.lpg);
-        else group_minmax_any(mn, mx, geo, lane);
+        for (int j = 0; j < kPerLane; ++j) v[j] = j < left ? v[j] : last;
     }
+
+    // group statistics
+    float mn = fmin3(v[0], v[1], v[2]), mx = fmax3(v[0], v[1], v[2]);
+#pragma unroll
+    for (int j = 3; j + 1 < kPerLane; j += 2) { mn = fmin3(mn, v[j], v[j + 1]); mx = fmax3(mx, v[j], v[j + 1]); }
+    mn = fmin3(mn, v[kPerLane - 1], v[kPerLane - 1]); mx = fmax3(mx, v[kPerLane - 1], v[kPerLane - 1]);
+    if (KIND == kFull || (KIND == kEdge && geo.pow2)) group_minmax_pow2(mn, mx, geo.lpg);
+    else group_minmax_any(mn, mx, geo, lane);
     mn = mn + 0.0f;                                  // store -0 as +0
     const float range = mx - mn;
     const float Bf = (float)B;
@@ -570,20 +566,9 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
                              ninv * (kPerNib == 4 ? 8.0f : 4.0f)};
 #pragma unroll
     for (int c = 3; c >= 0; --c) {
-        // valid elements from this lane's first on.  Opaque, so that the masks of the 32 comparisons
-        // are not kept from the statistics above (they would fill the scalar registers and spill).
-        int left = ne - my0;
-        if (KIND == kEdge) asm volatile("" : "+v"(left));
         uint32_t r[4];
-        if (KIND == kEdge) {
-            philox_head_any(tile_blk + (uint64_t)(4 * lane + c), k0, k1, r);
-            philox_rounds<3>(r[0], r[1], r[2], r[3], k0, k1);
-        } else if (c < 4 - kEarly) {
-            philox_head_uniform(lane_c0 + (uint32_t)c, pu, k0, k1, r);
-            philox_rounds<3>(r[0], r[1], r[2], r[3], k0, k1);
-        } else {
-            r[0] = noise[c][0]; r[1] = noise[c][1]; r[2] = noise[c][2]; r[3] = noise[c][3];
-        }
+        if (c < 4 - kEarly) draw(c, r);
+        else { r[0] = noise[c][0]; r[1] = noise[c][1]; r[2] = noise[c][2]; r[3] = noise[c][3]; }
         float tn[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j)                                        // -2^s T
@@ -601,7 +586,6 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
                 if (kPerNib == 2) y[j] = (j & 1) ? mad_hi16<8>(w, n1) : mad_lo16<2>(w, n1);
                 if (kPerNib == 4) y[j] = (j & 1) ? ((j & 2) ? mad_hi16<16>(w, n1) : mad_hi16<4>(w, n1))
                                                  : ((j & 2) ? mad_lo16<8>(w, n1) : mad_lo16<2>(w, n1));
-                if (KIND == kEdge && c * 8 + j >= left) y[j] = 0u;
             }
             // nibbles of this chunk: 8 / kPerNib of them, at the chunk's place in the word
             constexpr int kNibs = 8 / kPerNib;
@@ -626,7 +610,6 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
                 // t <= B (1 + 2^-23): an overshoot's fraction is below the smallest noise value
                 // 2^-17 unless B = 255, so only 8-bit codes can round past the top level
                 nq = nq > -(int32_t)B ? nq : -(int32_t)B;
-                if (KIND == kEdge && c * 8 + j >= left) nq = 0;
                 const int w = (c * 8 + j) >> 2;
                 out[w] = ((j & 3) == 3 ? 0u : out[w] << 8) + (uint32_t)nq;
                 if ((j & 3) == 0) out[w] = 0u - out[w];
@@ -659,11 +642,17 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
             }
         }
     } else {
-        // the packed buffer ends at a multiple of 16 bytes; pad words are zero
+        // the packed buffer ends at a multiple of 16 bytes; places past the end and pad words are zero
         const int64_t words_total = packed_words(t);
+        int bits_left = ne - lane * kPerLane;                      // not carried through the rounding loop
+        asm volatile("" : "+v"(bits_left));
+        bits_left *= BITS;
 #pragma unroll
-        for (int w = 0; w < BITS; ++w)
-            if (lane < geo.lanes_used && word0 + w < words_total) pk[w] = out[w];
+        for (int w = 0; w < BITS; ++w) {
+            const int valid = bits_left - 32 * w;                     // bits of this word that hold codes
+            const uint32_t mask = valid >= 32 ? 0xFFFFFFFFu : valid <= 0 ? 0u : (1u << valid) - 1u;
+            if (lane < geo.lanes_used && word0 + w < words_total) pk[w] = out[w] & mask;
+        }
         // when a tile is narrower than 128*8/BITS elements' worth of padding
         // (group sizes that are not a power of two), up to three pad words lie
         // past the last tile's lanes: the last tile zeroes them

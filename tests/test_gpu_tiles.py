@@ -132,3 +132,17 @@ def test_tables_uploaded_in_one_piece_and_in_several(gact, L):
         alone = gact.gact_compress(v, G, b, seed + l)
         assert all(torch.equal(p, q) for p, q in zip(alone, bufs[l])), l
         assert torch.equal(gact.gact_decompress(*alone, v.numel(), G, b, dtype=v.dtype), ys[l]), l
+
+
+@pytest.mark.parametrize("dtype", ("f32", "bf16"))
+@pytest.mark.parametrize("G", (32, 96, 128, 704, 1024))
+def test_last_tiles_that_end_anywhere(gact, dtype, G):
+    """The last tile with 1 to 17 elements, around whole 16-byte pieces, groups, lanes and the tile's end,
+    alone and behind a full tile."""
+    lanes = G // 32
+    tile = 64 // lanes * G
+    ends = (1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, G - 1, G, G + 1, tile - 9, tile - 8, tile - 7, tile - 4, tile - 1)
+    for k, m in enumerate(ends):
+        n = m + tile * (k % 2)
+        x = as_dtype(syn.draw_numpy(syn.NORMAL, n, 7 * G + k) + np.float32(3), dtype)
+        run_case(gact, x, G, (1, 2, 4, 8)[(k + lanes) % 4], seed=k)
