@@ -232,14 +232,15 @@ struct Reduction {
 
 // Builds the buffer table of a reduction launch and uploads it unless it is small.  The per-block
 // results lie behind the table's place in the workspace either way.
-int stage_reduction(const std::vector<gact::ReduceArgs>& bufs, void* d_workspace,
-                    size_t workspace_bytes, int nout, void* stream, Reduction* red) {
+int stage_reduction(const std::vector<gact::ReduceArgs>& bufs, bool statistics, void* d_workspace,
+                    size_t workspace_bytes, void* stream, Reduction* red) {
+    const int nout = statistics ? 2 : 1;
     std::vector<gact::ReduceArgs> live;
     std::vector<uint32_t> first;
     uint64_t blocks = 0;
     for (const gact::ReduceArgs& r : bufs) {
         if (r.n == 0) continue;
-        const int64_t chunk = gact::reduce_chunk_elems(r.dtype);
+        const int64_t chunk = statistics ? gact::kStatsChunkElems : gact::reduce_chunk_elems(r.dtype);
         first.push_back((uint32_t)blocks);
         live.push_back(r);
         blocks += (uint64_t)((r.n + chunk - 1) / chunk);
@@ -384,7 +385,7 @@ int gact_sensitivity(const gact_grad_pair* h_pairs, int K, int bits, double* d_o
         bufs.push_back(gact::ReduceArgs{p.g0, const_cast<void*>(p.g1), p.n, p.dtype, 0});
     }
     Reduction red;
-    if (const int rc = stage_reduction(bufs, d_workspace, workspace_bytes, 1, stream, &red)) return rc;
+    if (const int rc = stage_reduction(bufs, false, d_workspace, workspace_bytes, stream, &red)) return rc;
     if (red.K == 0)     // nothing to reduce: the result is zero
         return gact_launch_zero(d_out, 1, stream) == 0 ? GACT_OK : GACT_E_HIP;
     const double B = (double)((1 << bits) - 1);
@@ -403,7 +404,7 @@ int gact_grad_stats_update(const gact_grad_stat* h_stats, int K, int64_t t, doub
         bufs.push_back(gact::ReduceArgs{p.g, p.mean, p.n, p.dtype, 0});
     }
     Reduction red;
-    if (const int rc = stage_reduction(bufs, d_workspace, workspace_bytes, 2, stream, &red)) return rc;
+    if (const int rc = stage_reduction(bufs, true, d_workspace, workspace_bytes, stream, &red)) return rc;
     if (red.K == 0) return gact_launch_zero(d_out, 2, stream) == 0 ? GACT_OK : GACT_E_HIP;
     const float rt = (float)(1.0 / (double)t);
     return gact_launch_grad_stats(red.table(), red.d_table, red.d_first, red.K, rt, red.blocks,

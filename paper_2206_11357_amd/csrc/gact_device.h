@@ -101,8 +101,10 @@ struct ReduceTable {
     uint32_t   first_block[kInlineBuffers + 1];
 };
 
-// elements of one buffer a block covers: 256 threads x 4 pieces of 16 bytes
+// Elements of one buffer a block covers: 512 threads x 2 pieces, of 16 bytes where the buffers are only
+// read, of 4 elements in a statistics step (16 bytes of the fp32 mean, whatever the gradient's type).
 constexpr int64_t reduce_chunk_elems(int dtype) { return dtype == GACT_DT_F32 ? 4096 : 8192; }
+constexpr int64_t kStatsChunkElems = 4096;
 
 // Decompress launch shape.  A unit is the 1 KB of output one coalesced
 // wavefront store covers (256 fp32 or 512 bf16 elements); a block of four
