@@ -146,10 +146,17 @@ def dtype_code(dtype: torch.dtype) -> int:
         raise TypeError("gact handles float32 and bfloat16 tensors, got %s" % dtype) from None
 
 
+# The current stream's handle without a Stream object around it: 0.4 us a call instead of 2.7 us, on calls
+# of which the launch itself takes the host 3 us.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
     """hipStream_t as an integer: None = torch's current stream; a torch stream; or the integer itself
     (a call site that issues many calls resolves the stream once and passes the handle)."""
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if type(stream) is int:
         return stream
@@ -316,12 +323,12 @@ def gact_reduce_workspace_bytes(K: int, total_elems: int) -> int:
 
 
 def _reduce_workspace(tensors, workspace):
-    total = sum(int(t.numel()) for t in tensors)
-    need = gact_reduce_workspace_bytes(len(tensors), total)
-    if workspace is None:
-        dev = tensors[0].device if tensors else torch.device("cuda")
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
-    return workspace
+    """The caller's workspace, or one of the size that the buffers need (the library checks either)."""
+    if workspace is not None:
+        return workspace
+    need = gact_reduce_workspace_bytes(len(tensors), sum(int(t.numel()) for t in tensors))
+    dev = tensors[0].device if tensors else torch.device("cuda")
+    return torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
 
 
 def make_grad_pairs(g0: Sequence[torch.Tensor], g1: Sequence[torch.Tensor]):
@@ -359,7 +366,7 @@ def gact_sensitivity(g0: Sequence[torch.Tensor], g1: Sequence[torch.Tensor], bit
     `pairs` (from make_grad_pairs) skips re-marshalling the buffer list."""
     K = len(g0)
     arr = pairs if pairs is not None else make_grad_pairs(g0, g1)
-    workspace = _reduce_workspace(list(g0), workspace)
+    workspace = _reduce_workspace(g0, workspace)
     if out is None:
         out = torch.empty(1, dtype=torch.float64, device=workspace.device)
     rc = lib.gact_sensitivity(ctypes.addressof(arr), K, bits, out.data_ptr(), workspace.data_ptr(),
@@ -375,7 +382,7 @@ def gact_grad_stats_update(g: Sequence[torch.Tensor], mean: Sequence[torch.Tenso
     """Running-mean step t over gradient buffers -> device float64[2] = (sum g^2, sum mean^2)."""
     K = len(g)
     arr = stats if stats is not None else make_grad_stats(g, mean)
-    workspace = _reduce_workspace(list(g), workspace)
+    workspace = _reduce_workspace(g, workspace)
     if out is None:
         out = torch.empty(2, dtype=torch.float64, device=workspace.device)
     rc = lib.gact_grad_stats_update(ctypes.addressof(arr), K, t, out.data_ptr(), workspace.data_ptr(),

@@ -60,3 +60,11 @@ def test_tables_in_the_arguments_and_in_the_workspace(gact, K):
             want += oracle.grad_stats_update(g, m, 3)
             assert np.array_equal(d.cpu().numpy().view(np.uint32), m.view(np.uint32))
     assert out == pytest.approx(want, rel=REL)
+
+
+def test_calls_without_a_stream_go_to_the_current_one(gact):
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        assert gact._stream(None) == s.cuda_stream
+    assert gact._stream(None) == torch.cuda.current_stream().cuda_stream
+    assert gact._stream(s) == s.cuda_stream and gact._stream(7) == 7
