@@ -469,10 +469,10 @@ def live_traffic(workload: str):
                     continue
                 if "vectorized_elementwise_kernel" in name and "_add<" in name and val > 100000:      # the reference kernel
                     ref.append(val)
-                elif "gact::multi" in name and "<true>" in name:
-                    comp.append(val)
-                elif "gact::multi" in name and "<false>" in name:
+                elif "gact::multi" in name and "Work)0>" in name:          # gact::kDecompress
                     dec.append(val)
+                elif "gact::multi" in name:                                # kCompressBf16, kCompressAny
+                    comp.append(val)
             if not ref or not comp or not dec:
                 return None
             scale = gib / (sum(ref) / len(ref) * 1024.0)        # true bytes per counted byte
@@ -611,7 +611,7 @@ def bench_single_1m(steps, warmup, gact, torch, np, dev) -> dict:
                      "pct_hbm_peak": round(100 * alg / cm / 1e3 / HBM_PEAK_GBPS, 2)},
         "decompress": {"us_per_call_median": round(dm, 2), "us_per_call_min": round(float(d_us.min()), 2),
                        "pct_hbm_peak": round(100 * alg / dm / 1e3 / HBM_PEAK_GBPS, 2)},
-        "roofline": {"bound": "hbm", "kernel": "gact::single_kernel<true>", "achieved": round(alg / cm / 1e3, 1),
+        "roofline": {"bound": "hbm", "kernel": "gact::single_kernel<kCompressAny>", "achieved": round(alg / cm / 1e3, 1),
                      "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(alg / cm / 1e3 / HBM_PEAK_GBPS, 4),
                      "traffic": None},
     }
