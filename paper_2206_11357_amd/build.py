@@ -21,6 +21,7 @@ FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950",
     "-ffp-contract=off",                 # the contract rounds every operation on its own
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-kernarg-preload-count=9",     # leading scalar arguments arrive in registers
     "-fPIC", "-shared", "-fvisibility=default",
     "-Wall", "-Wno-unused-command-line-argument",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,

@@ -47,9 +47,12 @@ struct Geometry {
     int32_t group_size;
     int32_t group_shift;   // log2(group_size) when pow2
     int32_t lpg_magic;     // floor(65536 / lpg) + 1: lane / lpg = lane * lpg_magic >> 16 for lane < 64
-    int32_t run_shift;     // log2 of the neighbouring blocks one XCD takes in a run (run_shift_for), 0: plain order
+    int32_t run_shift;     // log2 of the neighbouring blocks one XCD takes in a run (set_runs)
+    uint32_t run_end;      // blocks in whole windows of eight runs; 0: plain order
     int32_t lds_wave_dwords;   // compress: LDS dwords per wavefront (lds_dwords_per_wave of the widest dtype launched)
+    int32_t pad[3];        // a launch table behind two dwords and this starts on a 64-byte line
 };
+static_assert(sizeof(Geometry) == 56, "two dwords and the geometry fill a line of the kernel arguments");
 
 // LDS one compressing wavefront stages its tile in: 64 rows of 32 elements in
 // the input's own format.
@@ -149,6 +152,11 @@ inline int run_shift_for(bool compress, uint64_t blocks) {
     while ((blocks >> log2) > 1) ++log2;
     if (compress) return log2 < 13 ? 0 : (log2 - 9 < 8 ? log2 - 9 : 8);
     return log2 < 14 ? 0 : 5;
+}
+
+inline void set_runs(Geometry* geo, bool compress, uint64_t blocks) {
+    geo->run_shift = run_shift_for(compress, blocks);
+    geo->run_end = geo->run_shift ? (uint32_t)(blocks >> (3 + geo->run_shift) << (3 + geo->run_shift)) : 0u;
 }
 
 }  // namespace gact

@@ -801,11 +801,15 @@ __device__ __forceinline__ void decompress_units(const TensorArgs& t, const Geom
 // leaves two caches as two partial writes, and one that two blocks read is
 // fetched twice.  Within a window of 8 * 2^s workgroups, XCD x therefore takes
 // the 2^s neighbouring blocks x * 2^s ...; what does not fill a window keeps
-// plain order.  s is geo.run_shift, chosen by the launcher.
-__device__ __forceinline__ uint32_t work_block(const Geometry& geo) {
-    const uint32_t b = blockIdx.x, s = (uint32_t)geo.run_shift;
+// plain order.  s and run_end, the first block past the last whole window (0:
+// plain order), come from the launcher as the kernel's first two arguments, which
+// the build has preloaded into scalar registers: from memory they put another
+// scalar load in front of every block's lookup and first loads, and cost short
+// launches up to 2 % (fp32 decompress of 0.7 G elements 0.5 %).
+__device__ __forceinline__ uint32_t work_block(uint32_t run_end, uint32_t s) {
+    const uint32_t b = blockIdx.x;
+    if (b >= run_end) return b;
     const uint32_t window = b >> (3 + s) << (3 + s);
-    if (s == 0u || window + (8u << s) > gridDim.x) return b;
     return window | ((b & 7u) << s) | ((b - window) >> 3);
 }
 
@@ -873,17 +877,17 @@ __device__ __forceinline__ void run_block(const TensorArgs& t, const Geometry& g
     __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(waves_per_simd(W), waves_per_simd(W)))) void
 
 template <Work W>
-GACT_KERNEL(W) single_kernel(TensorArgs t, Geometry geo) {
-    run_block<W>(t, geo, (int64_t)work_block(geo));
+GACT_KERNEL(W) single_kernel(uint32_t run_end, uint32_t run_shift, TensorArgs t, Geometry geo) {
+    run_block<W>(t, geo, (int64_t)work_block(run_end, run_shift));
 }
 
 // One tensor, compressed, with the sum of every block's elements as a by-product.  (One sum per block
 // and not per tile: the addition that follows reads a quarter of the terms, and the barrier costs
 // nothing, because a block's LDS is not given back before its last wavefront ends.)
-__global__ __launch_bounds__(kBlockThreads) void compress_sum_kernel(TensorArgs t, Geometry geo,
-                                                                     double* __restrict__ block_sum) {
+__global__ __launch_bounds__(kBlockThreads) void compress_sum_kernel(uint32_t run_end, uint32_t run_shift, TensorArgs t,
+                                                                     Geometry geo, double* __restrict__ block_sum) {
     __shared__ double part[kWavesPerBlk];
-    const uint32_t b = work_block(geo);
+    const uint32_t b = work_block(run_end, run_shift);
     double sum = 0.0;                                 // stays so for a wavefront past the end
     compress_block<true, true>(t, geo, (int64_t)b, sum);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
@@ -911,9 +915,9 @@ __device__ __forceinline__ int find_tensor(const uint32_t* first_block, const ui
 // Table in device memory (the caller's workspace): any number of tensors.
 template <Work W>
 GACT_KERNEL(W) multi_kernel(
-    const TensorArgs* __restrict__ table, const uint32_t* __restrict__ first_block,
+    uint32_t run_end, uint32_t run_shift, const TensorArgs* __restrict__ table, const uint32_t* __restrict__ first_block,
     const uint32_t* __restrict__ hint, uint32_t hint_shift, Geometry geo) {
-    const uint32_t b = work_block(geo);
+    const uint32_t b = work_block(run_end, run_shift);
     const int l = find_tensor<false>(first_block, hint, hint_shift, b);
     const TensorArgs t = table[l];
     run_block<W>(t, geo, (int64_t)(b - first_block[l]));
@@ -923,8 +927,8 @@ GACT_KERNEL(W) multi_kernel(
 // no upload and no host synchronisation before the launch.
 template <Work W>
 GACT_KERNEL(W) multi_inline_kernel(
-    InlineTable tab, Geometry geo) {
-    const uint32_t b = work_block(geo);
+    uint32_t run_end, uint32_t run_shift, Geometry geo, InlineTable tab) {
+    const uint32_t b = work_block(run_end, run_shift);
     const int l = find_tensor<true>(tab.first_block, tab.hint, tab.hint_shift, b);
     run_block<W>(tab.t[l], geo, (int64_t)(b - tab.first_block[l]));
 }
@@ -955,25 +959,25 @@ gact::Work work_of(int compress, const gact::Geometry* geo) {
 
 extern "C" int gact_launch_single(int compress, const gact::TensorArgs* t, const gact::Geometry* geo,
                                   unsigned blocks, void* stream) {
-    GACT_LAUNCH(gact::single_kernel, *t, *geo);
+    GACT_LAUNCH(gact::single_kernel, geo->run_end, (uint32_t)geo->run_shift, *t, *geo);
 }
 
 extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::Geometry* geo,
                                         unsigned blocks, double* d_block_sum, void* stream) {
     const unsigned lds = 4u * gact::kWavesPerBlk * (unsigned)geo->lds_wave_dwords;
     hipLaunchKernelGGL(gact::compress_sum_kernel, dim3(blocks), dim3(gact::kBlockThreads), lds,
-                       (hipStream_t)stream, *t, *geo, d_block_sum);
+                       (hipStream_t)stream, geo->run_end, (uint32_t)geo->run_shift, *t, *geo, d_block_sum);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 extern "C" int gact_launch_multi_inline(int compress, const gact::InlineTable* tab,
                                         const gact::Geometry* geo, unsigned blocks, void* stream) {
-    GACT_LAUNCH(gact::multi_inline_kernel, *tab, *geo);
+    GACT_LAUNCH(gact::multi_inline_kernel, geo->run_end, (uint32_t)geo->run_shift, *geo, *tab);
 }
 
 extern "C" int gact_launch_multi(int compress, const gact::TensorArgs* d_table,
                                  const uint32_t* d_first_block, const uint32_t* d_hint,
                                  unsigned hint_shift, const gact::Geometry* geo, unsigned blocks,
                                  void* stream) {
-    GACT_LAUNCH(gact::multi_kernel, d_table, d_first_block, d_hint, hint_shift, *geo);
+    GACT_LAUNCH(gact::multi_kernel, geo->run_end, (uint32_t)geo->run_shift, d_table, d_first_block, d_hint, hint_shift, *geo);
 }
