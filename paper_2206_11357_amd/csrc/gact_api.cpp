@@ -34,14 +34,11 @@ gact::Geometry make_geometry(int group_size) {
     geo.lpg = group_size / kPerLane;
     geo.lanes_used = (64 / geo.lpg) * geo.lpg;
     geo.pow2 = (geo.lpg & (geo.lpg - 1)) == 0 ? 1 : 0;
-    geo.lpg_shift = 0;
-    while ((1 << (geo.lpg_shift + 1)) <= geo.lpg) ++geo.lpg_shift;
     geo.groups_per_tile = geo.lanes_used / geo.lpg;
     geo.group_size = group_size;
-    geo.group_shift = geo.lpg_shift + 5;
+    geo.group_shift = 5;
+    while ((32 << (geo.group_shift - 4)) <= group_size) ++geo.group_shift;
     geo.lpg_magic = 65536 / geo.lpg + 1;
-    geo.run_shift = 0;            // set per launch from its number of blocks
-    geo.run_end = 0;
     geo.lds_wave_dwords = 0;      // set per launch from the dtypes in it
     return geo;
 }
@@ -88,11 +85,10 @@ int64_t blocks_for(bool compress, const gact::TensorArgs& t, const gact::Geometr
     return (t.n + span - 1) / span;
 }
 
-int run_single(bool compress, const gact::TensorArgs& t, gact::Geometry geo, void* stream) {
+int run_single(bool compress, const gact::TensorArgs& t, const gact::Geometry& geo, void* stream) {
     if (t.n == 0) return GACT_OK;
     const int64_t blocks = blocks_for(compress, t, geo);
     if (blocks > 0x7FFFFFFFll) return GACT_E_ARG;
-    gact::set_runs(&geo, compress, (uint64_t)blocks);
     return gact_launch_single(compress ? 1 : 0, &t, &geo, (unsigned)blocks, stream) == 0
                ? GACT_OK : GACT_E_HIP;
 }
@@ -179,7 +175,6 @@ int run_multi(bool compress, const gact_tensor_desc* descs, int L, int group_siz
     const int live = (int)table.size();
     if (live == 0) return GACT_OK;
     first.push_back((uint32_t)blocks);
-    gact::set_runs(&geo, compress, blocks);
 
     if (!d_workspace || !aligned(d_workspace, 16) ||
         workspace_bytes < gact_multi_workspace_bytes(L))
@@ -313,7 +308,6 @@ int compress_footprint(const void* d_x, gact_dtype dtype, int64_t n, int group_s
         return limited ? GACT_E_SCRATCH : GACT_E_ARG;
     const int64_t blocks = blocks_for(true, t, geo);
     if (blocks > 0x7FFFFFFFll) return GACT_E_ARG;
-    gact::set_runs(&geo, true, (uint64_t)blocks);
     if (gact_launch_compress_sum(&t, &geo, (unsigned)blocks, (double*)d_workspace, stream) != 0)
         return GACT_E_HIP;
     const gact::ReduceArgs r{d_x, nullptr, n, (int32_t)dtype, 0};

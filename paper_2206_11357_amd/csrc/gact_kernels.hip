@@ -801,8 +801,8 @@ __device__ __forceinline__ void decompress_units(const TensorArgs& t, const Geom
 // leaves two caches as two partial writes, and one that two blocks read is
 // fetched twice.  Within a window of 8 * 2^s workgroups, XCD x therefore takes
 // the 2^s neighbouring blocks x * 2^s ...; what does not fill a window keeps
-// plain order.  s and run_end, the first block past the last whole window (0:
-// plain order), come from the launcher as the kernel's first two arguments, which
+// plain order.  s and run_end, the first block past the last whole window (Runs;
+// 0: plain order), come from the launcher as the kernel's first two arguments, which
 // the build has preloaded into scalar registers: from memory they put another
 // scalar load in front of every block's lookup and first loads, and cost short
 // launches up to 2 % (fp32 decompress of 0.7 G elements 0.5 %).
@@ -927,7 +927,8 @@ GACT_KERNEL(W) multi_kernel(
 // no upload and no host synchronisation before the launch.
 template <Work W>
 GACT_KERNEL(W) multi_inline_kernel(
-    uint32_t run_end, uint32_t run_shift, Geometry geo, InlineTable tab) {
+    uint32_t run_end, uint32_t run_shift, LineGeometry line, InlineTable tab) {
+    const Geometry& geo = line.geo;
     const uint32_t b = work_block(run_end, run_shift);
     const int l = find_tensor<true>(tab.first_block, tab.hint, tab.hint_shift, b);
     run_block<W>(tab.t[l], geo, (int64_t)(b - tab.first_block[l]));
@@ -946,6 +947,7 @@ gact::Work work_of(int compress, const gact::Geometry* geo) {
 // KERNEL<work>, launched on `blocks` blocks with the LDS its work needs
 #define GACT_LAUNCH(KERNEL, ...)                                                                            \
     do {                                                                                                    \
+        const gact::Runs runs = gact::runs_for(compress != 0, blocks);                                      \
         const dim3 grid(blocks), block(gact::kBlockThreads);                                                \
         const unsigned lds = compress ? 4u * gact::kWavesPerBlk * (unsigned)geo->lds_wave_dwords : 0u;      \
         hipStream_t s = (hipStream_t)stream;                                                                \
@@ -959,25 +961,27 @@ gact::Work work_of(int compress, const gact::Geometry* geo) {
 
 extern "C" int gact_launch_single(int compress, const gact::TensorArgs* t, const gact::Geometry* geo,
                                   unsigned blocks, void* stream) {
-    GACT_LAUNCH(gact::single_kernel, geo->run_end, (uint32_t)geo->run_shift, *t, *geo);
+    GACT_LAUNCH(gact::single_kernel, runs.end, runs.shift, *t, *geo);
 }
 
 extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::Geometry* geo,
                                         unsigned blocks, double* d_block_sum, void* stream) {
     const unsigned lds = 4u * gact::kWavesPerBlk * (unsigned)geo->lds_wave_dwords;
+    const gact::Runs runs = gact::runs_for(true, blocks);
     hipLaunchKernelGGL(gact::compress_sum_kernel, dim3(blocks), dim3(gact::kBlockThreads), lds,
-                       (hipStream_t)stream, geo->run_end, (uint32_t)geo->run_shift, *t, *geo, d_block_sum);
+                       (hipStream_t)stream, runs.end, runs.shift, *t, *geo, d_block_sum);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 extern "C" int gact_launch_multi_inline(int compress, const gact::InlineTable* tab,
                                         const gact::Geometry* geo, unsigned blocks, void* stream) {
-    GACT_LAUNCH(gact::multi_inline_kernel, geo->run_end, (uint32_t)geo->run_shift, *geo, *tab);
+    const gact::LineGeometry line{*geo, {}};
+    GACT_LAUNCH(gact::multi_inline_kernel, runs.end, runs.shift, line, *tab);
 }
 
 extern "C" int gact_launch_multi(int compress, const gact::TensorArgs* d_table,
                                  const uint32_t* d_first_block, const uint32_t* d_hint,
                                  unsigned hint_shift, const gact::Geometry* geo, unsigned blocks,
                                  void* stream) {
-    GACT_LAUNCH(gact::multi_kernel, geo->run_end, (uint32_t)geo->run_shift, d_table, d_first_block, d_hint, hint_shift, *geo);
+    GACT_LAUNCH(gact::multi_kernel, runs.end, runs.shift, d_table, d_first_block, d_hint, hint_shift, *geo);
 }
