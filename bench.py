@@ -52,7 +52,7 @@ HBM_PEAK_GBPS = 8000.0       # MI355X HBM3E, published
 # instructions issue at half of it.
 VALU_PEAK_LANE_OPS = 256 * 128 * 2.4e9
 # VALU instructions per element of the compress kernel, from SQ_INSTS_VALU x 64 / elements (profiles/)
-COMPRESS_VALU_PER_ELEMENT = {"f32": 14.9, "bf16": 15.7}
+COMPRESS_VALU_PER_ELEMENT = {"f32": 13.2, "bf16": 14.0}
 
 WORKLOADS = {
     # name: (set builder, group size, average bits, sensitivity seed, uniform bits, description)
