@@ -186,11 +186,10 @@ int run_multi(bool compress, const gact_tensor_desc* descs, int L, int group_siz
         std::memset(&tab, 0, sizeof(tab));
         std::memcpy(tab.t, table.data(), (size_t)live * sizeof(gact::TensorArgs));
         std::memcpy(tab.first_block, first.data(), first.size() * sizeof(uint32_t));
-        tab.L = live;
         std::vector<uint8_t> hint;
-        tab.hint_shift = make_hints(first, gact::kInlineHints, &hint);
+        const unsigned shift = make_hints(first, gact::kInlineHints, &hint);
         for (size_t k = 0; k < hint.size(); ++k) tab.hint[k >> 2] |= (uint32_t)hint[k] << ((k & 3) * 8);
-        return gact_launch_multi_inline(compress ? 1 : 0, &tab, &geo, (unsigned)blocks, stream) == 0
+        return gact_launch_multi_inline(compress ? 1 : 0, &tab, shift, &geo, (unsigned)blocks, stream) == 0
                    ? GACT_OK : GACT_E_HIP;
     }
 

@@ -51,11 +51,12 @@ struct Geometry {
 // The single-tensor kernels' arguments stay below 112 bytes: from 120 on, the runtime takes the host 0.6 us
 // longer per launch (3.1 -> 3.7 us), which is what bounds small calls.
 static_assert(sizeof(TensorArgs) + sizeof(Geometry) + 16 <= 112, "arguments of the single-tensor kernels");
-// the geometry in front of a launch table that starts on a 64-byte line, behind two dwords
+// the geometry in front of a launch table that starts on a 64-byte line, behind three dwords
 struct LineGeometry {
     Geometry geo;
-    int32_t  pad[6];
+    int32_t  pad[5];
 };
+static_assert(12 + sizeof(LineGeometry) == 64, "the launch table starts on a line");
 
 // How blocks are dealt to the XCDs (work_block, runs_for).
 struct Runs {
@@ -88,8 +89,6 @@ constexpr int kInlineTensors = 64;
 struct InlineTable {
     TensorArgs t[kInlineTensors];
     uint32_t   first_block[kInlineTensors + 1];
-    int32_t    L;
-    uint32_t   hint_shift;
     uint32_t   hint[kInlineHints / 4 + 1];   // one byte per bucket, four to a dword (scalar loads fetch dwords)
 };
 // tensor of bucket k in a byte-packed hint array
@@ -133,8 +132,14 @@ constexpr int64_t kStatsChunkElems = 4096;
 //   b=8      694  -  665   -       665  -  556   -       724  -  664   -       700  -  645   -
 // A launch of 53 fp32 tensors of mixed widths around 2 bits, 89 M elements: 65.3 us
 // with four units at 2 bits, 66.7 with three.
+// The units of 1-, 2-, 4- and 8-bit codes, three bits of a constant each at 3 * bits: a
+// block computes its length from them without a branch.
+constexpr uint32_t dec_unit_table(uint32_t b1, uint32_t b2, uint32_t b4, uint32_t b8) {
+    return b1 << 3 | b2 << 6 | b4 << 12 | b8 << 24;
+}
+constexpr uint32_t kDecUnitsF32 = dec_unit_table(3, 4, 2, 2), kDecUnitsBf16 = dec_unit_table(3, 3, 2, 2);
 constexpr int dec_units_per_wave(int dtype, int bits) {
-    return bits == 1 ? 3 : bits == 2 ? (dtype == GACT_DT_F32 ? 4 : 3) : 2;
+    return (int)((dtype == GACT_DT_F32 ? kDecUnitsF32 : kDecUnitsBf16) >> (3 * bits) & 7u);
 }
 constexpr int dec_block_elems(int dtype, int bits) {
     return 4 * dec_units_per_wave(dtype, bits) * (dtype == GACT_DT_F32 ? 256 : 512);
@@ -153,14 +158,15 @@ constexpr int dec_block_elems(int dtype, int bits) {
 //   decompress 400 bf16 tensors, 49k blocks     133    129    128    127    127    130    129
 //   decompress 3 fp32 tensors, 32k blocks      76.2   73.7   73.5   73.8   74.5   75.3   77.9
 //   decompress 1 bf16 tensor, 1.8k blocks      4.85    --    5.35
-// Compress: runs as long as leave 64 windows, at most 256 blocks.  Decompress: runs of 32 (runs of 4 to 16 cost up to 10 % on bf16 output at 4 bits, and lengths that are
-// no power of two are worse than 32 throughout).  Launches of few windows keep plain order: the XCDs that
-// get the runs of a last, partial window finish late.
+// Compress: runs as long as leave 64 windows, at most 256 blocks.  Decompress: runs of 32 (runs of 4 to 16
+// cost up to 10 % on bf16 output at 4 bits, and lengths that are no power of two are worse than 32 throughout).
+// Launches of few windows keep plain order: the XCDs that get the runs of a last, partial window finish late.
+constexpr uint32_t kDecompressRunShift = 5;
 inline int run_shift_for(bool compress, uint64_t blocks) {
     int log2 = 0;
     while ((blocks >> log2) > 1) ++log2;
     if (compress) return log2 < 13 ? 0 : (log2 - 9 < 8 ? log2 - 9 : 8);
-    return log2 < 14 ? 0 : 5;
+    return log2 < 14 ? 0 : (int)kDecompressRunShift;
 }
 
 inline Runs runs_for(bool compress, uint64_t blocks) {
@@ -187,7 +193,7 @@ extern "C" int gact_launch_grad_stats(const gact::ReduceTable* inline_table, con
                                       const uint32_t* d_first, int K, float rt, unsigned blocks, double* d_partial, double* d_out,
                                       void* stream);
 extern "C" int gact_launch_copy(void* dst, const void* src, uint64_t nbytes, unsigned workgroups, void* stream);
-extern "C" int gact_launch_multi_inline(int compress, const gact::InlineTable* tab,
+extern "C" int gact_launch_multi_inline(int compress, const gact::InlineTable* tab, unsigned hint_shift,
                                         const gact::Geometry* geo, unsigned blocks, void* stream);
 extern "C" int gact_launch_multi(int compress, const gact::TensorArgs* d_table,
                                  const uint32_t* d_first_block, const uint32_t* d_hint,

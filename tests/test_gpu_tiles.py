@@ -146,3 +146,22 @@ def test_last_tiles_that_end_anywhere(gact, dtype, G):
         n = m + tile * (k % 2)
         x = as_dtype(syn.draw_numpy(syn.NORMAL, n, 7 * G + k) + np.float32(3), dtype)
         run_case(gact, x, G, (1, 2, 4, 8)[(k + lanes) % 4], seed=k)
+
+
+@pytest.mark.parametrize("dtype", ("f32", "bf16"))
+@pytest.mark.parametrize("bits", (1, 2, 4, 8))
+def test_last_blocks_of_the_decompressor(gact, dtype, bits):
+    """24,576 elements are whole blocks for every block length in use (2048 to 8192): a last block that is
+    full, one element short, one element long, alone and in a launch of several tensors."""
+    G, ns = 128, (24576, 24575, 24577, 1, 2 * 24576)
+    for k, n in enumerate(ns):
+        run_case(gact, as_dtype(syn.draw_numpy(syn.NORMAL, n, 60 + k), dtype), G, bits, seed=k)
+    xs = [to_device(as_dtype(syn.draw_numpy(syn.NORMAL, n, 60 + k), dtype)) for k, n in enumerate(ns)]
+    bufs = [gact.gact_compress(x, G, bits, k) for k, x in enumerate(xs)]
+    ys = [torch.zeros_like(x) for x in xs]
+    descs = gact.make_descs(xs, [b[0] for b in bufs], [b[1] for b in bufs], [b[2] for b in bufs], ys, ns,
+                            [bits] * len(ns), list(range(len(ns))), [x.dtype for x in xs])
+    gact.gact_decompress_multi(descs, len(ns), G, torch.empty(gact.gact_multi_workspace_bytes(len(ns)), dtype=torch.uint8,
+                                                              device="cuda"))
+    for n, b, x, y in zip(ns, bufs, xs, ys):
+        assert torch.equal(gact.gact_decompress(*b, n, G, bits, dtype=x.dtype), y), n
