@@ -469,7 +469,7 @@ def live_traffic(workload: str):
                     continue
                 if "vectorized_elementwise_kernel" in name and "_add<" in name and val > 100000:      # the reference kernel
                     ref.append(val)
-                elif "gact::multi" in name and "Work)0>" in name:          # gact::kDecompress
+                elif "gact::multi" in name and ("Work)0>" in name or "Work)3>" in name):      # kDecompress, kDecompressShort
                     dec.append(val)
                 elif "gact::multi" in name:                                # kCompressBf16, kCompressAny
                     comp.append(val)

@@ -79,16 +79,18 @@ int make_args(bool compress, const void* x, void* packed, float* gmin, float* gs
 
 // blocks a tensor needs: compress takes 4 wavefront tiles per block, decompress
 // a fixed span of elements per block
-int64_t blocks_for(bool compress, const gact::TensorArgs& t, const gact::Geometry& geo) {
+int64_t blocks_for(bool compress, const gact::TensorArgs& t, const gact::Geometry& geo,
+                   uint32_t bf16_units = gact::kDecUnitsBf16) {
     if (compress) return (tiles_for(t.n, geo) + kWavesPerBlock - 1) / kWavesPerBlock;
-    const int64_t span = gact::dec_block_elems(t.dtype(), t.bits());
+    const int64_t span = gact::dec_block_elems(t.dtype(), t.bits(), bf16_units);
     return (t.n + span - 1) / span;
 }
 
 int run_single(bool compress, const gact::TensorArgs& t, const gact::Geometry& geo, void* stream) {
     if (t.n == 0) return GACT_OK;
-    const int64_t blocks = blocks_for(compress, t, geo);
+    int64_t blocks = blocks_for(compress, t, geo);
     if (blocks > 0x7FFFFFFFll) return GACT_E_ARG;
+    if (!compress && blocks < (int64_t)gact::kShortLaunch) blocks = blocks_for(compress, t, geo, gact::kDecUnitsBf16Short);
     return gact_launch_single(compress ? 1 : 0, &t, &geo, (unsigned)blocks, stream) == 0
                ? GACT_OK : GACT_E_HIP;
 }
@@ -174,6 +176,13 @@ int run_multi(bool compress, const gact_tensor_desc* descs, int L, int group_siz
     }
     const int live = (int)table.size();
     if (live == 0) return GACT_OK;
+    if (!compress && blocks < gact::kShortLaunch) {
+        blocks = 0;
+        for (int l = 0; l < live; ++l) {
+            first[l] = (uint32_t)blocks;
+            blocks += (uint64_t)blocks_for(compress, table[l], geo, gact::kDecUnitsBf16Short);
+        }
+    }
     first.push_back((uint32_t)blocks);
 
     if (!d_workspace || !aligned(d_workspace, 16) ||

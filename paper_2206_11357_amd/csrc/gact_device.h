@@ -131,18 +131,26 @@ constexpr int64_t kStatsChunkElems = 4096;
 //   b=4      716 539 702  98       554 431 524  76       638 422 559  73       584 445 571  78
 //   b=8      694  -  665   -       665  -  556   -       724  -  664   -       700  -  645   -
 // A launch of 53 fp32 tensors of mixed widths around 2 bits, 89 M elements: 65.3 us
-// with four units at 2 bits, 66.7 with three.
-// The units of 1-, 2-, 4- and 8-bit codes, three bits of a constant each at 3 * bits: a
+// with four units at 2 bits, 66.7 with three.  bf16 at 2 bits takes four as well where
+// the launch is shorter than kShortLaunch blocks (us, one tensor; lists of 3 to 100
+// tensors cross at the same size, 48 M elements or 7.8k blocks):
+//   M elements    4    7.5    12    16    24    32    48    64   100   160
+//   three       3.7   4.9   7.0   8.4  11.6  14.7  20.5  26.4  39.5  61.7
+//   four        3.5   4.2   6.5   8.5  11.3  14.5  20.7  26.7  40.3  62.2
+// The units of 1-, 2-, 4- and 8-bit codes, three bits of a table each at 3 * bits: a
 // block computes its length from them without a branch.
 constexpr uint32_t dec_unit_table(uint32_t b1, uint32_t b2, uint32_t b4, uint32_t b8) {
     return b1 << 3 | b2 << 6 | b4 << 12 | b8 << 24;
 }
-constexpr uint32_t kDecUnitsF32 = dec_unit_table(3, 4, 2, 2), kDecUnitsBf16 = dec_unit_table(3, 3, 2, 2);
-constexpr int dec_units_per_wave(int dtype, int bits) {
-    return (int)((dtype == GACT_DT_F32 ? kDecUnitsF32 : kDecUnitsBf16) >> (3 * bits) & 7u);
-}
-constexpr int dec_block_elems(int dtype, int bits) {
-    return 4 * dec_units_per_wave(dtype, bits) * (dtype == GACT_DT_F32 ? 256 : 512);
+constexpr uint32_t kDecUnitsF32 = dec_unit_table(3, 4, 2, 2);
+constexpr uint32_t kDecUnitsBf16 = dec_unit_table(3, 3, 2, 2), kDecUnitsBf16Short = dec_unit_table(3, 4, 2, 2);
+// blocks, counted with kDecUnitsBf16 (the count with kDecUnitsBf16Short is never larger, so that either
+// tells which of the two a launch uses)
+constexpr uint64_t kShortLaunch = 8192;
+constexpr int dec_units(uint32_t table, int bits) { return (int)(table >> (3 * bits) & 7u); }
+// elements of a block; bf16_units: the table of bf16 tensors
+constexpr int dec_block_elems(int dtype, int bits, uint32_t bf16_units) {
+    return dtype == GACT_DT_F32 ? 4 * 256 * dec_units(kDecUnitsF32, bits) : 4 * 512 * dec_units(bf16_units, bits);
 }
 
 // Length of the runs of neighbouring blocks that go to one XCD, as a power of two

@@ -845,14 +845,15 @@ __device__ __forceinline__ void compress_block(const TensorArgs& t, const Geomet
 }
 
 // full: every element of the block's span exists
+template <uint32_t BF16_UNITS>
 __device__ __forceinline__ void decompress_block(const TensorArgs& t, const Geometry& geo,
                                                  int64_t block_in_tensor, bool full) {
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
 #define GACT_D_FULL(DT, BITS) \
-    decompress_units<DT, BITS, false, dec_units_per_wave(DT, BITS)>(t, geo, block_in_tensor, wave, lane);
+    decompress_units<DT, BITS, false, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS)>(t, geo, block_in_tensor, wave, lane);
 #define GACT_D_EDGE(DT, BITS) \
-    decompress_units<DT, BITS, true, dec_units_per_wave(DT, BITS)>(t, geo, block_in_tensor, wave, lane);
+    decompress_units<DT, BITS, true, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS)>(t, geo, block_in_tensor, wave, lane);
     if (full) { GACT_DISPATCH(t, true, GACT_D_FULL) } else { GACT_DISPATCH(t, true, GACT_D_EDGE) }
 #undef GACT_D_FULL
 #undef GACT_D_EDGE
@@ -862,15 +863,27 @@ __device__ __forceinline__ void decompress_block(const TensorArgs& t, const Geom
 //   kBf16  every tensor is bf16: 4 KB of LDS per wavefront, so eight wavefronts per
 //          SIMD are resident if they keep to 64 VGPRs;
 //   kAny   fp32 among them: 8 KB of LDS per wavefront, four per SIMD, 128 VGPRs each.
-enum Work { kDecompress, kCompressBf16, kCompressAny };
+// A decompressing launch of fewer than kShortLaunch blocks is a kernel of its own, for
+// its units per wavefront and because such a launch has no block order.  (As a branch
+// in one kernel it gave back half of what the other units gain: one bf16 tensor of
+// 7.5 M elements, 2 bits, 4.4 us; with three units 4.9, this kernel 4.1.)
+enum Work { kDecompress, kCompressBf16, kCompressAny, kDecompressShort };
 constexpr int waves_per_simd(Work w) { return w == kCompressAny ? 4 : 8; }
+constexpr bool decompresses(Work w) { return w == kDecompress || w == kDecompressShort; }
+constexpr uint32_t bf16_units(Work w) { return w == kDecompressShort ? kDecUnitsBf16Short : kDecUnitsBf16; }
+
+template <Work W>
+__device__ __forceinline__ uint32_t work_block_of(uint32_t run_end, uint32_t run_shift) {
+    if constexpr (W == kDecompressShort) return blockIdx.x;
+    else return work_block(run_end, W == kDecompress ? kDecompressRunShift : run_shift);
+}
 
 template <Work W>
 __device__ __forceinline__ void run_block(const TensorArgs& t, const Geometry& geo,
                                           int64_t block_in_tensor) {
-    if constexpr (W == kDecompress) {
-        decompress_block(t, geo, block_in_tensor,
-                         (block_in_tensor + 1) * (int64_t)dec_block_elems(t.dtype(), t.bits()) <= t.n);
+    if constexpr (decompresses(W)) {
+        const int64_t end = (block_in_tensor + 1) * dec_block_elems(t.dtype(), t.bits(), bf16_units(W));
+        decompress_block<bf16_units(W)>(t, geo, block_in_tensor, end <= t.n);
     } else {
         double unused;
         compress_block<W == kCompressAny, false>(t, geo, block_in_tensor, unused);
@@ -885,8 +898,8 @@ __device__ __forceinline__ void run_block(const TensorArgs& t, const Geometry& g
 // (one bf16 tensor of 14 M elements, 4 bits: 7.7 us without, 7.0 with).
 template <Work W>
 GACT_KERNEL(W) single_kernel(uint32_t run_end, uint32_t run_shift, uint32_t full_blocks, TensorArgs t, Geometry geo) {
-    const uint32_t b = work_block(run_end, W == kDecompress ? kDecompressRunShift : run_shift);
-    if constexpr (W == kDecompress) decompress_block(t, geo, (int64_t)b, b < full_blocks);
+    const uint32_t b = work_block_of<W>(run_end, run_shift);
+    if constexpr (decompresses(W)) decompress_block<bf16_units(W)>(t, geo, (int64_t)b, b < full_blocks);
     else run_block<W>(t, geo, (int64_t)b);
 }
 
@@ -926,7 +939,7 @@ template <Work W>
 GACT_KERNEL(W) multi_kernel(
     uint32_t run_end, uint32_t run_shift, const TensorArgs* __restrict__ table, const uint32_t* __restrict__ first_block,
     const uint32_t* __restrict__ hint, uint32_t hint_shift, Geometry geo) {
-    const uint32_t b = work_block(run_end, W == kDecompress ? kDecompressRunShift : run_shift);
+    const uint32_t b = work_block_of<W>(run_end, run_shift);
     const int l = find_tensor<false>(first_block, hint, hint_shift, b);
     const TensorArgs t = table[l];
     run_block<W>(t, geo, (int64_t)(b - first_block[l]));
@@ -938,7 +951,7 @@ template <Work W>
 GACT_KERNEL(W) multi_inline_kernel(
     uint32_t run_end, uint32_t run_shift, uint32_t hint_shift, LineGeometry line, InlineTable tab) {
     const Geometry& geo = line.geo;
-    const uint32_t b = work_block(run_end, W == kDecompress ? kDecompressRunShift : run_shift);
+    const uint32_t b = work_block_of<W>(run_end, run_shift);
     const int l = find_tensor<true>(tab.first_block, tab.hint, hint_shift, b);
     run_block<W>(tab.t[l], geo, (int64_t)(b - tab.first_block[l]));
 }
@@ -947,8 +960,8 @@ GACT_KERNEL(W) multi_inline_kernel(
 
 // ------------------------------------------------------------ host launchers
 namespace {
-gact::Work work_of(int compress, const gact::Geometry* geo) {
-    if (!compress) return gact::kDecompress;
+gact::Work work_of(int compress, const gact::Geometry* geo, unsigned blocks) {
+    if (!compress) return blocks < gact::kShortLaunch ? gact::kDecompressShort : gact::kDecompress;
     return geo->lds_wave_dwords == gact::lds_dwords_per_wave(GACT_DT_BF16) ? gact::kCompressBf16 : gact::kCompressAny;
 }
 }  // namespace
@@ -960,8 +973,9 @@ gact::Work work_of(int compress, const gact::Geometry* geo) {
         const dim3 grid(blocks), block(gact::kBlockThreads);                                                \
         const unsigned lds = compress ? 4u * gact::kWavesPerBlk * (unsigned)geo->lds_wave_dwords : 0u;      \
         hipStream_t s = (hipStream_t)stream;                                                                \
-        switch (work_of(compress, geo)) {                                                                   \
+        switch (work_of(compress, geo, blocks)) {                                                           \
             case gact::kDecompress:   hipLaunchKernelGGL(KERNEL<gact::kDecompress>, grid, block, lds, s, __VA_ARGS__); break;   \
+            case gact::kDecompressShort: hipLaunchKernelGGL(KERNEL<gact::kDecompressShort>, grid, block, lds, s, __VA_ARGS__); break; \
             case gact::kCompressBf16: hipLaunchKernelGGL(KERNEL<gact::kCompressBf16>, grid, block, lds, s, __VA_ARGS__); break; \
             case gact::kCompressAny:  hipLaunchKernelGGL(KERNEL<gact::kCompressAny>, grid, block, lds, s, __VA_ARGS__); break;  \
         }                                                                                                   \
@@ -970,7 +984,8 @@ gact::Work work_of(int compress, const gact::Geometry* geo) {
 
 extern "C" int gact_launch_single(int compress, const gact::TensorArgs* t, const gact::Geometry* geo,
                                   unsigned blocks, void* stream) {
-    const uint32_t full_blocks = compress ? 0u : (uint32_t)(t->n / gact::dec_block_elems(t->dtype(), t->bits()));
+    const uint32_t units = gact::bf16_units(work_of(compress, geo, blocks));
+    const uint32_t full_blocks = compress ? 0u : (uint32_t)(t->n / gact::dec_block_elems(t->dtype(), t->bits(), units));
     GACT_LAUNCH(gact::single_kernel, runs.end, runs.shift, full_blocks, *t, *geo);
 }
 

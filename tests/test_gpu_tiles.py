@@ -165,3 +165,24 @@ def test_last_blocks_of_the_decompressor(gact, dtype, bits):
                                                               device="cuda"))
     for n, b, x, y in zip(ns, bufs, xs, ys):
         assert torch.equal(gact.gact_decompress(*b, n, G, bits, dtype=x.dtype), y), n
+
+
+@pytest.mark.parametrize("blocks", (8191, 8192))
+def test_two_bit_bf16_blocks_of_short_and_long_launches(gact, blocks):
+    """Blocks of 8,192 elements in launches shorter than 8,192 blocks of 6,144, of 6,144 from there on: the
+    longest of the short and the shortest of the long, as one tensor and as a list, against short launches."""
+    G, bits, n = 128, 2, (blocks - 1) * 6144 + 1
+    x = torch.randn(n, device="cuda", generator=torch.Generator("cuda").manual_seed(blocks)).to(torch.bfloat16)
+    p, mn, sc = gact.gact_compress(x, G, bits, 3)
+    y = gact.gact_decompress(p, mn, sc, n, G, bits, dtype=x.dtype)
+    cuts = [k * 700 * 8192 for k in range(n // (700 * 8192) + 1)] + [n]
+    parts = [(p[a * bits // 8:], mn[a // G:], sc[a // G:], b - a) for a, b in zip(cuts, cuts[1:])]
+    ys = [torch.zeros(q[3], dtype=x.dtype, device="cuda") for q in parts]
+    L = len(parts)
+    descs = gact.make_descs([None] * L, [q[0] for q in parts], [q[1] for q in parts], [q[2] for q in parts], ys,
+                            [q[3] for q in parts], [bits] * L, [0] * L, [x.dtype] * L)
+    gact.gact_decompress_multi(descs, L, G, torch.empty(gact.gact_multi_workspace_bytes(L), dtype=torch.uint8, device="cuda"))
+    for a, q, part in zip(cuts, parts, ys):
+        alone = gact.gact_decompress(*q, G, bits, dtype=x.dtype)
+        assert torch.equal(alone.view(torch.int16), y[a:a + q[3]].view(torch.int16)), a
+        assert torch.equal(alone.view(torch.int16), part.view(torch.int16)), a
