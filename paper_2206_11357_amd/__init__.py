@@ -326,6 +326,7 @@ def _reduce_workspace(tensors, workspace):
     """The caller's workspace, or one of the size that the buffers need (the library checks either)."""
     if workspace is not None:
         return workspace
+    tensors = list(tensors)              # a stacked tensor and a dict's values as well
     need = gact_reduce_workspace_bytes(len(tensors), sum(int(t.numel()) for t in tensors))
     dev = tensors[0].device if tensors else torch.device("cuda")
     return torch.empty(max(need, 16), dtype=torch.uint8, device=dev)

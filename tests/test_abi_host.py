@@ -8,6 +8,7 @@ import sys
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_2206_11357_amd as gact
@@ -226,3 +227,14 @@ def test_bench_refuses_more_than_one_gpu():
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+@pytest.mark.parametrize("buffers", (torch.zeros(3, 5000), {"a": torch.zeros(7), "b": torch.zeros(9000)}.values(),
+                                     (torch.zeros(4), torch.zeros(0)), [torch.zeros(1)]))
+def test_reduction_workspace_of_any_collection_of_buffers(buffers):
+    """A stacked tensor and a dict's values as well as lists: the rows, the values are the buffers."""
+    total = sum(t.numel() for t in buffers)
+    ws = gact._reduce_workspace(buffers, None)
+    assert ws.dtype == torch.uint8 and ws.device.type == "cpu"
+    assert ws.numel() == gact.gact_reduce_workspace_bytes(len(buffers), total)
+    assert gact._reduce_workspace(buffers, ws) is ws
