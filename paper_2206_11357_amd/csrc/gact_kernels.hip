@@ -396,15 +396,17 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // range / (2^BITS - 1), correctly rounded, for range >= 2^-100: a product with the rounded reciprocal
-// and one fused correction (three instructions instead of the eleven of a general division).  Every
-// significand was compared with the division on the host for the divisors 3, 15 and 255; the result does
-// not depend on the exponent as long as the remainder (down to 2^-149) and the quotient are exact.
+// and one fused correction (P. Markstein, IBM J. Res. Dev. 34 (1990) 111: four instructions with the
+// fix-up instead of the eleven of a general division).  Every significand was compared with the division
+// on the host for the divisors 3, 15 and 255; the result does not depend on the exponent as long as the
+// remainder (down to 2^-149) and the quotient are exact.  The fix-up gives an infinite range, whose
+// correction is inf - inf, its infinite quotient.
 template <int BITS>
 __device__ __forceinline__ float div_levels(float range) {
     constexpr float Bf = (float)((1u << BITS) - 1u), r = 1.0f / Bf;
     if (BITS == 1) return range;
     const float q = range * r;
-    return __builtin_fmaf(__builtin_fmaf(-q, Bf, range), r, q);
+    return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-q, Bf, range), r, q), Bf, range);
 }
 
 // Eight 4-bit fields, each in bits 17..20 of its word, to one word: field k in bits 4k..4k+3.

@@ -186,3 +186,24 @@ def test_two_bit_bf16_blocks_of_short_and_long_launches(gact, blocks):
         alone = gact.gact_decompress(*q, G, bits, dtype=x.dtype)
         assert torch.equal(alone.view(torch.int16), y[a:a + q[3]].view(torch.int16)), a
         assert torch.equal(alone.view(torch.int16), part.view(torch.int16)), a
+
+
+@pytest.mark.parametrize("dtype", ("f32", "bf16"))
+@pytest.mark.parametrize("bits", (1, 2, 4, 8))
+def test_a_range_that_overflows_has_an_infinite_step(gact, dtype, bits):
+    """Outside the contract's inputs, but range / B all the same: an infinite step, in full tiles and in the
+    last one, and nothing of it in the neighbouring groups."""
+    G, n = 64, 3 * 2048 + 5 * 64
+    x = syn.draw_numpy(syn.NORMAL, n, 5)
+    wide = (3, 40, 97, 100)                            # 97 and 100 lie in the last tile
+    for g in wide:
+        x[g * G + 7], x[g * G + 50] = -3e38, 3e38
+    x = as_dtype(x, dtype)
+    p, mn, sc = (to_host(t) for t in gact.gact_compress(to_device(x), G, bits, 2))
+    p_ref, mn_ref, sc_ref = oracle.compress(x, G, bits, 2)
+    assert np.isposinf(sc[list(wide)]).all()
+    assert np.array_equal(sc, sc_ref) and np.array_equal(mn, mn_ref)
+    same = np.ones(n // G, dtype=bool)
+    same[list(wide)] = False
+    per = G * bits // 8
+    assert np.array_equal(p[:n // G * per].reshape(-1, per)[same], p_ref[:n // G * per].reshape(-1, per)[same])
