@@ -895,13 +895,15 @@ __device__ __forceinline__ void run_block(const TensorArgs& t, const Geometry& g
 #define GACT_KERNEL(W) \
     __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(waves_per_simd(W), waves_per_simd(W)))) void
 
-// full_blocks, for decompress: the blocks in front of the one that the tensor's end cuts, so that a block
-// of a short launch waits for no multiplication by a block length that depends on the tensor's record
-// (one bf16 tensor of 14 M elements, 4 bits: 7.7 us without, 7.0 with).
+// The second argument is the shift of a run where the tensor is compressed.  Where it is decompressed, it is
+// the number of blocks in front of the one that the tensor's end cuts, so that a block of a short launch waits
+// for no multiplication by a block length that depends on the tensor's record (one bf16 tensor of 14 M
+// elements, 4 bits: 7.7 us without, 7.0 with).  An argument of its own puts the record across a 64-byte line,
+// which costs a compressing launch of 7 M elements 0.6 %.
 template <Work W>
-GACT_KERNEL(W) single_kernel(uint32_t run_end, uint32_t run_shift, uint32_t full_blocks, TensorArgs t, Geometry geo) {
-    const uint32_t b = work_block_of<W>(run_end, run_shift);
-    if constexpr (decompresses(W)) decompress_block<bf16_units(W)>(t, geo, (int64_t)b, b < full_blocks);
+GACT_KERNEL(W) single_kernel(uint32_t run_end, uint32_t shift_or_full, TensorArgs t, Geometry geo) {
+    const uint32_t b = work_block_of<W>(run_end, shift_or_full);
+    if constexpr (decompresses(W)) decompress_block<bf16_units(W)>(t, geo, (int64_t)b, b < shift_or_full);
     else run_block<W>(t, geo, (int64_t)b);
 }
 
@@ -988,7 +990,7 @@ extern "C" int gact_launch_single(int compress, const gact::TensorArgs* t, const
                                   unsigned blocks, void* stream) {
     const uint32_t units = gact::bf16_units(work_of(compress, geo, blocks));
     const uint32_t full_blocks = compress ? 0u : (uint32_t)(t->n / gact::dec_block_elems(t->dtype(), t->bits(), units));
-    GACT_LAUNCH(gact::single_kernel, runs.end, runs.shift, full_blocks, *t, *geo);
+    GACT_LAUNCH(gact::single_kernel, runs.end, compress ? runs.shift : full_blocks, *t, *geo);
 }
 
 extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::Geometry* geo,
