@@ -226,6 +226,7 @@ size_t reduce_table_bytes(int K) {
 struct Reduction {
     int K = 0;                                    // buffers that are not empty; 0: nothing to reduce
     unsigned blocks = 0;
+    int bf16_chunks = 1;                          // statistics: chunks of a bf16 buffer per block
     gact::ReduceTable inline_table{};             // their table, when it fits the kernel arguments
     bool is_inline = false;
     const gact::ReduceArgs* d_table = nullptr;    // else uploaded to the workspace
@@ -241,21 +242,33 @@ int stage_reduction(const std::vector<gact::ReduceArgs>& bufs, bool statistics, 
     const int nout = statistics ? 2 : 1;
     std::vector<gact::ReduceArgs> live;
     std::vector<uint32_t> first;
-    uint64_t blocks = 0;
-    for (const gact::ReduceArgs& r : bufs) {
-        if (r.n == 0) continue;
-        const int64_t chunk = statistics ? gact::kStatsChunkElems : gact::reduce_chunk_elems(r.dtype);
-        first.push_back((uint32_t)blocks);
-        live.push_back(r);
-        blocks += (uint64_t)((r.n + chunk - 1) / chunk);
-        if (blocks > 0x7FFFFFFFull) return GACT_E_ARG;
-    }
-    first.push_back((uint32_t)blocks);
+    for (const gact::ReduceArgs& r : bufs)
+        if (r.n != 0) live.push_back(r);
     const int K = (int)live.size();
-    if (K == 0) return GACT_OK;
     const size_t tb = reduce_table_bytes(K);
-    const size_t need = tb + (size_t)nout * blocks * sizeof(double);
-    if (!d_workspace || !aligned(d_workspace, 16) || workspace_bytes < need) return GACT_E_ARG;
+    uint64_t blocks = 0;
+    // false: more blocks than a launch has
+    const auto count = [&]() {
+        first.clear();
+        blocks = 0;
+        for (const gact::ReduceArgs& r : live) {
+            const int64_t chunk = statistics ? gact::stats_block_elems(r.dtype, red->bf16_chunks)
+                                             : gact::reduce_chunk_elems(r.dtype);
+            first.push_back((uint32_t)blocks);
+            blocks += (uint64_t)((r.n + chunk - 1) / chunk);
+            if (blocks > 0x7FFFFFFFull) return false;
+        }
+        first.push_back((uint32_t)blocks);
+        return true;
+    };
+    const auto need = [&]() { return tb + (size_t)nout * blocks * sizeof(double); };
+    bool fits = count();
+    if (K == 0) return GACT_OK;
+    if (statistics && (!fits || workspace_bytes < need())) {
+        red->bf16_chunks = 2;
+        fits = count();
+    }
+    if (!fits || !d_workspace || !aligned(d_workspace, 16) || workspace_bytes < need()) return GACT_E_ARG;
     if (const int rc = refuse_if_capturing(stream)) return rc;      // for both kinds of table
     red->K = K;
     red->blocks = (unsigned)blocks;
@@ -410,7 +423,7 @@ int gact_grad_stats_update(const gact_grad_stat* h_stats, int K, int64_t t, doub
     if (const int rc = stage_reduction(bufs, true, d_workspace, workspace_bytes, stream, &red)) return rc;
     if (red.K == 0) return gact_launch_zero(d_out, 2, stream) == 0 ? GACT_OK : GACT_E_HIP;
     const float rt = (float)(1.0 / (double)t);
-    return gact_launch_grad_stats(red.table(), red.d_table, red.d_first, red.K, rt, red.blocks,
+    return gact_launch_grad_stats(red.table(), red.d_table, red.d_first, red.K, rt, red.bf16_chunks, red.blocks,
                                   red.d_partial, d_out, stream) == 0 ? GACT_OK : GACT_E_HIP;
 }
 

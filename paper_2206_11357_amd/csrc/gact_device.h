@@ -114,8 +114,16 @@ struct ReduceTable {
 
 // Elements of one buffer a block covers: 512 threads x 2 pieces, of 16 bytes where the buffers are only
 // read, of 4 elements in a statistics step (16 bytes of the fp32 mean, whatever the gradient's type).
+// A statistics step in a workspace that holds a pair of results for every reduce_chunk_elems(dtype) and no
+// more has its blocks take two such chunks of a bf16 buffer, one after the other (302 M parameters: 528 us;
+// 505 us with one chunk a block, which is what gact_reduce_workspace_bytes has room for).
 constexpr int64_t reduce_chunk_elems(int dtype) { return dtype == GACT_DT_F32 ? 4096 : 8192; }
 constexpr int64_t kStatsChunkElems = 4096;
+constexpr int64_t stats_block_elems(int dtype, int bf16_chunks) {
+    return dtype == GACT_DT_F32 ? kStatsChunkElems : kStatsChunkElems * bf16_chunks;
+}
+static_assert(stats_block_elems(GACT_DT_BF16, 2) == reduce_chunk_elems(GACT_DT_BF16) &&
+              stats_block_elems(GACT_DT_F32, 2) == reduce_chunk_elems(GACT_DT_F32), "the least workspace");
 
 // Decompress launch shape.  A unit is the 1 KB of output one coalesced
 // wavefront store covers (256 fp32 or 512 bf16 elements); a block of four
@@ -198,8 +206,8 @@ extern "C" int gact_launch_footprint(const gact::ReduceArgs* r, unsigned blocks,
                                      int n_samples, double* d_out, void* stream);
 extern "C" int gact_launch_zero(double* d_out, int nout, void* stream);
 extern "C" int gact_launch_grad_stats(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
-                                      const uint32_t* d_first, int K, float rt, unsigned blocks, double* d_partial, double* d_out,
-                                      void* stream);
+                                      const uint32_t* d_first, int K, float rt, int bf16_chunks, unsigned blocks,
+                                      double* d_partial, double* d_out, void* stream);
 extern "C" int gact_launch_copy(void* dst, const void* src, uint64_t nbytes, unsigned workgroups, void* stream);
 extern "C" int gact_launch_multi_inline(int compress, const gact::InlineTable* tab, unsigned hint_shift,
                                         const gact::Geometry* geo, unsigned blocks, void* stream);

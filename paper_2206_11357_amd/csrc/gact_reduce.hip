@@ -253,18 +253,23 @@ __device__ __forceinline__ void stats_chunk(const ReduceArgs& r, int64_t chunk, 
     }
 }
 
-__device__ __forceinline__ void grad_stats_block(const ReduceArgs& r, int64_t chunk, float rt, uint32_t blocks,
-                                                 double* __restrict__ partial) {
+// bf16_chunks: how many chunks of a bf16 buffer this launch's blocks take (stats_block_elems)
+__device__ __forceinline__ void grad_stats_block(const ReduceArgs& r, int64_t block, float rt, int bf16_chunks,
+                                                 uint32_t blocks, double* __restrict__ partial) {
     __shared__ double lds[kRedWaves];
     const uint32_t b = blockIdx.x;
     double sg2 = 0.0, sm2 = 0.0;
-    const bool full = (chunk + 1) * kStatsChunkElems <= r.n;
+    const int chunks = r.dtype == GACT_DT_F32 ? 1 : bf16_chunks;
+    int64_t chunk = block * chunks;
     if (r.dtype == GACT_DT_F32) {
-        if (full) stats_chunk<GACT_DT_F32, true>(r, chunk, rt, sg2, sm2);
+        if ((chunk + 1) * kStatsChunkElems <= r.n) stats_chunk<GACT_DT_F32, true>(r, chunk, rt, sg2, sm2);
         else stats_chunk<GACT_DT_F32, false>(r, chunk, rt, sg2, sm2);
     } else {
-        if (full) stats_chunk<GACT_DT_BF16, true>(r, chunk, rt, sg2, sm2);
-        else stats_chunk<GACT_DT_BF16, false>(r, chunk, rt, sg2, sm2);
+#pragma unroll 1
+        for (const int64_t end = chunk + chunks; chunk < end; ++chunk) {
+            if ((chunk + 1) * kStatsChunkElems <= r.n) stats_chunk<GACT_DT_BF16, true>(r, chunk, rt, sg2, sm2);
+            else stats_chunk<GACT_DT_BF16, false>(r, chunk, rt, sg2, sm2);
+        }
     }
     const double s0 = block_sum(sg2, lds);
     const double s1 = block_sum(sm2, lds);
@@ -273,18 +278,18 @@ __device__ __forceinline__ void grad_stats_block(const ReduceArgs& r, int64_t ch
 
 __global__ __launch_bounds__(kRedThreads) void grad_stats_kernel(const ReduceArgs* __restrict__ table,
                                                                  const uint32_t* __restrict__ first_block,
-                                                                 int K, float rt, uint32_t blocks,
+                                                                 int K, float rt, int bf16_chunks, uint32_t blocks,
                                                                  double* __restrict__ partial) {
     const int k = find_buffer(first_block, K, blockIdx.x);
     const ReduceArgs r = table[k];
-    grad_stats_block(r, (int64_t)(blockIdx.x - first_block[k]), rt, blocks, partial);
+    grad_stats_block(r, (int64_t)(blockIdx.x - first_block[k]), rt, bf16_chunks, blocks, partial);
 }
 
 __global__ __launch_bounds__(kRedThreads) void grad_stats_inline_kernel(ReduceTable tab, int K, float rt,
-                                                                        uint32_t blocks,
+                                                                        int bf16_chunks, uint32_t blocks,
                                                                         double* __restrict__ partial) {
     const int k = find_buffer(tab.first_block, K, blockIdx.x);
-    grad_stats_block(tab.t[k], (int64_t)(blockIdx.x - tab.first_block[k]), rt, blocks, partial);
+    grad_stats_block(tab.t[k], (int64_t)(blockIdx.x - tab.first_block[k]), rt, bf16_chunks, blocks, partial);
 }
 
 // ------------------------------------------------------------ final addition
@@ -377,15 +382,15 @@ extern "C" int gact_launch_diff_sq(const gact::ReduceTable* inline_table, const 
 }
 
 extern "C" int gact_launch_grad_stats(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
-                                      const uint32_t* d_first, int K, float rt, unsigned blocks,
+                                      const uint32_t* d_first, int K, float rt, int bf16_chunks, unsigned blocks,
                                       double* d_partial, double* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     if (inline_table)
         hipLaunchKernelGGL(gact::grad_stats_inline_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s,
-                           *inline_table, K, rt, blocks, d_partial);
+                           *inline_table, K, rt, bf16_chunks, blocks, d_partial);
     else
         hipLaunchKernelGGL(gact::grad_stats_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, d_table,
-                           d_first, K, rt, blocks, d_partial);
+                           d_first, K, rt, bf16_chunks, blocks, d_partial);
     gact::launch_finish(d_partial, blocks, 2, 1.0, d_out, s);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }

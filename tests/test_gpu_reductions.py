@@ -68,3 +68,29 @@ def test_calls_without_a_stream_go_to_the_current_one(gact):
         assert gact._stream(None) == s.cuda_stream
     assert gact._stream(None) == torch.cuda.current_stream().cuda_stream
     assert gact._stream(s) == s.cuda_stream and gact._stream(7) == 7
+
+
+@pytest.mark.parametrize("sizes,dtypes", [((40000,), ("bf16",)), ((8192, 1, 50001, 4096, 4097), ("bf16", "f32", "bf16", "f32", "bf16")),
+                                          (tuple(range(1, 40000, 300)), ("bf16",))])
+def test_statistics_in_the_least_workspace(gact, sizes, dtypes):
+    """A result pair for every 4,096 fp32 or 8,192 bf16 elements of a buffer, begun ones too, behind the table of 36
+    bytes a buffer: enough although it is less than gact_reduce_workspace_bytes, and nothing behind it is
+    touched; 16 bytes less is refused."""
+    K = len(sizes)
+    kinds = [dtypes[k % len(dtypes)] for k in range(K)]
+    pairs = sum(-(-n // (4096 if d == "f32" else 8192)) for n, d in zip(sizes, kinds))
+    need = (36 * K + 4 + 15) // 16 * 16 + 16 * pairs
+    assert need < gact.gact_reduce_workspace_bytes(K, sum(sizes))
+    g = [buffers([n], 20 + k, d)[0] for k, (n, d) in enumerate(zip(sizes, kinds))]
+    means = [syn.draw_numpy(syn.NORMAL, n, 90 + k) for k, n in enumerate(sizes)]
+    d_g, d_means = [dev(x) for x in g], [dev(m) for m in means]
+    area = torch.full((need + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    with pytest.raises(gact.GactError):
+        gact.gact_grad_stats_update(d_g, d_means, 3, workspace=area[:need - 16])
+    out = gact.gact_grad_stats_update(d_g, d_means, 3, workspace=area[:need]).cpu().numpy()
+    want = np.zeros(2)
+    for x, m, d in zip(g, means, d_means):
+        want += oracle.grad_stats_update(x, m, 3)
+        assert np.array_equal(d.cpu().numpy().view(np.uint32), m.view(np.uint32))
+    assert out == pytest.approx(want, rel=REL)
+    assert (area[need:].cpu().numpy() == 0xA5).all()
