@@ -3,6 +3,7 @@
 #ifndef GACT_DEVICE_H
 #define GACT_DEVICE_H
 
+#include <stddef.h>
 #include <stdint.h>
 
 #ifndef __HIPCC__
@@ -84,13 +85,16 @@ constexpr int hint_buckets(int L) {
     return h;
 }
 
-// A launch table small enough to travel in the kernel arguments (4 KB limit).
+// Bytes of arguments a kernel can have.
+constexpr size_t kKernelArguments = 4096;
+// A launch table small enough to travel in the kernel arguments.
 constexpr int kInlineTensors = 64;
 struct InlineTable {
     TensorArgs t[kInlineTensors];
     uint32_t   first_block[kInlineTensors + 1];
     uint32_t   hint[kInlineHints / 4 + 1];   // one byte per bucket, four to a dword (scalar loads fetch dwords)
 };
+static_assert(12 + sizeof(LineGeometry) + sizeof(InlineTable) <= kKernelArguments, "a list's launch table and what precedes it");
 // tensor of bucket k in a byte-packed hint array
 __host__ __device__ inline int packed_hint(const uint32_t* hint, uint32_t k) {
     return (int)((hint[k >> 2] >> ((k & 3u) * 8u)) & 0xFFu);
@@ -105,12 +109,14 @@ struct ReduceArgs {
     int32_t     dtype;     // of a (and of b for sensitivity)
     int32_t     pad;
 };
-// A buffer table small enough to travel in the kernel arguments (4 KB limit).
+// A buffer table small enough to travel in the kernel arguments: 36 bytes a buffer, so that up to 112 would
+// fit beside the 28 bytes of the statistics kernel's other arguments; eight buffers' room is left.
 constexpr int kInlineBuffers = 104;
 struct ReduceTable {
     ReduceArgs t[kInlineBuffers];
     uint32_t   first_block[kInlineBuffers + 1];
 };
+static_assert(sizeof(ReduceTable) + 32 <= kKernelArguments, "a buffer table and what follows it");
 
 // Elements of one buffer a block covers: 512 threads x 2 pieces, of 16 bytes where the buffers are only
 // read, of 4 elements in a statistics step (16 bytes of the fp32 mean, whatever the gradient's type).
