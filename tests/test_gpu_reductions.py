@@ -30,6 +30,23 @@ def test_footprint_sums_per_block_and_samples_in_one_kernel(gact, dtype):
         assert np.array_equal(sc.cpu().numpy(), sc_ref), n
 
 
+@pytest.mark.parametrize("dtype,G,blocks", [("f32", 256, 8192 + 37), ("bf16", 96, 16384 + 300), ("bf16", 128, 32768 + 5)])
+def test_fused_footprint_of_long_launches(gact, dtype, G, blocks):
+    """Runs of 16 blocks and more per XCD with a last partial window, where a block's sum goes to the block's place;
+    more sums than one addition takes.  Whole numbers, whose sum is exact in binary64."""
+    bits, period = 2, 256
+    n = blocks * 4 * (64 // (G // 32) * G) - 1234
+    x = torch.arange(period, device="cuda", dtype=torch.float32).repeat(n // period + 1)[:n]
+    x = x.to(torch.bfloat16) if dtype == "bf16" else x
+    x[5] = 300.0                                       # no period over the whole of it
+    full, rest = divmod(n, period)
+    p, mn, sc, fp = gact.gact_compress_footprint(x, G, bits, 9, 7)
+    got = fp.cpu().numpy()
+    assert got[0] == full * (period * (period - 1) // 2) + rest * (rest - 1) // 2 + 295
+    assert np.array_equal(got[1:], [float((j * n // 7) % period) for j in range(7)])
+    assert all(torch.equal(a, b) for a, b in zip((p, mn, sc), gact.gact_compress(x, G, bits, 9)))
+
+
 def test_footprint_of_more_blocks_than_one_addition_takes(gact):
     n = 32769 * 4096 + 5
     x = torch.arange(1024, device="cuda", dtype=torch.float32).repeat(n // 1024 + 1)[:n]

@@ -29,10 +29,12 @@ def test_full_tiles_of_group_sizes_that_are_no_power_of_two(gact, dtype, lanes):
             run_case(gact, x, G, bits, seed=lanes + k)
 
 
-@pytest.mark.parametrize("dtype,bits,blocks", [("bf16", 4, 8192 + 37), ("f32", 2, 8192), ("f32", 1, 16384 + 300)])
+@pytest.mark.parametrize("dtype,bits,blocks", [("bf16", 4, 8192 + 37), ("f32", 2, 8192), ("f32", 1, 16384 + 300),
+                                               ("bf16", 2, 32768 + 513), ("f32", 1, 65536 + 1025), ("bf16", 1, 131072 + 2049)])
 def test_runs_of_neighbouring_blocks_per_xcd(gact, dtype, bits, blocks):
     """Launches that are long enough for another block order, with and without a last partial window,
-    against the same tensor in pieces that are not."""
+    against the same tensor in pieces that are not.  Compress: runs of 16, 32, 64, 128 and 256 blocks;
+    decompress: runs of 32."""
     G, seed, n = 256, 9, blocks * 8192 - 1234
     gen = torch.Generator(device="cuda").manual_seed(blocks)
     x = torch.randn(n, device="cuda", generator=gen).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
@@ -113,13 +115,28 @@ def test_steps_are_correctly_rounded(gact):
         run_case(gact, x.ravel(), G, bits, seed=bits)
 
 
-@pytest.mark.parametrize("L", (65, 215, 245, 430, 470, 640, 760))
-def test_tables_uploaded_in_one_piece_and_in_several(gact, L):
-    """Launch tables of 6 to 60 KB: one copy of up to 16 KB, two or three of them, one larger copy.  Each
-    tensor's bytes against the call for it alone."""
-    G, seed = 64, 3
-    x = torch.randn(L * 512, device="cuda", generator=torch.Generator("cuda").manual_seed(L)).to(torch.bfloat16)
-    xs = [x[l * 512:l * 512 + 1 + (l * 37) % 512] for l in range(L)]
+def table_bytes(L, blocks):
+    """Launch table of L tensors: 56 bytes each, the first block of each and the total, an index over the blocks
+    (a power of two of at least 4 L buckets, as few blocks to each as fill no more)."""
+    up = lambda v: (v + 15) // 16 * 16
+    buckets, shift = 64, 0
+    while buckets < 4 * L:
+        buckets *= 2
+    while (blocks - 1 >> shift) + 1 > buckets:
+        shift += 1
+    return up(56 * L) + up(4 * (L + 1)) + 4 * ((blocks - 1 >> shift) + 2)
+
+
+@pytest.mark.parametrize("L,per,copies", [(65, 1, 1), (255, 1, 1), (256, 1, 2), (511, 1, 2), (512, 1, 3), (767, 1, 3),
+                                          (768, 1, 0), (600, 5, 3), (620, 6, 0)])
+def test_tables_uploaded_in_one_piece_and_in_several(gact, L, per, copies):
+    """Launch tables on either side of 16, 32 and 48 KB: one copy of up to 16 KB, two or three of them, one larger
+    copy (0).  L tensors of `per` blocks; each tensor's bytes against the call for it alone."""
+    size = table_bytes(L, L * per)
+    assert copies == (0 if size > 3 * 16384 else -(-size // 16384))
+    G, seed, span = 64, 3, 512 if per == 1 else per * 8192
+    x = torch.randn(L * span, device="cuda", generator=torch.Generator("cuda").manual_seed(L)).to(torch.bfloat16)
+    xs = [x[l * span:l * span + (1 + (l * 37) % 512 if per == 1 else span - l % 9)] for l in range(L)]
     bits = [(1, 2, 4, 8)[l % 4] for l in range(L)]
     bufs = [gact.alloc_compressed(v.numel(), G, b, "cuda") for v, b in zip(xs, bits)]
     ys = [torch.empty_like(v) for v in xs]
