@@ -846,16 +846,21 @@ __device__ __forceinline__ void compress_block(const TensorArgs& t, const Geomet
 #undef GACT_C_EDGE
 }
 
-// full: every element of the block's span exists
+// full: every element of the block's span exists.
+// A wavefront ends where its stores are out and not behind the dispatch: otherwise it takes four more jumps,
+// each to a line of instructions of its own, which a launch between a model's kernels fetches anew (bf16,
+// 4 bits, between the kernels of a training step: 16.8 M elements 11.7 -> 11.3 us, 50 M 24.7 -> 24.1).
 template <uint32_t BF16_UNITS>
 __device__ __forceinline__ void decompress_block(const TensorArgs& t, const Geometry& geo,
                                                  int64_t block_in_tensor, bool full) {
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
 #define GACT_D_FULL(DT, BITS) \
-    decompress_units<DT, BITS, false, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS)>(t, geo, block_in_tensor, wave, lane);
+    decompress_units<DT, BITS, false, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS)>(t, geo, block_in_tensor, wave, lane); \
+    __builtin_amdgcn_endpgm();
 #define GACT_D_EDGE(DT, BITS) \
-    decompress_units<DT, BITS, true, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS)>(t, geo, block_in_tensor, wave, lane);
+    decompress_units<DT, BITS, true, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS)>(t, geo, block_in_tensor, wave, lane); \
+    __builtin_amdgcn_endpgm();
     if (full) { GACT_DISPATCH(t, true, GACT_D_FULL) } else { GACT_DISPATCH(t, true, GACT_D_EDGE) }
 #undef GACT_D_FULL
 #undef GACT_D_EDGE
