@@ -76,7 +76,8 @@ enum {
     GACT_E_BUDGET = -4,  /* avg_bit_budget < 1 or NaN: no feasible scheme */
     GACT_E_HIP    = -5,  /* the HIP runtime refused the launch or copy */
     GACT_E_CAPTURE = -6, /* the stream is being captured into a HIP graph and this call
-                            would have to upload a table from host memory */
+                            would have to upload a table from host memory (the two
+                            reductions over buffer lists: whether they would or not) */
     GACT_E_SCRATCH = -7  /* gact_compress_footprint_noalloc: the tensor needs more than the
                             library's static scratch area */
 };
@@ -177,9 +178,12 @@ int gact_decompress_multi(const gact_tensor_desc *h_descs, int L, int group_size
  *   d_workspace  device scratch, >= gact_reduce_workspace_bytes(K, sum of n),
  *                16-byte aligned; in use until the enqueued kernels have run.
  * K == 0 or all n == 0 writes 0.
- * The buffer table is uploaded from host memory the call owns, so this call
- * and gact_grad_stats_update return GACT_E_CAPTURE, with nothing enqueued, on
- * a stream that is being captured into a HIP graph.
+ * HIP graphs: this call and gact_grad_stats_update return GACT_E_CAPTURE, with
+ * nothing enqueued, on a stream that is being captured.  A list of more than
+ * 104 non-empty buffers needs its table uploaded from host memory the call
+ * owns, which a graph could not replay; shorter lists travel in the kernel
+ * arguments and are refused all the same, so that what a caller can capture
+ * does not depend on how many of its buffers happen to be empty.
  */
 typedef struct {
     const void *g0;
@@ -260,16 +264,16 @@ int gact_copy_bounded(void *dst, const void *src, size_t nbytes, int workgroups,
 /*
  * gact_compress_footprint for callers that cannot allocate device memory and
  * so cannot bring a workspace: code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc.  The per-tile partial sums go to a
+ * loops, harnesses that forbid hipMalloc.  The kernel's partial sums go to a
  * scratch area of GACT_NOALLOC_SCRATCH_BYTES that is part of the library's
  * device image (each GPU the library runs on holds one copy until the process
  * ends); the call allocates and frees nothing.  Same arguments, results and
  * error codes as gact_compress_footprint without the workspace pair; results
  * are byte-identical to that call's.
- *   Limit: one 8-byte partial per tile of 2048 elements (63 * 32 ... 64 * 32
- *   elements when group_size / 32 is not a power of two), i.e. up to
- *   536,870,912 elements for power-of-two group sizes.  A larger n returns
- *   GACT_E_SCRATCH and enqueues nothing.
+ *   Limit: room for one 8-byte partial per tile of 2048 elements (44 * 32 ...
+ *   63 * 32 elements when group_size / 32 is not a power of two), i.e. up to
+ *   536,870,912 elements for power-of-two group sizes; the kernel writes one per
+ *   four tiles.  A larger n returns GACT_E_SCRATCH and enqueues nothing.
  *   All calls on one GPU share that GPU's area: two calls whose kernels may
  *   overlap in time (different streams, or graph launches in flight together)
  *   race on it and must be ordered by the caller.  The area keeps the last

@@ -106,8 +106,9 @@ int refuse_if_capturing(void* stream) {
 // Enqueues a copy of a launch table to the workspace; `src` may go when this returns (it is pageable
 // memory, of which the runtime takes its own copy first).  The runtime moves up to 16 KB with a small
 // kernel, 4.6 us of the stream, and more with the DMA engine, whose hand-over leaves the stream idle for
-// 18 to 20 us: tables of up to three such pieces (about 700 tensors) go piece by piece.  400 tensors, 28 KB:
-// compress 115 -> 106 us, decompress 131 -> 109 us (0.25 G bf16 elements).
+// 18 to 20 us: tables of up to three such pieces go piece by piece (up to 767 tensors of a block each; fewer
+// where the launch has blocks enough to fill the index over them, 545 to 680).  400 tensors, 28 KB: compress
+// 115 -> 106 us, decompress 131 -> 109 us (0.25 G bf16 elements).
 int upload(void* dst, const unsigned char* src, size_t bytes, void* stream) {
     constexpr size_t kPiece = 16384;
     const size_t piece = bytes <= 3 * kPiece ? kPiece : bytes;

@@ -175,14 +175,19 @@ constexpr int dec_block_elems(int dtype, int bits, uint32_t bf16_units) {
 //   compress  53 fp32 tensors, 87k blocks       498    486    481    481    481    483    483
 //   compress  400 bf16 tensors, 32k blocks      121    116    115    114    115    117    120
 //   compress  3 fp32 tensors, 16k blocks       69.4   68.3   68.2   68.6   69.4   70.0   70.3
-//   decompress 96 bf16 tensors, 1.2M blocks    2378   2428   2336   2350   2343   2329   2340
-//   decompress 53 fp32 tensors, 230k blocks     492    493    490    492    495    503    510
-//   decompress 400 bf16 tensors, 49k blocks     133    129    128    127    127    130    129
-//   decompress 3 fp32 tensors, 32k blocks      76.2   73.7   73.5   73.8   74.5   75.3   77.9
+//   decompress 96 bf16 tensors, 1.3M blocks    2382   2514   2353   2360   2351   2334   2329
+//   decompress 400 bf16 tensors, 419k blocks    830    853    836    839    840    846    846
+//   decompress 53 fp32 tensors, 226k blocks     494    493    491    492    494    502    508
+//   decompress 400 bf16 tensors, 53k blocks   111.9  108.7  109.3  109.2  107.9  109.7  111.1
+//   decompress 3 fp32 tensors, 34k blocks      76.4   73.6   73.4   73.6   74.5   75.4   77.6
+//   the same, every buffer on a line           71.8   71.9   71.7   71.9   72.6   73.5   75.7
+//   decompress 53 fp32 tensors, 28k blocks     65.2   65.1   65.0   65.5   67.1   67.8   68.8
 //   decompress 1 bf16 tensor, 1.8k blocks      4.85    --    5.35
 // Compress: runs as long as leave 64 windows, at most 256 blocks.  Decompress: runs of 32 (runs of 4 to 16
-// cost up to 10 % on bf16 output at 4 bits, and lengths that are no power of two are worse than 32 throughout).
-// Launches of few windows keep plain order: the XCDs that get the runs of a last, partial window finish late.
+// cost up to 10 % on bf16 output at 4 bits, and lengths that are no power of two are worse than 32 throughout),
+// for all types and alignments: where no line is shared between blocks they cost nothing, and of the launches
+// above one loses (0.7 %).  Launches of few windows keep plain order: the XCDs that get the runs of a last,
+// partial window finish late.
 constexpr uint32_t kDecompressRunShift = 5;
 inline int run_shift_for(bool compress, uint64_t blocks) {
     int log2 = 0;

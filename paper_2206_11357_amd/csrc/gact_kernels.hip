@@ -798,10 +798,11 @@ __device__ __forceinline__ void decompress_units(const TensorArgs& t, const Geom
 // The block of work this workgroup takes.  Workgroups go to the eight XCDs in
 // turn, each XCD with an L2 of its own, so that in plain order neighbouring
 // blocks never share one: a line of packed codes, minima or steps that two
-// blocks write parts of (every line at a block's edge where the caller's buffers
-// are not aligned to 128 bytes, as in one buffer per kind cut at multiples of 16)
-// leaves two caches as two partial writes, and one that two blocks read is
-// fetched twice.  Within a window of 8 * 2^s workgroups, XCD x therefore takes
+// blocks write parts of leaves two caches as two partial writes, and one that two
+// blocks read is fetched twice.  (That is every line at a block's edge where the
+// caller's buffers are not aligned to 128 bytes, as in one buffer per kind cut at
+// multiples of 16, and the lines of minima and steps wherever a block has less than
+// a line of them: 64 bytes for 4,096 elements in groups of 256.)  Within a window of 8 * 2^s workgroups, XCD x therefore takes
 // the 2^s neighbouring blocks x * 2^s ...; what does not fill a window keeps
 // plain order.  s and run_end, the first block past the last whole window (Runs;
 // 0: plain order), come from the launcher as the kernel's first two arguments, which
@@ -810,7 +811,7 @@ __device__ __forceinline__ void decompress_units(const TensorArgs& t, const Geom
 // loads.  A block loads nothing before this chain of scalar instructions is through, so
 // a decompressing kernel has s as a constant: with s in a register, the lookup's shift in
 // memory and the block length found by branches (dec_unit_table), decompressing 53
-// fp32 tensors of 89 M elements took 65.45 us, now 64.8, and 64.8 without a block order.
+// fp32 tensors of 89 M elements took 65.6 us, now 64.9 (65.0 before there was an order).
 __device__ __forceinline__ uint32_t work_block(uint32_t run_end, uint32_t s) {
     const uint32_t b = blockIdx.x;
     if (b >= run_end) return b;
