@@ -224,3 +224,29 @@ def test_a_range_that_overflows_has_an_infinite_step(gact, dtype, bits):
     same[list(wide)] = False
     per = G * bits // 8
     assert np.array_equal(p[:n // G * per].reshape(-1, per)[same], p_ref[:n // G * per].reshape(-1, per)[same])
+
+
+@pytest.mark.parametrize("dtype", ("f32", "bf16"))
+@pytest.mark.parametrize("bits", (1, 2, 4, 8))
+@pytest.mark.parametrize("G", (32, 96, 992))
+def test_long_decompressing_launches_against_short_ones(gact, dtype, bits, G):
+    """The kernel for launches of 8,192 blocks and more and the one for shorter launches: one tensor that ends
+    inside a block, and a list of five that each do, against the call for each of the five."""
+    units = {1: 3, 2: 4 if dtype == "f32" else 3, 4: 2, 8: 2}[bits]
+    span = 4 * units * (256 if dtype == "f32" else 512)
+    n = 8192 * span + 777
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.randn(n, device="cuda", generator=torch.Generator("cuda").manual_seed(bits * G)).to(dt)
+    p, mn, sc = gact.gact_compress(x, G, bits, 3)
+    y = gact.gact_decompress(p, mn, sc, n, G, bits, dtype=dt)
+    step = n // 5 // (128 * G) * 128 * G              # whole groups, and codes that begin on 16 bytes
+    cuts = [0, step, 2 * step, 3 * step, 4 * step, n]
+    parts = [(p[a * bits // 8:], mn[a // G:], sc[a // G:], b - a) for a, b in zip(cuts, cuts[1:])]
+    ys = [torch.zeros(q[3], dtype=dt, device="cuda") for q in parts]
+    descs = gact.make_descs([None] * 5, [q[0] for q in parts], [q[1] for q in parts], [q[2] for q in parts], ys,
+                            [q[3] for q in parts], [bits] * 5, [0] * 5, [dt] * 5)
+    gact.gact_decompress_multi(descs, 5, G, torch.empty(gact.gact_multi_workspace_bytes(5), dtype=torch.uint8, device="cuda"))
+    for a, q, part in zip(cuts, parts, ys):
+        alone = gact.gact_decompress(*q, G, bits, dtype=dt).view(torch.uint8)
+        assert torch.equal(alone, y[a:a + q[3]].view(torch.uint8)), a
+        assert torch.equal(alone, part.view(torch.uint8)), a
