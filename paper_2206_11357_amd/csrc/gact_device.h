@@ -65,6 +65,15 @@ struct Runs {
     uint32_t shift;        // log2 of the neighbouring blocks one XCD takes in a run
 };
 
+#ifdef __HIPCC__
+// The block of work that workgroup b takes (work_block in gact_kernels.hip says why).
+__device__ __forceinline__ uint32_t ordered_block(uint32_t b, uint32_t run_end, uint32_t s) {
+    if (b >= run_end) return b;
+    const uint32_t low = (8u << s) - 1u;
+    return (b & ~low) | ((b & 7u) << s) | ((b & low) >> 3);
+}
+#endif
+
 // LDS one compressing wavefront stages its tile in: 64 rows of 32 elements in
 // the input's own format.
 constexpr int lds_dwords_per_wave(int dtype) { return dtype == GACT_DT_F32 ? 64 * 32 : 64 * 16; }
@@ -117,6 +126,18 @@ struct ReduceTable {
     uint32_t   first_block[kInlineBuffers + 1];
 };
 static_assert(sizeof(ReduceTable) + 32 <= kKernelArguments, "a buffer table and what follows it");
+
+// Runs of the reductions' blocks (16 KB of each buffer they only read) that go to one XCD, as a power of two.
+// Us a call on MI355X, plain order and runs of 2^s blocks, buffers of an encoder's sizes:
+//                                      plain   s=2    s=3    s=4    s=5    s=6    s=7
+//   sensitivity, fp32, 302 M elements   350    354    343    344    344    347    351
+//   sensitivity, bf16, 302 M            178    179    178    178    181    181    181
+//   statistics, fp32, 302 M             601    639    589    609    587    583    595
+//   statistics, bf16, 302 M             501    504    483    492    477    478    487
+//   statistics, bf16, 85 M              142    141    139    139    138    138    140
+// Launches below one window of eight runs keep plain order.
+constexpr uint32_t kDiffRunShift = 3, kStatsRunShift = 5;
+constexpr uint32_t runs_end(uint32_t blocks, uint32_t s) { return blocks >> (3 + s) << (3 + s); }
 
 // Elements of one buffer a block covers: 512 threads x 2 pieces, of 16 bytes where the buffers are only
 // read, of 4 elements in a statistics step (16 bytes of the fp32 mean, whatever the gradient's type).
@@ -198,7 +219,7 @@ inline int run_shift_for(bool compress, uint64_t blocks) {
 
 inline Runs runs_for(bool compress, uint64_t blocks) {
     const int s = run_shift_for(compress, blocks);
-    return Runs{s ? (uint32_t)(blocks >> (3 + s) << (3 + s)) : 0u, (uint32_t)s};
+    return Runs{s ? runs_end((uint32_t)blocks, (uint32_t)s) : 0u, (uint32_t)s};
 }
 
 }  // namespace gact

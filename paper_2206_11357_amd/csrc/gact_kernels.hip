@@ -813,10 +813,7 @@ __device__ __forceinline__ void decompress_units(const TensorArgs& t, const Geom
 // memory and the block length found by branches (dec_unit_table), decompressing 53
 // fp32 tensors of 89 M elements took 65.6 us, now 64.9 (65.0 before there was an order).
 __device__ __forceinline__ uint32_t work_block(uint32_t run_end, uint32_t s) {
-    const uint32_t b = blockIdx.x;
-    if (b >= run_end) return b;
-    const uint32_t low = (8u << s) - 1u;
-    return (b & ~low) | ((b & 7u) << s) | ((b & low) >> 3);
+    return ordered_block(blockIdx.x, run_end, s);
 }
 
 template <bool WITH_F32, bool SUM>

@@ -111,3 +111,26 @@ def test_statistics_in_the_least_workspace(gact, sizes, dtypes):
         assert np.array_equal(d.cpu().numpy().view(np.uint32), m.view(np.uint32))
     assert out == pytest.approx(want, rel=REL)
     assert (area[need:].cpu().numpy() == 0xA5).all()
+
+
+@pytest.mark.parametrize("dtype", ("f32", "bf16"))
+@pytest.mark.parametrize("blocks", (1, 63, 64, 65, 129, 255, 256, 257, 700))
+def test_every_block_is_taken_once_in_any_order(gact, dtype, blocks):
+    """Launches of no, one and several whole windows of eight runs (64 blocks of a sensitivity, 256 of a statistics
+    step), with and without blocks behind them, in one buffer and in three.  Small whole numbers, a sum of which
+    is exact; every chunk of a buffer has a value of its own, so that none can stand for another."""
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    for lists in (1, 3):
+        per, total = (4096 if dtype == "f32" else 8192), 0
+        g0, g1 = [], []
+        for k in range(lists):
+            n = max(blocks // lists, 1) * per - (3 if k else 0)
+            i = torch.arange(n, device="cuda") // 2048 + 7 * k
+            g0.append((i % 31).to(dt))
+            g1.append((i % 31 - i % 13 - 1).to(dt))
+            total += int(((i % 13 + 1) ** 2).sum())
+        assert gact.gact_sensitivity(g0, g1, 1).item() == 0.5 * total
+        means = [torch.zeros(g.numel(), device="cuda") for g in g0]
+        out = gact.gact_grad_stats_update(g0, means, 1).cpu().tolist()
+        want = float(sum((g.double() ** 2).sum() for g in g0))
+        assert out == [want, want] and all(torch.equal(m, g.float()) for m, g in zip(means, g0))
