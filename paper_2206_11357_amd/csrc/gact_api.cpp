@@ -3,6 +3,8 @@
 // touch the GPU (sizes, bit allocator, variance alert) are in gact_host.cpp.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -12,6 +14,7 @@
 
 #include "gact.h"
 #include "gact_device.h"
+#include "gact_sum.h"
 
 // Scratch area of gact_compress_footprint_noalloc: device memory that is part
 // of the library's code object, one copy per GPU, held until the process ends.
@@ -219,6 +222,19 @@ int run_multi(bool compress, const gact_tensor_desc* descs, int L, int group_siz
 }
 
 // ---------------------------------------------------------------- reductions
+// The tag of one call's results (gact_sum.h): a number that no other call of this process has, spread over all
+// 64 bits (the finaliser of splitmix64), never 0 (untagged) nor all ones (whose complement is).
+uint64_t next_tag() {
+    static std::atomic<uint64_t> calls{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count()};
+    for (;;) {
+        uint64_t z = calls.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull;
+        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+        z ^= z >> 31;
+        if (z != 0 && z != ~0ull) return z;
+    }
+}
+
 size_t reduce_table_bytes(int K) {
     return ((size_t)K * sizeof(gact::ReduceArgs) + (size_t)(K + 1) * sizeof(uint32_t) + 15) / 16 * 16;
 }
@@ -233,6 +249,7 @@ struct Reduction {
     const gact::ReduceArgs* d_table = nullptr;    // else uploaded to the workspace
     const uint32_t* d_first = nullptr;
     double* d_partial = nullptr;
+    bool tagged = false;                          // room for two words per result: the launch adds them itself
     const gact::ReduceTable* table() const { return is_inline ? &inline_table : nullptr; }
 };
 
@@ -274,6 +291,7 @@ int stage_reduction(const std::vector<gact::ReduceArgs>& bufs, bool statistics, 
     red->K = K;
     red->blocks = (unsigned)blocks;
     red->d_partial = (double*)((unsigned char*)d_workspace + tb);
+    red->tagged = !statistics && workspace_bytes >= tb + 2 * blocks * sizeof(double) && blocks < 0x70000000u;
     if (K <= gact::kInlineBuffers) {
         std::memcpy(red->inline_table.t, live.data(), (size_t)K * sizeof(gact::ReduceArgs));
         std::memcpy(red->inline_table.first_block, first.data(), first.size() * sizeof(uint32_t));
@@ -333,7 +351,7 @@ int compress_footprint(const void* d_x, gact_dtype dtype, int64_t n, int group_s
     if (gact_launch_compress_sum(&t, &geo, (unsigned)blocks, (double*)d_workspace, stream) != 0)
         return GACT_E_HIP;
     const gact::ReduceArgs r{d_x, nullptr, n, (int32_t)dtype, 0};
-    return gact_launch_footprint_finish(&r, (unsigned)blocks, (double*)d_workspace, n_samples,
+    return gact_launch_footprint_finish(&r, (unsigned)blocks, (double*)d_workspace, next_tag(), n_samples,
                                         d_footprint, stream) == 0 ? GACT_OK : GACT_E_HIP;
 }
 
@@ -407,7 +425,7 @@ int gact_sensitivity(const gact_grad_pair* h_pairs, int K, int bits, double* d_o
         return gact_launch_zero(d_out, 1, stream) == 0 ? GACT_OK : GACT_E_HIP;
     const double B = (double)((1 << bits) - 1);
     return gact_launch_diff_sq(red.table(), red.d_table, red.d_first, red.K, red.blocks, red.d_partial,
-                               0.5 * B * B, d_out, stream) == 0 ? GACT_OK : GACT_E_HIP;
+                               red.tagged, next_tag(), 0.5 * B * B, d_out, stream) == 0 ? GACT_OK : GACT_E_HIP;
 }
 
 int gact_grad_stats_update(const gact_grad_stat* h_stats, int K, int64_t t, double* d_out,
@@ -425,7 +443,7 @@ int gact_grad_stats_update(const gact_grad_stat* h_stats, int K, int64_t t, doub
     if (red.K == 0) return gact_launch_zero(d_out, 2, stream) == 0 ? GACT_OK : GACT_E_HIP;
     const float rt = (float)(1.0 / (double)t);
     return gact_launch_grad_stats(red.table(), red.d_table, red.d_first, red.K, rt, red.bf16_chunks, red.blocks,
-                                  red.d_partial, d_out, stream) == 0 ? GACT_OK : GACT_E_HIP;
+                                  red.d_partial, next_tag(), d_out, stream) == 0 ? GACT_OK : GACT_E_HIP;
 }
 
 int gact_footprint(const void* d_x, gact_dtype dtype, int64_t n, int n_samples, double* d_out,
@@ -442,7 +460,7 @@ int gact_footprint(const void* d_x, gact_dtype dtype, int64_t n, int n_samples, 
         workspace_bytes < (size_t)blocks * sizeof(double))
         return GACT_E_ARG;
     const gact::ReduceArgs r{d_x, nullptr, n, (int32_t)dtype, 0};
-    return gact_launch_footprint(&r, (unsigned)blocks, (double*)d_workspace, n_samples, d_out,
+    return gact_launch_footprint(&r, (unsigned)blocks, (double*)d_workspace, next_tag(), n_samples, d_out,
                                  stream) == 0 ? GACT_OK : GACT_E_HIP;
 }
 

@@ -118,14 +118,14 @@ struct ReduceArgs {
     int32_t     dtype;     // of a (and of b for sensitivity)
     int32_t     pad;
 };
-// A buffer table small enough to travel in the kernel arguments: 36 bytes a buffer, so that up to 112 would
-// fit beside the 28 bytes of the statistics kernel's other arguments; eight buffers' room is left.
+// A buffer table small enough to travel in the kernel arguments: 36 bytes a buffer, so that up to 111 would
+// fit beside the 48 bytes of the sensitivity kernel's other arguments; eight buffers' room is left.
 constexpr int kInlineBuffers = 104;
 struct ReduceTable {
     ReduceArgs t[kInlineBuffers];
     uint32_t   first_block[kInlineBuffers + 1];
 };
-static_assert(sizeof(ReduceTable) + 32 <= kKernelArguments, "a buffer table and what follows it");
+static_assert(sizeof(ReduceTable) + 64 <= kKernelArguments, "a buffer table and what follows it");
 
 // Runs of the reductions' blocks (16 KB of each buffer they only read) that go to one XCD, as a power of two.
 // Us a call on MI355X, plain order and runs of 2^s blocks, buffers of an encoder's sizes:
@@ -228,18 +228,18 @@ extern "C" int gact_launch_single(int compress, const gact::TensorArgs* t,
                                   const gact::Geometry* geo, unsigned blocks, void* stream);
 // `inline_table` is used when it is not null, else the table in device memory
 extern "C" int gact_launch_diff_sq(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
-                                   const uint32_t* d_first, int K, unsigned blocks, double* d_partial, double scale, double* d_out,
-                                   void* stream);
+                                   const uint32_t* d_first, int K, unsigned blocks, double* d_partial, int tagged,
+                                   uint64_t tag, double scale, double* d_out, void* stream);
 extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::Geometry* geo,
                                         unsigned blocks, double* d_block_sum, void* stream);
-extern "C" int gact_launch_footprint_finish(const gact::ReduceArgs* r, unsigned count, double* d_partial,
+extern "C" int gact_launch_footprint_finish(const gact::ReduceArgs* r, unsigned count, double* d_partial, uint64_t tag,
                                             int n_samples, double* d_out, void* stream);
-extern "C" int gact_launch_footprint(const gact::ReduceArgs* r, unsigned blocks, double* d_partial,
+extern "C" int gact_launch_footprint(const gact::ReduceArgs* r, unsigned blocks, double* d_partial, uint64_t tag,
                                      int n_samples, double* d_out, void* stream);
 extern "C" int gact_launch_zero(double* d_out, int nout, void* stream);
 extern "C" int gact_launch_grad_stats(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
                                       const uint32_t* d_first, int K, float rt, int bf16_chunks, unsigned blocks,
-                                      double* d_partial, double* d_out, void* stream);
+                                      double* d_partial, uint64_t tag, double* d_out, void* stream);
 extern "C" int gact_launch_copy(void* dst, const void* src, uint64_t nbytes, unsigned workgroups, void* stream);
 extern "C" int gact_launch_multi_inline(int compress, const gact::InlineTable* tab, unsigned hint_shift,
                                         const gact::Geometry* geo, unsigned blocks, void* stream);

@@ -4,8 +4,8 @@
 // Both are multi-buffer streaming reductions bound by HBM: a block of 512
 // threads takes 16 KB of each buffer it only reads with two coalesced 16-byte
 // loads per thread, accumulates in binary64 per thread, reduces over the block,
-// and writes one partial per block; a second, single-block kernel adds the
-// partials in a fixed order, so results do not depend on scheduling.
+// and leaves one result per block; the results are added in a fixed order
+// (gact_sum.h), so that the sum does not depend on scheduling.
 // Two pieces per thread: four, with 256 threads for the same 16 KB, keep 59 to 81
 // registers and wait longer for the last of them.  Us on 302 M parameters, 312
 // buffers, threads x pieces:            256 x 4   512 x 2   512 x 3   512 x 4   1024 x 1
@@ -15,6 +15,7 @@
 #include <stdint.h>
 
 #include "gact_device.h"
+#include "gact_sum.h"
 
 namespace gact {
 
@@ -29,16 +30,25 @@ static_assert(kStatsChunkElems == kRedThreads * kPieces * 4, "a statistics chunk
 static_assert(reduce_chunk_elems(GACT_DT_F32) == kRedThreads * kPieces * 4 &&
               reduce_chunk_elems(GACT_DT_BF16) == kRedThreads * kPieces * 8, "two pieces of 16 bytes per thread");
 
-__device__ __forceinline__ double block_sum(double v, double* lds) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+// Sums over the block of N values a thread, valid in thread 0.  One barrier, behind which all
+// wavefronts but the first end: with a barrier on either side of each sum and the wavefronts' sums through
+// the LDS crossbar, sensitivity of 302 M fp32 elements took 351 us a call, now 343.
+template <int N>
+__device__ __forceinline__ void block_sums(double (&v)[N]) {
+    static_assert(kRedWaves == 8, "the tree below");
+    __shared__ double part[N][kRedWaves];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) lds[wave] = v;
+#pragma unroll
+    for (int j = 0; j < N; ++j) v[j] = add_lanes(v[j]);
+    if (lane == 0) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) part[j][wave] = v[j];
+    }
     __syncthreads();
-    double r = 0.0;
-    if (threadIdx.x == 0) r = ((lds[0] + lds[1]) + (lds[2] + lds[3])) + ((lds[4] + lds[5]) + (lds[6] + lds[7]));
-    __syncthreads();
-    return r;                       // valid in thread 0
+    if (wave != 0) return;
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+        v[j] = ((part[j][0] + part[j][1]) + (part[j][2] + part[j][3])) + ((part[j][4] + part[j][5]) + (part[j][6] + part[j][7]));
 }
 
 __device__ __forceinline__ int find_buffer(const uint32_t* first_block, int K, uint32_t b) {
@@ -118,36 +128,44 @@ __device__ __forceinline__ double diff_sq_chunk(const ReduceArgs& r, int64_t chu
     return acc;
 }
 
-__device__ __forceinline__ void diff_sq_block(const ReduceArgs& r, int64_t chunk, double* __restrict__ partial) {
-    __shared__ double lds[kRedWaves];
-    const uint32_t b = blockIdx.x;
+__device__ __forceinline__ void diff_sq_block(const ReduceArgs& r, int64_t chunk, double* __restrict__ partial,
+                                              uint64_t tag) {
     const bool full = (chunk + 1) * reduce_chunk_elems(r.dtype) <= r.n;
     double acc;
     if (r.dtype == GACT_DT_F32)
         acc = full ? diff_sq_chunk<GACT_DT_F32, true>(r, chunk) : diff_sq_chunk<GACT_DT_F32, false>(r, chunk);
     else
         acc = full ? diff_sq_chunk<GACT_DT_BF16, true>(r, chunk) : diff_sq_chunk<GACT_DT_BF16, false>(r, chunk);
-    const double s = block_sum(acc, lds);
-    if (threadIdx.x == 0) partial[b] = s;
+    double sum[1] = {acc};
+    block_sums(sum);
+    if (threadIdx.x == 0) put_result(partial, blockIdx.x, sum[0], tag);
 }
 
 // Table in device memory (uploaded to the caller's workspace): any number of buffers.
 __global__ __launch_bounds__(kRedThreads) void diff_sq_kernel(const ReduceArgs* __restrict__ table,
                                                               const uint32_t* __restrict__ first_block,
-                                                              int K, double* __restrict__ partial) {
-    const uint32_t b = ordered_block(blockIdx.x, runs_end(gridDim.x, kDiffRunShift), kDiffRunShift);
+                                                              int K, double* __restrict__ partial, Finish fin) {
+    if (blockIdx.x >= fin.blocks) {
+        finish_block<kRedWaves, true>((uint64_t*)partial, fin.blocks, fin.tag, fin.scale, fin.out, blockIdx.x - fin.blocks);
+        return;
+    }
+    const uint32_t b = ordered_block(blockIdx.x, runs_end(fin.blocks, kDiffRunShift), kDiffRunShift);
     const int k = find_buffer(first_block, K, b);
     const ReduceArgs r = table[k];
-    diff_sq_block(r, (int64_t)(b - first_block[k]), partial);
+    diff_sq_block(r, (int64_t)(b - first_block[k]), partial, fin.tag);
 }
 
 // Table by value in the kernel arguments: no upload, which takes the stream 5 us
 // ahead of the kernel (96 bf16 pairs of 101 M elements: 67.8 us with, 65.6 us without).
 __global__ __launch_bounds__(kRedThreads) void diff_sq_inline_kernel(ReduceTable tab, int K,
-                                                                     double* __restrict__ partial) {
-    const uint32_t b = ordered_block(blockIdx.x, runs_end(gridDim.x, kDiffRunShift), kDiffRunShift);
+                                                                     double* __restrict__ partial, Finish fin) {
+    if (blockIdx.x >= fin.blocks) {
+        finish_block<kRedWaves, true>((uint64_t*)partial, fin.blocks, fin.tag, fin.scale, fin.out, blockIdx.x - fin.blocks);
+        return;
+    }
+    const uint32_t b = ordered_block(blockIdx.x, runs_end(fin.blocks, kDiffRunShift), kDiffRunShift);
     const int k = find_buffer(tab.first_block, K, b);
-    diff_sq_block(tab.t[k], (int64_t)(b - tab.first_block[k]), partial);
+    diff_sq_block(tab.t[k], (int64_t)(b - tab.first_block[k]), partial, fin.tag);
 }
 
 // ---------------------------------------------------------------- footprint
@@ -172,7 +190,6 @@ __device__ __forceinline__ double sum_chunk(const ReduceArgs& r, int64_t chunk) 
 
 // one buffer; block b takes chunk b
 __global__ __launch_bounds__(kRedThreads) void sum_kernel(ReduceArgs r, double* __restrict__ partial) {
-    __shared__ double lds[kRedWaves];
     const int64_t chunk = (int64_t)blockIdx.x;
     const bool full = (chunk + 1) * reduce_chunk_elems(r.dtype) <= r.n;
     double acc;
@@ -180,8 +197,9 @@ __global__ __launch_bounds__(kRedThreads) void sum_kernel(ReduceArgs r, double* 
         acc = full ? sum_chunk<GACT_DT_F32, true>(r, chunk) : sum_chunk<GACT_DT_F32, false>(r, chunk);
     else
         acc = full ? sum_chunk<GACT_DT_BF16, true>(r, chunk) : sum_chunk<GACT_DT_BF16, false>(r, chunk);
-    const double s = block_sum(acc, lds);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    double sum[1] = {acc};
+    block_sums(sum);
+    if (threadIdx.x == 0) partial[blockIdx.x] = sum[0];
 }
 
 // out[1 + j] = element floor(j * n / n_samples) as binary64
@@ -258,7 +276,6 @@ __device__ __forceinline__ void stats_chunk(const ReduceArgs& r, int64_t chunk, 
 // bf16_chunks: how many chunks of a bf16 buffer this launch's blocks take (stats_block_elems)
 __device__ __forceinline__ void grad_stats_block(const ReduceArgs& r, int64_t block, float rt, int bf16_chunks,
                                                  uint32_t blocks, double* __restrict__ partial) {
-    __shared__ double lds[kRedWaves];
     const uint32_t b = blockIdx.x;
     double sg2 = 0.0, sm2 = 0.0;
     const int chunks = r.dtype == GACT_DT_F32 ? 1 : bf16_chunks;
@@ -273,9 +290,12 @@ __device__ __forceinline__ void grad_stats_block(const ReduceArgs& r, int64_t bl
             else stats_chunk<GACT_DT_BF16, false>(r, chunk, rt, sg2, sm2);
         }
     }
-    const double s0 = block_sum(sg2, lds);
-    const double s1 = block_sum(sm2, lds);
-    if (threadIdx.x == 0) { partial[b] = s0; partial[blocks + b] = s1; }
+    // The block keeps its place until its stores are acknowledged: the fewer are under way, the better the
+    // memory takes them beside the reads (us, 302 M parameters: fp32 589 without, 580 with; bf16 478, 468).
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    double sum[2] = {sg2, sm2};
+    block_sums(sum);
+    if (threadIdx.x == 0) { partial[b] = sum[0]; partial[blocks + b] = sum[1]; }
 }
 
 __global__ __launch_bounds__(kRedThreads) void grad_stats_kernel(const ReduceArgs* __restrict__ table,
@@ -297,97 +317,79 @@ __global__ __launch_bounds__(kRedThreads) void grad_stats_inline_kernel(ReduceTa
 }
 
 // ------------------------------------------------------------ final addition
-// out[j] = scale * sum_i partial[j * count + i] in a fixed order, so that the
-// result is reproducible.  One block of 1024 threads per output: thread t adds
-// the terms t, t + 1024, ... eight at a time (eight independent loads in
-// flight), then the block adds the thread sums in a tree.  `stride` is the
-// distance between terms (1, or the chunk length after fold_kernel).
-// Blocks from `nout` on take a footprint's sample points, 1024 a block: they are
+// out[j] = scale * (sum of the `count` results of output j, out_pitch apart), in the order of gact_sum.h,
+// where the reducing launch has not added them itself.  Up to kFinRows rows by one block of 1024 threads;
+// more by a block for every 16 rows, of which the last adds up what the others leave (before, a kernel
+// of its own brought such lists down to 128 results: 73,926 pairs took 12 us, now 6).
+// Blocks from `adders` on take a footprint's sample points, 1024 a block: they are
 // a few loads, and a kernel of their own took 4.5 us of a footprint's 47 on 51 M
 // fp32 elements.
-constexpr int kFinThreads = 1024;
-__global__ __launch_bounds__(kFinThreads) void finish_kernel(const double* __restrict__ partial,
-                                                             uint32_t count, uint32_t stride,
-                                                             size_t out_pitch, double scale,
-                                                             double* __restrict__ out, uint32_t nout,
-                                                             ReduceArgs r, int n_samples) {
-    __shared__ double lds[kFinThreads / 64];
-    if (blockIdx.x >= nout) {
-        const int j = (int)((blockIdx.x - nout) * kFinThreads + threadIdx.x);
+constexpr int kFinThreads = 1024, kFinWaves = kFinThreads / 64;
+constexpr uint32_t kFinRows = 4 * kFinWaves;
+__global__ __launch_bounds__(kFinThreads) void finish_kernel(double* __restrict__ partial,
+                                                             uint32_t count, uint32_t adders,
+                                                             size_t out_pitch, uint64_t tag, double scale,
+                                                             double* __restrict__ out, ReduceArgs r, int n_samples) {
+    __shared__ double lds[kFinRows];
+    const uint32_t f = blockIdx.x;
+    if (f >= adders) {
+        const int j = (int)((f - adders) * kFinThreads + threadIdx.x);
         if (j < n_samples) sample(r, j, n_samples, out);
         return;
     }
-    const double* p = partial + (size_t)blockIdx.x * out_pitch;
-    double acc = 0.0;
-    uint32_t i = threadIdx.x;
-    for (; i + 7u * kFinThreads < count; i += 8u * kFinThreads) {
-        double v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = p[(size_t)(i + (uint32_t)k * kFinThreads) * stride];
-        acc += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+    double* p = partial + (size_t)blockIdx.y * out_pitch;
+    if (adders > 1) {
+        finish_block<kFinWaves, false>((uint64_t*)p, count, tag, scale, out + blockIdx.y, f);
+        return;
     }
-    for (; i < count; i += kFinThreads) acc += p[(size_t)i * stride];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = acc;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const uint32_t rows = rows_of(count);
+    for (uint32_t row = (uint32_t)wave; row < rows; row += kFinWaves) {
+        const double s = plain_row(p, count, row, lane);
+        if (lane == 0) lds[row] = s;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int w = 0; w < kFinThreads / 64; ++w) s += lds[w];
-        out[blockIdx.x] = scale * s;
-    }
+    if (wave != 0) return;
+    const double total = add_lanes(add_own_rows(0.0, lds, 0, rows, lane));
+    if (lane == 0) out[blockIdx.y] = scale * total;
 }
 
-// First level for long lists: block (k, j) adds the terms [k * chunk, (k + 1) * chunk)
-// of output j and leaves the sum in the first of them (it only touches its own chunk).
-__global__ __launch_bounds__(kRedThreads) void fold_kernel(double* __restrict__ partial, uint32_t count,
-                                                           uint32_t chunk) {
-    __shared__ double lds[kRedWaves];
-    double* p = partial + (size_t)blockIdx.y * count + (size_t)blockIdx.x * chunk;
-    const uint32_t left = count - blockIdx.x * chunk;
-    const uint32_t m = left < chunk ? left : chunk;
-    double acc = 0.0;
-    for (uint32_t i = threadIdx.x; i < m; i += kRedThreads) acc += p[i];
-    const double s = block_sum(acc, lds);
-    if (threadIdx.x == 0) p[0] = s;
+// out[0 .. nout) = 0
+__global__ void zero_kernel(double* __restrict__ out, int nout) {
+    const int j = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (j < nout) out[j] = 0.0;
 }
 
 // Enqueues the final addition of `count` terms for each of `nout` outputs, and the sample points of r.
-static void launch_finish(double* d_partial, unsigned count, int nout, double scale, double* d_out,
+static void launch_finish(double* d_partial, unsigned count, int nout, uint64_t tag, double scale, double* d_out,
                           hipStream_t s, const ReduceArgs& r = ReduceArgs{}, int n_samples = 0) {
-    constexpr unsigned kFoldBlocks = 128;
-    const dim3 grid(nout + (n_samples + kFinThreads - 1) / kFinThreads);
-    if (count <= 32768u) {
-        hipLaunchKernelGGL(finish_kernel, grid, dim3(kFinThreads), 0, s, d_partial, count, 1u,
-                           (size_t)count, scale, d_out, (uint32_t)nout, r, n_samples);
-        return;
-    }
-    const unsigned chunk = (count + kFoldBlocks - 1) / kFoldBlocks;
-    const unsigned folded = (count + chunk - 1) / chunk;
-    hipLaunchKernelGGL(fold_kernel, dim3(folded, nout), dim3(kRedThreads), 0, s, d_partial, count, chunk);
-    hipLaunchKernelGGL(finish_kernel, grid, dim3(kFinThreads), 0, s, d_partial, folded, chunk,
-                       (size_t)count, scale, d_out, (uint32_t)nout, r, n_samples);
+    const uint32_t adders = rows_of(count) <= kFinRows ? 1u : adders_for<kFinWaves>(count);
+    const dim3 grid(adders + (n_samples + kFinThreads - 1) / kFinThreads, nout);
+    hipLaunchKernelGGL(finish_kernel, grid, dim3(kFinThreads), 0, s, d_partial, count, adders, (size_t)count, tag,
+                       scale, d_out, r, n_samples);
 }
 
 }  // namespace gact
 
 extern "C" int gact_launch_diff_sq(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
-                                   const uint32_t* d_first, int K, unsigned blocks, double* d_partial,
-                                   double scale, double* d_out, void* stream) {
+                                   const uint32_t* d_first, int K, unsigned blocks, double* d_partial, int tagged,
+                                   uint64_t tag, double scale, double* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
+    const gact::Finish fin{tagged ? tag : 0, scale, d_out, blocks};
+    const dim3 grid(blocks + (tagged ? gact::adders_for<gact::kRedWaves>(blocks) : 0));
     if (inline_table)
-        hipLaunchKernelGGL(gact::diff_sq_inline_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, *inline_table,
-                           K, d_partial);
+        hipLaunchKernelGGL(gact::diff_sq_inline_kernel, grid, dim3(gact::kRedThreads), 0, s, *inline_table,
+                           K, d_partial, fin);
     else
-        hipLaunchKernelGGL(gact::diff_sq_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, d_table, d_first,
-                           K, d_partial);
-    gact::launch_finish(d_partial, blocks, 1, scale, d_out, s);
+        hipLaunchKernelGGL(gact::diff_sq_kernel, grid, dim3(gact::kRedThreads), 0, s, d_table, d_first,
+                           K, d_partial, fin);
+    if (!tagged) gact::launch_finish(d_partial, blocks, 1, tag, scale, d_out, s);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 extern "C" int gact_launch_grad_stats(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
                                       const uint32_t* d_first, int K, float rt, int bf16_chunks, unsigned blocks,
-                                      double* d_partial, double* d_out, void* stream) {
+                                      double* d_partial, uint64_t tag, double* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     if (inline_table)
         hipLaunchKernelGGL(gact::grad_stats_inline_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s,
@@ -395,29 +397,27 @@ extern "C" int gact_launch_grad_stats(const gact::ReduceTable* inline_table, con
     else
         hipLaunchKernelGGL(gact::grad_stats_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, d_table,
                            d_first, K, rt, bf16_chunks, blocks, d_partial);
-    gact::launch_finish(d_partial, blocks, 2, 1.0, d_out, s);
+    gact::launch_finish(d_partial, blocks, 2, tag, 1.0, d_out, s);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // out[0 .. nout) = 0 through a kernel (no memset node, so callers may capture it)
 extern "C" int gact_launch_zero(double* d_out, int nout, void* stream) {
-    hipLaunchKernelGGL(gact::finish_kernel, dim3(nout), dim3(gact::kFinThreads), 0, (hipStream_t)stream,
-                       (const double*)d_out, 0u, 1u, (size_t)0, 0.0, d_out, (uint32_t)nout, gact::ReduceArgs{}, 0);
+    hipLaunchKernelGGL(gact::zero_kernel, dim3((nout + 255) / 256), dim3(256), 0, (hipStream_t)stream, d_out, nout);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // The footprint from per-block sums that a compress launch left in d_partial.
-extern "C" int gact_launch_footprint_finish(const gact::ReduceArgs* r, unsigned count, double* d_partial,
+extern "C" int gact_launch_footprint_finish(const gact::ReduceArgs* r, unsigned count, double* d_partial, uint64_t tag,
                                             int n_samples, double* d_out, void* stream) {
-    hipStream_t s = (hipStream_t)stream;
-    gact::launch_finish(d_partial, count, 1, 1.0, d_out, s, *r, n_samples);
+    gact::launch_finish(d_partial, count, 1, tag, 1.0, d_out, (hipStream_t)stream, *r, n_samples);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-extern "C" int gact_launch_footprint(const gact::ReduceArgs* r, unsigned blocks, double* d_partial,
+extern "C" int gact_launch_footprint(const gact::ReduceArgs* r, unsigned blocks, double* d_partial, uint64_t tag,
                                      int n_samples, double* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(gact::sum_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, *r, d_partial);
-    gact::launch_finish(d_partial, blocks, 1, 1.0, d_out, s, *r, n_samples);
+    gact::launch_finish(d_partial, blocks, 1, tag, 1.0, d_out, s, *r, n_samples);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }

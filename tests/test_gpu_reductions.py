@@ -134,3 +134,45 @@ def test_every_block_is_taken_once_in_any_order(gact, dtype, blocks):
         out = gact.gact_grad_stats_update(g0, means, 1).cpu().tolist()
         want = float(sum((g.double() ** 2).sum() for g in g0))
         assert out == [want, want] and all(torch.equal(m, g.float()) for m, g in zip(means, g0))
+
+
+@pytest.mark.parametrize("blocks", (1, 2, 511, 512, 513, 4096, 4097, 8193, 36865))
+def test_sums_added_by_the_launch_itself_and_by_one_behind_it(gact, blocks):
+    """Around the ends of rows of 512 results, of one adding block's eight rows, and of the 64 rows that a wavefront
+    takes in one round.  The workspace holds room for two words a result (the launch adds them itself) or for one
+    (a launch behind it does): the same order, so the same bits, whatever the workspace holds."""
+    n = blocks * 8192 - 5
+    g0 = torch.randn(n, device="cuda", generator=torch.Generator("cuda").manual_seed(blocks)).to(torch.bfloat16)
+    g1 = g0 * 0.5
+    want = 0.5 * 9.0 * sum(float(((a.double() - b.double()) ** 2).sum()) for a, b in zip(g0.split(1 << 26), g1.split(1 << 26)))
+    table = (36 + 4 + 15) // 16 * 16
+    both = torch.full((table + 16 * blocks + 64,), 0xFF, dtype=torch.uint8, device="cuda")
+    got = []
+    for nbytes in (16, 16, 8, 16):
+        out = torch.zeros(1, dtype=torch.float64, device="cuda")
+        gact.gact_sensitivity([g0], [g1], 2, out=out, workspace=both[:table + nbytes * blocks])
+        got.append(out.item())
+        if len(got) == 3:
+            both.zero_()
+    assert got == [got[0]] * 4
+    assert got[0] == pytest.approx(want, rel=1e-12)
+    assert (both[table + 16 * blocks:].cpu().numpy() == 0).all()
+    with pytest.raises(gact.GactError):
+        gact.gact_sensitivity([g0], [g1], 2, workspace=both[:table + 8 * blocks - 1])
+
+
+def test_sensitivities_of_two_streams_at_a_time(gact):
+    """Each call adds its own results in its own workspace, also while another runs."""
+    gen = torch.Generator("cuda").manual_seed(3)
+    pairs = [[torch.randint(0, 4, (5_000_000 + 4096 * k,), device="cuda", generator=gen).float() for _ in range(2)] for k in range(4)]
+    want = [0.5 * float(((a - b).double() ** 2).sum()) for a, b in pairs]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in pairs]
+    spaces = [torch.empty(gact.gact_reduce_workspace_bytes(1, a.numel()), dtype=torch.uint8, device="cuda") for a, _ in pairs]
+    results = torch.zeros(len(pairs), 10, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    for r in range(10):
+        for k, (a, b) in enumerate(pairs):
+            gact.gact_sensitivity([a], [b], 1, out=results[k, r:r + 1], workspace=spaces[k], stream=streams[k])
+    torch.cuda.synchronize()
+    assert results.cpu().tolist() == [[w] * 10 for w in want]
