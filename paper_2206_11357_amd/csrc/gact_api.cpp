@@ -249,6 +249,7 @@ struct Reduction {
     const gact::ReduceArgs* d_table = nullptr;    // else uploaded to the workspace
     const uint32_t* d_first = nullptr;
     double* d_partial = nullptr;
+    bool wide = false;                            // statistics: blocks of 1024 threads
     bool tagged = false;                          // room for two words per result: the launch adds them itself
     const gact::ReduceTable* table() const { return is_inline ? &inline_table : nullptr; }
 };
@@ -291,6 +292,8 @@ int stage_reduction(const std::vector<gact::ReduceArgs>& bufs, bool statistics, 
     red->K = K;
     red->blocks = (unsigned)blocks;
     red->d_partial = (double*)((unsigned char*)d_workspace + tb);
+    red->wide = statistics && blocks >= gact::kWideStats &&
+                std::all_of(live.begin(), live.end(), [](const gact::ReduceArgs& r) { return r.dtype == GACT_F32 && aligned(r.b, 128); });
     red->tagged = !statistics && workspace_bytes >= tb + 2 * blocks * sizeof(double) && blocks < 0x70000000u;
     if (K <= gact::kInlineBuffers) {
         std::memcpy(red->inline_table.t, live.data(), (size_t)K * sizeof(gact::ReduceArgs));
@@ -442,7 +445,7 @@ int gact_grad_stats_update(const gact_grad_stat* h_stats, int K, int64_t t, doub
     if (const int rc = stage_reduction(bufs, true, d_workspace, workspace_bytes, stream, &red)) return rc;
     if (red.K == 0) return gact_launch_zero(d_out, 2, stream) == 0 ? GACT_OK : GACT_E_HIP;
     const float rt = (float)(1.0 / (double)t);
-    return gact_launch_grad_stats(red.table(), red.d_table, red.d_first, red.K, rt, red.bf16_chunks, red.blocks,
+    return gact_launch_grad_stats(red.table(), red.d_table, red.d_first, red.K, rt, red.bf16_chunks, red.wide, red.blocks,
                                   red.d_partial, next_tag(), d_out, stream) == 0 ? GACT_OK : GACT_E_HIP;
 }
 

@@ -152,6 +152,10 @@ constexpr int64_t stats_block_elems(int dtype, int bf16_chunks) {
 static_assert(stats_block_elems(GACT_DT_BF16, 2) == reduce_chunk_elems(GACT_DT_BF16) &&
               stats_block_elems(GACT_DT_F32, 2) == reduce_chunk_elems(GACT_DT_F32), "the least workspace");
 
+// A statistics launch of this many blocks and more, all of whose buffers are fp32 with a mean that starts
+// on a line, is one of wide blocks (stats_chunk).
+constexpr uint64_t kWideStats = 8192;
+
 // Decompress launch shape.  A unit is the 1 KB of output one coalesced
 // wavefront store covers (256 fp32 or 512 bf16 elements); a block of four
 // wavefronts takes 4 * units consecutive units.  Units per wavefront trade the
@@ -238,7 +242,7 @@ extern "C" int gact_launch_footprint(const gact::ReduceArgs* r, unsigned blocks,
                                      int n_samples, double* d_out, void* stream);
 extern "C" int gact_launch_zero(double* d_out, int nout, void* stream);
 extern "C" int gact_launch_grad_stats(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
-                                      const uint32_t* d_first, int K, float rt, int bf16_chunks, unsigned blocks,
+                                      const uint32_t* d_first, int K, float rt, int bf16_chunks, int wide, unsigned blocks,
                                       double* d_partial, uint64_t tag, double* d_out, void* stream);
 extern "C" int gact_launch_copy(void* dst, const void* src, uint64_t nbytes, unsigned workgroups, void* stream);
 extern "C" int gact_launch_multi_inline(int compress, const gact::InlineTable* tab, unsigned hint_shift,

@@ -26,17 +26,21 @@ typedef float    f4r __attribute__((ext_vector_type(4)));
 constexpr int kRedThreads = 512;
 constexpr int kPieces = 2;              // per thread and buffer
 constexpr int kRedWaves = kRedThreads / 64;
-static_assert(kStatsChunkElems == kRedThreads * kPieces * 4, "a statistics chunk is two pieces of four elements per thread");
+// A statistics chunk is two pieces of four elements per thread, or one of twice as many threads (stats_chunk).
+constexpr int stats_threads(bool wide) { return wide ? 1024 : kRedThreads; }
+constexpr int stats_pieces(bool wide) { return wide ? 1 : kPieces; }
+static_assert(kStatsChunkElems == stats_threads(false) * stats_pieces(false) * 4 &&
+              kStatsChunkElems == stats_threads(true) * stats_pieces(true) * 4, "the elements of a statistics chunk");
 static_assert(reduce_chunk_elems(GACT_DT_F32) == kRedThreads * kPieces * 4 &&
               reduce_chunk_elems(GACT_DT_BF16) == kRedThreads * kPieces * 8, "two pieces of 16 bytes per thread");
 
 // Sums over the block of N values a thread, valid in thread 0.  One barrier, behind which all
 // wavefronts but the first end: with a barrier on either side of each sum and the wavefronts' sums through
 // the LDS crossbar, sensitivity of 302 M fp32 elements took 351 us a call, now 343.
-template <int N>
+template <int WAVES, int N>
 __device__ __forceinline__ void block_sums(double (&v)[N]) {
-    static_assert(kRedWaves == 8, "the tree below");
-    __shared__ double part[N][kRedWaves];
+    static_assert((WAVES & (WAVES - 1)) == 0, "the tree below");
+    __shared__ double part[N][WAVES];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
     for (int j = 0; j < N; ++j) v[j] = add_lanes(v[j]);
@@ -47,8 +51,16 @@ __device__ __forceinline__ void block_sums(double (&v)[N]) {
     __syncthreads();
     if (wave != 0) return;
 #pragma unroll
-    for (int j = 0; j < N; ++j)
-        v[j] = ((part[j][0] + part[j][1]) + (part[j][2] + part[j][3])) + ((part[j][4] + part[j][5]) + (part[j][6] + part[j][7]));
+    for (int j = 0; j < N; ++j) {
+        double s[WAVES];
+#pragma unroll
+        for (int i = 0; i < WAVES; ++i) s[i] = part[j][i];
+#pragma unroll
+        for (int m = WAVES / 2; m > 0; m /= 2)
+#pragma unroll
+            for (int i = 0; i < m; ++i) s[i] = s[2 * i] + s[2 * i + 1];
+        v[j] = s[0];
+    }
 }
 
 __device__ __forceinline__ int find_buffer(const uint32_t* first_block, int K, uint32_t b) {
@@ -137,7 +149,7 @@ __device__ __forceinline__ void diff_sq_block(const ReduceArgs& r, int64_t chunk
     else
         acc = full ? diff_sq_chunk<GACT_DT_BF16, true>(r, chunk) : diff_sq_chunk<GACT_DT_BF16, false>(r, chunk);
     double sum[1] = {acc};
-    block_sums(sum);
+    block_sums<kRedWaves>(sum);
     if (threadIdx.x == 0) put_result(partial, blockIdx.x, sum[0], tag);
 }
 
@@ -198,7 +210,7 @@ __global__ __launch_bounds__(kRedThreads) void sum_kernel(ReduceArgs r, double* 
     else
         acc = full ? sum_chunk<GACT_DT_BF16, true>(r, chunk) : sum_chunk<GACT_DT_BF16, false>(r, chunk);
     double sum[1] = {acc};
-    block_sums(sum);
+    block_sums<kRedWaves>(sum);
     if (threadIdx.x == 0) partial[blockIdx.x] = sum[0];
 }
 
@@ -231,24 +243,35 @@ __device__ __forceinline__ u4r load_bf16x4(const void* base, int64_t e, int64_t 
 // A piece is four elements for both types of gradient, so that neighbouring lanes read and write
 // neighbouring 16 bytes of the mean.  (With 16 bytes of a bf16 gradient per lane, every lane had two
 // 16-byte pieces of the mean 32 bytes from the next lane's, loads and stores of half lines: 764 us for
-// 302 M parameters, 312 buffers, now 506 us, 6.0 TB/s.)
-template <int DT, bool FULL>
+// 302 M parameters, 312 buffers, now 472 us, 6.4 TB/s.)
+//
+// WIDE: one piece a thread, blocks of 1024, the mean written through the L2 (non-temporal, device scope).  A
+// wavefront's stores are then one burst of 1 KB a block, which HBM takes better beside two streams of
+// reads, but the block's sum is a larger part of its life.  Us, fp32, hidden width and parameters:
+//               1024, 302 M   768, 170 M   1024, 101 M   1024, 50 M   768, 28 M   384, 2.4 M   1000, 360 M
+//   512 x 2         581           325          194          98.0         57.2         11.0          693
+//   1024 x 1        552           315          188          97.0         57.4         11.6          707
+// So it is for launches of kWideStats blocks and more (stage_reduction), and only where every mean starts
+// on a line: in the last column most do not, and a line that two wavefronts write leaves in two parts.  bf16
+// gradients, half the bytes for as much to add up: 1024 x 1 takes 507 us on 302 M parameters, 512 x 2 472.
+template <int DT, bool FULL, bool WIDE>
 __device__ __forceinline__ void stats_chunk(const ReduceArgs& r, int64_t chunk, float rt,
                                             double& sg2, double& sm2) {
+    constexpr int T = stats_threads(WIDE), P = stats_pieces(WIDE);
     const int64_t e0 = chunk * kStatsChunkElems + (int64_t)threadIdx.x * 4;
     float* mean = (float*)r.b;
-    u4r g[kPieces];
-    f4r m[kPieces];
+    u4r g[P];
+    f4r m[P];
 #pragma unroll
-    for (int k = 0; k < kPieces; ++k) {
-        const int64_t e = e0 + (int64_t)k * kRedThreads * 4;
+    for (int k = 0; k < P; ++k) {
+        const int64_t e = e0 + (int64_t)k * T * 4;
         if (DT == GACT_DT_F32) g[k] = load_piece16<GACT_DT_F32, FULL>(r.a, e, r.n);
         else g[k] = load_bf16x4<FULL>(r.a, e, r.n);
         m[k] = __builtin_bit_cast(f4r, load_piece16<GACT_DT_F32, FULL>(mean, e, r.n));
     }
 #pragma unroll
-    for (int k = 0; k < kPieces; ++k) {
-        const int64_t e = e0 + (int64_t)k * kRedThreads * 4;
+    for (int k = 0; k < P; ++k) {
+        const int64_t e = e0 + (int64_t)k * T * 4;
         float x[8];
         unpack_piece<DT>(g[k], x);
         const float old[4] = {m[k].x, m[k].y, m[k].z, m[k].w};
@@ -264,8 +287,15 @@ __device__ __forceinline__ void stats_chunk(const ReduceArgs& r, int64_t chunk, 
                 sm2 += (double)nw[j] * (double)nw[j];
             }
         }
-        if (FULL || e + 4 <= r.n) {
-            const f4r o = {nw[0], nw[1], nw[2], nw[3]};
+        const f4r o = {nw[0], nw[1], nw[2], nw[3]};
+        if (FULL && WIDE) {
+            // The offset is the lanes' own and there is no scalar one: with a scalar offset the compiler
+            // leaves out the wait states between such a store and the next write to its data registers.
+            constexpr int kBytes = (int)kStatsChunkElems * 4, kThrough = 2 | 16;      // nt, sc1
+            const __amdgpu_buffer_rsrc_t span =
+                __builtin_amdgcn_make_buffer_rsrc(mean + chunk * kStatsChunkElems, 0, kBytes, 0x00027000);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4r, o), span, (int)threadIdx.x * 16, 0, kThrough);
+        } else if (FULL || e + 4 <= r.n) {
             __builtin_nontemporal_store(o, (f4r*)(mean + e));
         } else {
             for (int j = 0; j < 4; ++j) if (e + j < r.n) mean[e + j] = nw[j];
@@ -274,46 +304,49 @@ __device__ __forceinline__ void stats_chunk(const ReduceArgs& r, int64_t chunk, 
 }
 
 // bf16_chunks: how many chunks of a bf16 buffer this launch's blocks take (stats_block_elems)
+template <bool WIDE>
 __device__ __forceinline__ void grad_stats_block(const ReduceArgs& r, int64_t block, float rt, int bf16_chunks,
                                                  uint32_t blocks, double* __restrict__ partial) {
     const uint32_t b = blockIdx.x;
     double sg2 = 0.0, sm2 = 0.0;
-    const int chunks = r.dtype == GACT_DT_F32 ? 1 : bf16_chunks;
-    int64_t chunk = block * chunks;
-    if (r.dtype == GACT_DT_F32) {
-        if ((chunk + 1) * kStatsChunkElems <= r.n) stats_chunk<GACT_DT_F32, true>(r, chunk, rt, sg2, sm2);
-        else stats_chunk<GACT_DT_F32, false>(r, chunk, rt, sg2, sm2);
+    if (WIDE || r.dtype == GACT_DT_F32) {
+        if ((block + 1) * kStatsChunkElems <= r.n) stats_chunk<GACT_DT_F32, true, WIDE>(r, block, rt, sg2, sm2);
+        else stats_chunk<GACT_DT_F32, false, WIDE>(r, block, rt, sg2, sm2);
     } else {
+        int64_t chunk = block * bf16_chunks;
 #pragma unroll 1
-        for (const int64_t end = chunk + chunks; chunk < end; ++chunk) {
-            if ((chunk + 1) * kStatsChunkElems <= r.n) stats_chunk<GACT_DT_BF16, true>(r, chunk, rt, sg2, sm2);
-            else stats_chunk<GACT_DT_BF16, false>(r, chunk, rt, sg2, sm2);
+        for (const int64_t end = chunk + bf16_chunks; chunk < end; ++chunk) {
+            if ((chunk + 1) * kStatsChunkElems <= r.n) stats_chunk<GACT_DT_BF16, true, false>(r, chunk, rt, sg2, sm2);
+            else stats_chunk<GACT_DT_BF16, false, false>(r, chunk, rt, sg2, sm2);
         }
     }
     // The block keeps its place until its stores are acknowledged: the fewer are under way, the better the
-    // memory takes them beside the reads (us, 302 M parameters: fp32 589 without, 580 with; bf16 478, 468).
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // memory takes them beside the reads (us, 302 M parameters: fp32 589 without, 580 with; bf16 478, 468;
+    // WIDE 552 without, 571 with).
+    if (!WIDE) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     double sum[2] = {sg2, sm2};
-    block_sums(sum);
+    block_sums<stats_threads(WIDE) / 64>(sum);
     if (threadIdx.x == 0) { partial[b] = sum[0]; partial[blocks + b] = sum[1]; }
 }
 
-__global__ __launch_bounds__(kRedThreads) void grad_stats_kernel(const ReduceArgs* __restrict__ table,
-                                                                 const uint32_t* __restrict__ first_block,
-                                                                 int K, float rt, int bf16_chunks, uint32_t blocks,
-                                                                 double* __restrict__ partial) {
+template <bool WIDE>
+__global__ __launch_bounds__(stats_threads(WIDE)) void grad_stats_kernel(const ReduceArgs* __restrict__ table,
+                                                                         const uint32_t* __restrict__ first_block,
+                                                                         int K, float rt, int bf16_chunks, uint32_t blocks,
+                                                                         double* __restrict__ partial) {
     const uint32_t b = ordered_block(blockIdx.x, runs_end(blocks, kStatsRunShift), kStatsRunShift);
     const int k = find_buffer(first_block, K, b);
     const ReduceArgs r = table[k];
-    grad_stats_block(r, (int64_t)(b - first_block[k]), rt, bf16_chunks, blocks, partial);
+    grad_stats_block<WIDE>(r, (int64_t)(b - first_block[k]), rt, bf16_chunks, blocks, partial);
 }
 
-__global__ __launch_bounds__(kRedThreads) void grad_stats_inline_kernel(ReduceTable tab, int K, float rt,
-                                                                        int bf16_chunks, uint32_t blocks,
-                                                                        double* __restrict__ partial) {
+template <bool WIDE>
+__global__ __launch_bounds__(stats_threads(WIDE)) void grad_stats_inline_kernel(ReduceTable tab, int K, float rt,
+                                                                                int bf16_chunks, uint32_t blocks,
+                                                                                double* __restrict__ partial) {
     const uint32_t b = ordered_block(blockIdx.x, runs_end(blocks, kStatsRunShift), kStatsRunShift);
     const int k = find_buffer(tab.first_block, K, b);
-    grad_stats_block(tab.t[k], (int64_t)(b - tab.first_block[k]), rt, bf16_chunks, blocks, partial);
+    grad_stats_block<WIDE>(tab.t[k], (int64_t)(b - tab.first_block[k]), rt, bf16_chunks, blocks, partial);
 }
 
 // ------------------------------------------------------------ final addition
@@ -387,16 +420,24 @@ extern "C" int gact_launch_diff_sq(const gact::ReduceTable* inline_table, const 
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+template <bool WIDE>
+static void launch_stats(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table, const uint32_t* d_first,
+                         int K, float rt, int bf16_chunks, unsigned blocks, double* d_partial, hipStream_t s) {
+    const dim3 grid(blocks), block(gact::stats_threads(WIDE));
+    if (inline_table)
+        hipLaunchKernelGGL(gact::grad_stats_inline_kernel<WIDE>, grid, block, 0, s, *inline_table, K, rt, bf16_chunks,
+                           blocks, d_partial);
+    else
+        hipLaunchKernelGGL(gact::grad_stats_kernel<WIDE>, grid, block, 0, s, d_table, d_first, K, rt, bf16_chunks,
+                           blocks, d_partial);
+}
+
 extern "C" int gact_launch_grad_stats(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
-                                      const uint32_t* d_first, int K, float rt, int bf16_chunks, unsigned blocks,
+                                      const uint32_t* d_first, int K, float rt, int bf16_chunks, int wide, unsigned blocks,
                                       double* d_partial, uint64_t tag, double* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
-    if (inline_table)
-        hipLaunchKernelGGL(gact::grad_stats_inline_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s,
-                           *inline_table, K, rt, bf16_chunks, blocks, d_partial);
-    else
-        hipLaunchKernelGGL(gact::grad_stats_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, d_table,
-                           d_first, K, rt, bf16_chunks, blocks, d_partial);
+    if (wide) launch_stats<true>(inline_table, d_table, d_first, K, rt, bf16_chunks, blocks, d_partial, s);
+    else launch_stats<false>(inline_table, d_table, d_first, K, rt, bf16_chunks, blocks, d_partial, s);
     gact::launch_finish(d_partial, blocks, 2, tag, 1.0, d_out, s);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }

@@ -176,3 +176,28 @@ def test_sensitivities_of_two_streams_at_a_time(gact):
             gact.gact_sensitivity([a], [b], 1, out=results[k, r:r + 1], workspace=spaces[k], stream=streams[k])
     torch.cuda.synchronize()
     assert results.cpu().tolist() == [[w] * 10 for w in want]
+
+
+@pytest.mark.parametrize("K", (1, 105))
+@pytest.mark.parametrize("blocks,shift", [(8191, 0), (8192, 0), (8192, 4), (8193 + 40, 0)])
+def test_statistics_in_wide_blocks(gact, K, blocks, shift):
+    """The shortest launch of wide blocks and the longest of the others, means that start on a line and 16 bytes
+    behind one, buffers that end inside a chunk, inside a piece and on a chunk's end; the tables of both kinds.
+    Element by element as torch computes the three operations; sums of whole numbers, exact in binary64."""
+    sizes = [4096 * (blocks - K + 1)] + [4096] * (K - 1)
+    if blocks % 2:
+        sizes[0] -= 4093
+        sizes[-1] -= 1 if K > 1 else 0
+    g, means = [], []
+    for k, n in enumerate(sizes):
+        g.append(((torch.arange(n, device="cuda") * 7 + k) % 33 - 16).float())
+        room = torch.full((n + shift + 32,), 5.0, device="cuda")
+        room[shift:shift + n] = ((torch.arange(n, device="cuda") + 3 * k) % 17 - 8).float()
+        means.append(room)
+    views = [m[shift:shift + n] for m, n in zip(means, sizes)]
+    want = [v + (x - v) * 0.5 for x, v in zip(g, views)]
+    out = gact.gact_grad_stats_update(g, views, 2).cpu().tolist()
+    assert out == [float(sum((x.double() ** 2).sum() for x in g)), float(sum((w.double() ** 2).sum() for w in want))]
+    for m, w in zip(means, want):
+        assert torch.equal(m[shift:shift + w.numel()], w)
+        assert bool((m[:shift] == 5.0).all()) and bool((m[shift + w.numel():] == 5.0).all())
