@@ -106,6 +106,14 @@ int refuse_if_capturing(void* stream) {
     return status == hipStreamCaptureStatusNone ? GACT_OK : GACT_E_CAPTURE;
 }
 
+// Whether a launch on `stream` would be recorded into a graph (or that cannot be told).
+bool recorded(void* stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing((hipStream_t)stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();          // not the launch's error
+    return true;
+}
+
 // Enqueues a copy of a launch table to the workspace; `src` may go when this returns (it is pageable
 // memory, of which the runtime takes its own copy first).  The runtime moves up to 16 KB with a small
 // kernel, 4.6 us of the stream, and more with the DMA engine, whose hand-over leaves the stream idle for
@@ -351,10 +359,18 @@ int compress_footprint(const void* d_x, gact_dtype dtype, int64_t n, int group_s
         return limited ? GACT_E_SCRATCH : GACT_E_ARG;
     const int64_t blocks = blocks_for(true, t, geo);
     if (blocks > 0x7FFFFFFFll) return GACT_E_ARG;
-    if (gact_launch_compress_sum(&t, &geo, (unsigned)blocks, (double*)d_workspace, stream) != 0)
+    // The launch adds its sums itself where the workspace has two words for each (all of the documented size
+    // have from two tiles on) and the tag is this call's alone: not in a graph, whose replays share one, nor in
+    // the library's scratch area, which calls that overlap in time may overwrite under each other.
+    const uint64_t tag = next_tag();
+    const bool tagged = !limited && workspace_bytes >= 2 * (size_t)blocks * sizeof(double) && blocks < 0x70000000 &&
+                        !recorded(stream);
+    if (gact_launch_compress_sum(&t, &geo, (unsigned)blocks, (double*)d_workspace, tagged, tag, n_samples, d_footprint,
+                                 stream) != 0)
         return GACT_E_HIP;
+    if (tagged) return GACT_OK;
     const gact::ReduceArgs r{d_x, nullptr, n, (int32_t)dtype, 0};
-    return gact_launch_footprint_finish(&r, (unsigned)blocks, (double*)d_workspace, next_tag(), n_samples,
+    return gact_launch_footprint_finish(&r, (unsigned)blocks, (double*)d_workspace, tag, n_samples,
                                         d_footprint, stream) == 0 ? GACT_OK : GACT_E_HIP;
 }
 

@@ -235,7 +235,8 @@ extern "C" int gact_launch_diff_sq(const gact::ReduceTable* inline_table, const 
                                    const uint32_t* d_first, int K, unsigned blocks, double* d_partial, int tagged,
                                    uint64_t tag, double scale, double* d_out, void* stream);
 extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::Geometry* geo,
-                                        unsigned blocks, double* d_block_sum, void* stream);
+                                        unsigned blocks, double* d_block_sum, int tagged, uint64_t tag,
+                                        int n_samples, double* d_out, void* stream);
 extern "C" int gact_launch_footprint_finish(const gact::ReduceArgs* r, unsigned count, double* d_partial, uint64_t tag,
                                             int n_samples, double* d_out, void* stream);
 extern "C" int gact_launch_footprint(const gact::ReduceArgs* r, unsigned blocks, double* d_partial, uint64_t tag,

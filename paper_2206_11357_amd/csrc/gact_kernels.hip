@@ -37,6 +37,7 @@
 #include <stdint.h>
 
 #include "gact_device.h"
+#include "gact_sum.h"
 
 namespace gact {
 
@@ -493,9 +494,7 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j)
             if (KIND == kFull || j < left_here) acc += (double)v[j];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-        tile_sum = acc;
+        tile_sum = add_lanes(acc);
     }
 
     // Places past the end take the last valid element: it belongs to the last group, whose minimum and
@@ -912,16 +911,25 @@ GACT_KERNEL(W) single_kernel(uint32_t run_end, uint32_t shift_or_full, TensorArg
 
 // One tensor, compressed, with the sum of every block's elements as a by-product.  (One sum per block
 // and not per tile: the addition that follows reads a quarter of the terms, and the barrier costs
-// nothing, because a block's LDS is not given back before its last wavefront ends.)
+// nothing, because a block's LDS is not given back before its last wavefront ends.)  Behind fin.blocks
+// blocks come those that take the sample points and add the sums, if these are tagged.
 __global__ __launch_bounds__(kBlockThreads) void compress_sum_kernel(uint32_t run_end, uint32_t run_shift, TensorArgs t,
-                                                                     Geometry geo, double* __restrict__ block_sum) {
+                                                                     Geometry geo, double* __restrict__ block_sum,
+                                                                     Finish fin, int n_samples) {
     __shared__ double part[kWavesPerBlk];
+    if (blockIdx.x >= fin.blocks) {
+        const uint32_t f = blockIdx.x - fin.blocks, adders = adders_for<kWavesPerBlk>(fin.blocks);
+        for (int j = (int)(f * kBlockThreads + threadIdx.x); j < n_samples; j += (int)(adders * kBlockThreads))
+            sample(t.io, t.dtype(), t.n, j, n_samples, fin.out);
+        finish_block<kWavesPerBlk, true>((uint64_t*)block_sum, fin.blocks, fin.tag, fin.scale, fin.out, f);
+        return;
+    }
     const uint32_t b = work_block(run_end, run_shift);
     double sum = 0.0;                                 // stays so for a wavefront past the end
     compress_block<true, true>(t, geo, (int64_t)b, sum);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
     __syncthreads();
-    if (threadIdx.x == 0) block_sum[b] = (part[0] + part[1]) + (part[2] + part[3]);
+    if (threadIdx.x == 0) put_result(block_sum, b, (part[0] + part[1]) + (part[2] + part[3]), fin.tag);
 }
 
 // Multi-tensor: block b belongs to the tensor l with first_block[l] <= b <
@@ -996,12 +1004,15 @@ extern "C" int gact_launch_single(int compress, const gact::TensorArgs* t, const
     GACT_LAUNCH(gact::single_kernel, runs.end, compress ? runs.shift : full_blocks, *t, *geo);
 }
 
-extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::Geometry* geo,
-                                        unsigned blocks, double* d_block_sum, void* stream) {
+extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::Geometry* geo, unsigned blocks,
+                                        double* d_block_sum, int tagged, uint64_t tag, int n_samples, double* d_out,
+                                        void* stream) {
     const unsigned lds = 4u * gact::kWavesPerBlk * (unsigned)geo->lds_wave_dwords;
     const gact::Runs runs = gact::runs_for(true, blocks);
-    hipLaunchKernelGGL(gact::compress_sum_kernel, dim3(blocks), dim3(gact::kBlockThreads), lds,
-                       (hipStream_t)stream, runs.end, runs.shift, *t, *geo, d_block_sum);
+    const gact::Finish fin{tagged ? tag : 0, 1.0, d_out, blocks};
+    const dim3 grid(blocks + (tagged ? gact::adders_for<gact::kWavesPerBlk>(blocks) : 0));
+    hipLaunchKernelGGL(gact::compress_sum_kernel, grid, dim3(gact::kBlockThreads), lds,
+                       (hipStream_t)stream, runs.end, runs.shift, *t, *geo, d_block_sum, fin, n_samples);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -214,15 +214,6 @@ __global__ __launch_bounds__(kRedThreads) void sum_kernel(ReduceArgs r, double* 
     if (threadIdx.x == 0) partial[blockIdx.x] = sum[0];
 }
 
-// out[1 + j] = element floor(j * n / n_samples) as binary64
-__device__ __forceinline__ void sample(const ReduceArgs& r, int j, int n_samples, double* __restrict__ out) {
-    const int64_t i = (int64_t)(((unsigned __int128)(uint64_t)j * (uint64_t)r.n) / (uint64_t)n_samples);
-    float v;
-    if (r.dtype == GACT_DT_F32) v = ((const float*)r.a)[i];
-    else v = __builtin_bit_cast(float, (uint32_t)((const uint16_t*)r.a)[i] << 16);
-    out[1 + j] = (double)v;
-}
-
 // ------------------------------------------------------- gradient statistics
 // Four elements of a bf16 buffer from element e on, as load_piece16 (in the low half).
 template <bool FULL>
@@ -367,7 +358,7 @@ __global__ __launch_bounds__(kFinThreads) void finish_kernel(double* __restrict_
     const uint32_t f = blockIdx.x;
     if (f >= adders) {
         const int j = (int)((f - adders) * kFinThreads + threadIdx.x);
-        if (j < n_samples) sample(r, j, n_samples, out);
+        if (j < n_samples) sample(r.a, r.dtype, r.n, j, n_samples, out);
         return;
     }
     double* p = partial + (size_t)blockIdx.y * out_pitch;

@@ -29,6 +29,8 @@
 
 #include <stdint.h>
 
+#include "gact_device.h"
+
 namespace gact {
 
 constexpr uint32_t kRowTerms = 512;               // eight a lane: their loads are in flight together
@@ -177,6 +179,15 @@ __device__ __forceinline__ void finish_block(uint64_t* words, uint32_t count, ui
     if (wave != 0) return;
     const double total = add_lanes(add_own_rows(acc, lds, f * WAVES, rows, lane));
     if (lane == 0) *out = scale * total;
+}
+
+// A footprint's sample point: out[1 + j] = element floor(j * n / n_samples) as binary64
+__device__ __forceinline__ void sample(const void* x, int dtype, int64_t n, int j, int n_samples, double* __restrict__ out) {
+    const int64_t i = (int64_t)(((unsigned __int128)(uint64_t)j * (uint64_t)n) / (uint64_t)n_samples);
+    float v;
+    if (dtype == GACT_DT_F32) v = ((const float*)x)[i];
+    else v = __builtin_bit_cast(float, (uint32_t)((const uint16_t*)x)[i] << 16);
+    out[1 + j] = (double)v;
 }
 #endif  // __HIPCC__
 

@@ -201,3 +201,34 @@ def test_statistics_in_wide_blocks(gact, K, blocks, shift):
     for m, w in zip(means, want):
         assert torch.equal(m[shift:shift + w.numel()], w)
         assert bool((m[:shift] == 5.0).all()) and bool((m[shift + w.numel():] == 5.0).all())
+
+
+@pytest.mark.parametrize("n", (2048, 2049, 8192 * 512, 8192 * 2049 + 7))
+def test_footprints_recorded_into_a_graph(gact, n):
+    """A recorded call adds its sums in a launch behind, whose replays share one tag; sizes of one tile (no room for
+    two words a sum), of one row of sums and of more rows than one adding block has.  Replayed on changed inputs
+    with eager calls on the same workspace in between, and compared with an eager call's bits."""
+    G, bits, ns = 256, 2, 5
+    x = torch.empty(n, device="cuda")
+    p, mn, sc = gact.alloc_compressed(n, G, bits, x.device)
+    ws = torch.zeros(gact.gact_compress_footprint_workspace_bytes(n, G), dtype=torch.uint8, device="cuda")
+    fp = torch.zeros(1 + ns, dtype=torch.float64, device="cuda")
+    gen = torch.Generator("cuda").manual_seed(n)
+    x.normal_(generator=gen)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        gact.gact_compress_footprint(x, G, bits, 3, ns, p, mn, sc, fp, ws)
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gact.gact_compress_footprint(x, G, bits, 3, ns, p, mn, sc, fp, ws)
+    for _ in range(4):
+        x.normal_(generator=gen)
+        graph.replay()
+        got = [t.clone() for t in (p, mn, sc, fp)]
+        fp.zero_()
+        gact.gact_compress_footprint(x, G, bits, 3, ns, p, mn, sc, fp, ws)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, (p, mn, sc, fp)))
+        assert fp[0].item() == pytest.approx(float(x.double().sum()), abs=60 * 1.2e-16 * float(x.abs().double().sum()))
