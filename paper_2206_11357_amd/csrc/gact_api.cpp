@@ -25,7 +25,6 @@ static __device__ __align__(256) unsigned char scratch[GACT_NOALLOC_SCRATCH_BYTE
 namespace {
 
 constexpr int kPerLane = 32;
-constexpr int kWavesPerBlock = 4;
 
 bool bits_ok(int bits) { return bits == 1 || bits == 2 || bits == 4 || bits == 8; }
 bool group_ok(int g) { return g >= 32 && g <= 1024 && g % 32 == 0; }
@@ -80,21 +79,35 @@ int make_args(bool compress, const void* x, void* packed, float* gmin, float* gs
     return GACT_OK;
 }
 
-// blocks a tensor needs: compress takes 4 wavefront tiles per block, decompress
+// blocks a tensor needs: compress takes a wavefront per tile, decompress
 // a fixed span of elements per block
-int64_t blocks_for(bool compress, const gact::TensorArgs& t, const gact::Geometry& geo,
-                   uint32_t bf16_units = gact::kDecUnitsBf16) {
-    if (compress) return (tiles_for(t.n, geo) + kWavesPerBlock - 1) / kWavesPerBlock;
-    const int64_t span = gact::dec_block_elems(t.dtype(), t.bits(), bf16_units);
+int64_t blocks_for(gact::Work work, const gact::TensorArgs& t, const gact::Geometry& geo) {
+    const int waves = gact::waves_per_block(work);
+    if (!decompresses(work)) return (tiles_for(t.n, geo) + waves - 1) / waves;
+    const int64_t span = gact::dec_block_elems(t.dtype(), t.bits(), work == gact::kDecompressShort ? gact::kDecUnitsBf16Short : gact::kDecUnitsBf16);
     return (t.n + span - 1) / span;
+}
+
+// The kind of a launch, from the LDS its widest dtype needs; then, its blocks counted as those of that kind,
+// the kind it is launched as.
+gact::Work work_for(bool compress, const gact::Geometry& geo) {
+    if (!compress) return gact::kDecompress;
+    return geo.lds_wave_dwords == gact::lds_dwords_per_wave(GACT_BF16) ? gact::kCompressBf16 : gact::kCompressAny;
+}
+gact::Work work_of_length(gact::Work work, uint64_t blocks) {
+    if (work == gact::kDecompress && blocks < gact::kShortLaunch) return gact::kDecompressShort;
+    if (work == gact::kCompressAny && blocks >= gact::kLongCompress && blocks <= 0x7FFFFFFFull / 4) return gact::kCompressLong;
+    return work;
 }
 
 int run_single(bool compress, const gact::TensorArgs& t, const gact::Geometry& geo, void* stream) {
     if (t.n == 0) return GACT_OK;
-    int64_t blocks = blocks_for(compress, t, geo);
+    const gact::Work work = work_for(compress, geo);
+    int64_t blocks = blocks_for(work, t, geo);
     if (blocks > 0x7FFFFFFFll) return GACT_E_ARG;
-    if (!compress && blocks < (int64_t)gact::kShortLaunch) blocks = blocks_for(compress, t, geo, gact::kDecUnitsBf16Short);
-    return gact_launch_single(compress ? 1 : 0, &t, &geo, (unsigned)blocks, stream) == 0
+    const gact::Work final_work = work_of_length(work, (uint64_t)blocks);
+    if (final_work != work) blocks = blocks_for(final_work, t, geo);
+    return gact_launch_single(final_work, &t, &geo, (unsigned)blocks, stream) == 0
                ? GACT_OK : GACT_E_HIP;
 }
 
@@ -183,16 +196,18 @@ int run_multi(bool compress, const gact_tensor_desc* descs, int L, int group_siz
         first.push_back((uint32_t)blocks);
         table.push_back(t);
         geo.lds_wave_dwords = std::max(geo.lds_wave_dwords, gact::lds_dwords_per_wave(d.dtype));
-        blocks += (uint64_t)blocks_for(compress, t, geo);
+        blocks += (uint64_t)blocks_for(compress ? gact::kCompressAny : gact::kDecompress, t, geo);
         if (blocks > 0x7FFFFFFFull) return GACT_E_ARG;
     }
     const int live = (int)table.size();
     if (live == 0) return GACT_OK;
-    if (!compress && blocks < gact::kShortLaunch) {
+    gact::Work work = work_for(compress, geo);
+    if (const gact::Work w = work_of_length(work, blocks); w != work) {
+        work = w;
         blocks = 0;
         for (int l = 0; l < live; ++l) {
             first[l] = (uint32_t)blocks;
-            blocks += (uint64_t)blocks_for(compress, table[l], geo, gact::kDecUnitsBf16Short);
+            blocks += (uint64_t)blocks_for(work, table[l], geo);
         }
     }
     first.push_back((uint32_t)blocks);
@@ -210,7 +225,7 @@ int run_multi(bool compress, const gact_tensor_desc* descs, int L, int group_siz
         std::vector<uint8_t> hint;
         const unsigned shift = make_hints(first, gact::kInlineHints, &hint);
         for (size_t k = 0; k < hint.size(); ++k) tab.hint[k >> 2] |= (uint32_t)hint[k] << ((k & 3) * 8);
-        return gact_launch_multi_inline(compress ? 1 : 0, &tab, shift, &geo, (unsigned)blocks, stream) == 0
+        return gact_launch_multi_inline(work, &tab, shift, &geo, (unsigned)blocks, stream) == 0
                    ? GACT_OK : GACT_E_HIP;
     }
 
@@ -224,7 +239,7 @@ int run_multi(bool compress, const gact_tensor_desc* descs, int L, int group_siz
     std::memcpy(image.data() + tb + fb, hint.data(), hint.size() * sizeof(uint32_t));
     if (const int rc = upload(d_workspace, image.data(), image.size(), stream)) return rc;
     const unsigned char* base = (const unsigned char*)d_workspace;
-    return gact_launch_multi(compress ? 1 : 0, (const gact::TensorArgs*)base, (const uint32_t*)(base + tb),
+    return gact_launch_multi(work, (const gact::TensorArgs*)base, (const uint32_t*)(base + tb),
                              (const uint32_t*)(base + tb + fb), shift, &geo, (unsigned)blocks,
                              stream) == 0 ? GACT_OK : GACT_E_HIP;
 }
@@ -357,7 +372,7 @@ int compress_footprint(const void* d_x, gact_dtype dtype, int64_t n, int group_s
     const size_t need = (size_t)tiles_for(n, geo) * sizeof(double);
     if (!d_workspace || !aligned(d_workspace, 16) || workspace_bytes < need)
         return limited ? GACT_E_SCRATCH : GACT_E_ARG;
-    const int64_t blocks = blocks_for(true, t, geo);
+    const int64_t blocks = blocks_for(gact::kCompressAny, t, geo);
     if (blocks > 0x7FFFFFFFll) return GACT_E_ARG;
     // The launch adds its sums itself where the workspace has two words for each (all of the documented size
     // have from two tiles on) and the tag is this call's alone: not in a graph, whose replays share one, nor in

@@ -74,6 +74,26 @@ __device__ __forceinline__ uint32_t ordered_block(uint32_t b, uint32_t run_end, 
 }
 #endif
 
+// What a launch does.  A compressing launch is one of three kernels:
+//   kCompressBf16  every tensor is bf16: 4 KB of LDS per wavefront, so eight wavefronts per
+//                  SIMD are resident if they keep to 64 VGPRs;
+//   kCompressAny   fp32 among them: 8 KB of LDS per wavefront, four per SIMD, 128 VGPRs each;
+//   kCompressLong  the same in launches of kLongCompress such blocks and more, in blocks of one wavefront:
+//                  of these more are resident (a block of four needs 32 KB of the 160 at once) and each
+//                  leaves by itself.  Us, blocks of four | of one: 53 fp32 tensors of 0.7 G elements 479 | 469,
+//                  4 bits 520 | 507, groups of 1024 490 | 480, one of 0.42 G, 4 bits 307 | 294; 40 of both types,
+//                  0.9 G 504 | 505.  Shorter launches gain nothing for sure, or lose (89 M elements 59.4 | 59.7,
+//                  87 M 69.3 | 69.0, 67 M 45.8 | 46.5, 7 M 6.3 | 6.6), and bf16 gains 1 % on some sets
+//                  and loses 2 % on others (400 tensors of 2 G elements 829 | 843).
+// A decompressing launch of fewer than kShortLaunch blocks is a kernel of its own, for
+// its units per wavefront and because such a launch has no block order.  (As a branch
+// in one kernel it gave back half of what the other units gain: one bf16 tensor of
+// 7.5 M elements, 2 bits, 4.4 us; with three units 4.9, this kernel 4.1.)
+enum Work { kDecompress, kCompressBf16, kCompressAny, kDecompressShort, kCompressLong };
+constexpr bool decompresses(Work w) { return w == kDecompress || w == kDecompressShort; }
+constexpr int waves_per_block(Work w) { return w == kCompressLong ? 1 : 4; }
+constexpr uint64_t kLongCompress = 32768;
+
 // LDS one compressing wavefront stages its tile in: 64 rows of 32 elements in
 // the input's own format.
 constexpr int lds_dwords_per_wave(int dtype) { return dtype == GACT_DT_F32 ? 64 * 32 : 64 * 16; }
@@ -214,21 +234,25 @@ constexpr int dec_block_elems(int dtype, int bits, uint32_t bf16_units) {
 // above one loses (0.7 %).  Launches of few windows keep plain order: the XCDs that get the runs of a last,
 // partial window finish late.
 constexpr uint32_t kDecompressRunShift = 5;
-inline int run_shift_for(bool compress, uint64_t blocks) {
+// Blocks of one wavefront (kCompressLong), 53 fp32 tensors of 0.7 G elements, s = 4 .. 8: 479, 479, 472, 472, 475 us;
+// at 4 bits 523, 526, 508, 513, 520.
+constexpr uint32_t kCompressLongRunShift = 6;
+inline int run_shift_for(Work w, uint64_t blocks) {
     int log2 = 0;
     while ((blocks >> log2) > 1) ++log2;
-    if (compress) return log2 < 13 ? 0 : (log2 - 9 < 8 ? log2 - 9 : 8);
+    if (w == kCompressLong) return (int)kCompressLongRunShift;
+    if (!decompresses(w)) return log2 < 13 ? 0 : (log2 - 9 < 8 ? log2 - 9 : 8);
     return log2 < 14 ? 0 : (int)kDecompressRunShift;
 }
 
-inline Runs runs_for(bool compress, uint64_t blocks) {
-    const int s = run_shift_for(compress, blocks);
+inline Runs runs_for(Work w, uint64_t blocks) {
+    const int s = run_shift_for(w, blocks);
     return Runs{s ? runs_end((uint32_t)blocks, (uint32_t)s) : 0u, (uint32_t)s};
 }
 
 }  // namespace gact
 
-extern "C" int gact_launch_single(int compress, const gact::TensorArgs* t,
+extern "C" int gact_launch_single(gact::Work work, const gact::TensorArgs* t,
                                   const gact::Geometry* geo, unsigned blocks, void* stream);
 // `inline_table` is used when it is not null, else the table in device memory
 extern "C" int gact_launch_diff_sq(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
@@ -246,9 +270,9 @@ extern "C" int gact_launch_grad_stats(const gact::ReduceTable* inline_table, con
                                       const uint32_t* d_first, int K, float rt, int bf16_chunks, int wide, unsigned blocks,
                                       double* d_partial, uint64_t tag, double* d_out, void* stream);
 extern "C" int gact_launch_copy(void* dst, const void* src, uint64_t nbytes, unsigned workgroups, void* stream);
-extern "C" int gact_launch_multi_inline(int compress, const gact::InlineTable* tab, unsigned hint_shift,
+extern "C" int gact_launch_multi_inline(gact::Work work, const gact::InlineTable* tab, unsigned hint_shift,
                                         const gact::Geometry* geo, unsigned blocks, void* stream);
-extern "C" int gact_launch_multi(int compress, const gact::TensorArgs* d_table,
+extern "C" int gact_launch_multi(gact::Work work, const gact::TensorArgs* d_table,
                                  const uint32_t* d_first_block, const uint32_t* d_hint,
                                  unsigned hint_shift, const gact::Geometry* geo, unsigned blocks,
                                  void* stream);

@@ -815,7 +815,7 @@ __device__ __forceinline__ uint32_t work_block(uint32_t run_end, uint32_t s) {
     return ordered_block(blockIdx.x, run_end, s);
 }
 
-template <bool WITH_F32, bool SUM>
+template <bool WITH_F32, bool SUM, int WAVES>
 __device__ __forceinline__ void compress_block(const TensorArgs& t, const Geometry& geo,
                                                int64_t block_in_tensor, double& tile_sum) {
     // sized by the launcher: geo.lds_wave_dwords per wavefront
@@ -823,7 +823,7 @@ __device__ __forceinline__ void compress_block(const TensorArgs& t, const Geomet
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     uint32_t* lds = lds_all + wave * geo.lds_wave_dwords;
-    const int64_t tile = block_in_tensor * kWavesPerBlk + __builtin_amdgcn_readfirstlane(wave);
+    const int64_t tile = block_in_tensor * WAVES + __builtin_amdgcn_readfirstlane(wave);
     if (tile * (int64_t)(geo.lanes_used * kPerLane) >= t.n) return;
     // A tile is "full" when all its elements exist.  With other group sizes the last tile is never
     // treated as one: it also zeroes the pad words that lie past its lanes.
@@ -863,23 +863,14 @@ __device__ __forceinline__ void decompress_block(const TensorArgs& t, const Geom
 #undef GACT_D_EDGE
 }
 
-// What a launch does.  A compressing launch is one of two kernels:
-//   kBf16  every tensor is bf16: 4 KB of LDS per wavefront, so eight wavefronts per
-//          SIMD are resident if they keep to 64 VGPRs;
-//   kAny   fp32 among them: 8 KB of LDS per wavefront, four per SIMD, 128 VGPRs each.
-// A decompressing launch of fewer than kShortLaunch blocks is a kernel of its own, for
-// its units per wavefront and because such a launch has no block order.  (As a branch
-// in one kernel it gave back half of what the other units gain: one bf16 tensor of
-// 7.5 M elements, 2 bits, 4.4 us; with three units 4.9, this kernel 4.1.)
-enum Work { kDecompress, kCompressBf16, kCompressAny, kDecompressShort };
-constexpr int waves_per_simd(Work w) { return w == kCompressAny ? 4 : 8; }
-constexpr bool decompresses(Work w) { return w == kDecompress || w == kDecompressShort; }
+// The kernel of each kind of launch (Work in gact_device.h).
+constexpr int waves_per_simd(Work w) { return w == kCompressAny || w == kCompressLong ? 4 : 8; }
 constexpr uint32_t bf16_units(Work w) { return w == kDecompressShort ? kDecUnitsBf16Short : kDecUnitsBf16; }
 
 template <Work W>
 __device__ __forceinline__ uint32_t work_block_of(uint32_t run_end, uint32_t run_shift) {
     if constexpr (W == kDecompressShort) return blockIdx.x;
-    else return work_block(run_end, W == kDecompress ? kDecompressRunShift : run_shift);
+    else return work_block(run_end, W == kDecompress ? kDecompressRunShift : W == kCompressLong ? kCompressLongRunShift : run_shift);
 }
 
 template <Work W>
@@ -890,12 +881,12 @@ __device__ __forceinline__ void run_block(const TensorArgs& t, const Geometry& g
         decompress_block<bf16_units(W)>(t, geo, block_in_tensor, end <= t.n);
     } else {
         double unused;
-        compress_block<W == kCompressAny, false>(t, geo, block_in_tensor, unused);
+        compress_block<W != kCompressBf16, false, waves_per_block(W)>(t, geo, block_in_tensor, unused);
     }
 }
 
 #define GACT_KERNEL(W) \
-    __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(waves_per_simd(W), waves_per_simd(W)))) void
+    __global__ __launch_bounds__(kLanes * waves_per_block(W)) __attribute__((amdgpu_waves_per_eu(waves_per_simd(W), waves_per_simd(W)))) void
 
 // The second argument is the shift of a run where the tensor is compressed.  Where it is decompressed, it is
 // the number of blocks in front of the one that the tensor's end cuts, so that a block of a short launch waits
@@ -926,7 +917,7 @@ __global__ __launch_bounds__(kBlockThreads) void compress_sum_kernel(uint32_t ru
     }
     const uint32_t b = work_block(run_end, run_shift);
     double sum = 0.0;                                 // stays so for a wavefront past the end
-    compress_block<true, true>(t, geo, (int64_t)b, sum);
+    compress_block<true, true, kWavesPerBlk>(t, geo, (int64_t)b, sum);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
     __syncthreads();
     if (threadIdx.x == 0) put_result(block_sum, b, (part[0] + part[1]) + (part[2] + part[3]), fin.tag);
@@ -974,41 +965,34 @@ GACT_KERNEL(W) multi_inline_kernel(
 }  // namespace gact
 
 // ------------------------------------------------------------ host launchers
-namespace {
-gact::Work work_of(int compress, const gact::Geometry* geo, unsigned blocks) {
-    if (!compress) return blocks < gact::kShortLaunch ? gact::kDecompressShort : gact::kDecompress;
-    return geo->lds_wave_dwords == gact::lds_dwords_per_wave(GACT_DT_BF16) ? gact::kCompressBf16 : gact::kCompressAny;
-}
-}  // namespace
-
 // KERNEL<work>, launched on `blocks` blocks with the LDS its work needs
 #define GACT_LAUNCH(KERNEL, ...)                                                                            \
     do {                                                                                                    \
-        const gact::Runs runs = gact::runs_for(compress != 0, blocks);                                      \
-        const dim3 grid(blocks), block(gact::kBlockThreads);                                                \
-        const unsigned lds = compress ? 4u * gact::kWavesPerBlk * (unsigned)geo->lds_wave_dwords : 0u;      \
+        const gact::Runs runs = gact::runs_for(work, blocks);                                               \
+        const dim3 grid(blocks), block(gact::kLanes * gact::waves_per_block(work));                         \
+        const unsigned lds = decompresses(work) ? 0u : 4u * gact::waves_per_block(work) * (unsigned)geo->lds_wave_dwords; \
         hipStream_t s = (hipStream_t)stream;                                                                \
-        switch (work_of(compress, geo, blocks)) {                                                           \
+        switch (work) {                                                                                     \
             case gact::kDecompress:   hipLaunchKernelGGL(KERNEL<gact::kDecompress>, grid, block, lds, s, __VA_ARGS__); break;   \
             case gact::kDecompressShort: hipLaunchKernelGGL(KERNEL<gact::kDecompressShort>, grid, block, lds, s, __VA_ARGS__); break; \
             case gact::kCompressBf16: hipLaunchKernelGGL(KERNEL<gact::kCompressBf16>, grid, block, lds, s, __VA_ARGS__); break; \
             case gact::kCompressAny:  hipLaunchKernelGGL(KERNEL<gact::kCompressAny>, grid, block, lds, s, __VA_ARGS__); break;  \
+            case gact::kCompressLong: hipLaunchKernelGGL(KERNEL<gact::kCompressLong>, grid, block, lds, s, __VA_ARGS__); break; \
         }                                                                                                   \
         return hipGetLastError() == hipSuccess ? 0 : -1;                                                    \
     } while (0)
 
-extern "C" int gact_launch_single(int compress, const gact::TensorArgs* t, const gact::Geometry* geo,
+extern "C" int gact_launch_single(gact::Work work, const gact::TensorArgs* t, const gact::Geometry* geo,
                                   unsigned blocks, void* stream) {
-    const uint32_t units = gact::bf16_units(work_of(compress, geo, blocks));
-    const uint32_t full_blocks = compress ? 0u : (uint32_t)(t->n / gact::dec_block_elems(t->dtype(), t->bits(), units));
-    GACT_LAUNCH(gact::single_kernel, runs.end, compress ? runs.shift : full_blocks, *t, *geo);
+    const uint32_t full_blocks = decompresses(work) ? (uint32_t)(t->n / gact::dec_block_elems(t->dtype(), t->bits(), gact::bf16_units(work))) : 0u;
+    GACT_LAUNCH(gact::single_kernel, runs.end, decompresses(work) ? full_blocks : runs.shift, *t, *geo);
 }
 
 extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::Geometry* geo, unsigned blocks,
                                         double* d_block_sum, int tagged, uint64_t tag, int n_samples, double* d_out,
                                         void* stream) {
     const unsigned lds = 4u * gact::kWavesPerBlk * (unsigned)geo->lds_wave_dwords;
-    const gact::Runs runs = gact::runs_for(true, blocks);
+    const gact::Runs runs = gact::runs_for(gact::kCompressAny, blocks);
     const gact::Finish fin{tagged ? tag : 0, 1.0, d_out, blocks};
     const dim3 grid(blocks + (tagged ? gact::adders_for<gact::kWavesPerBlk>(blocks) : 0));
     hipLaunchKernelGGL(gact::compress_sum_kernel, grid, dim3(gact::kBlockThreads), lds,
@@ -1016,13 +1000,13 @@ extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::G
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-extern "C" int gact_launch_multi_inline(int compress, const gact::InlineTable* tab, unsigned hint_shift,
+extern "C" int gact_launch_multi_inline(gact::Work work, const gact::InlineTable* tab, unsigned hint_shift,
                                         const gact::Geometry* geo, unsigned blocks, void* stream) {
     const gact::LineGeometry line{*geo, {}};
     GACT_LAUNCH(gact::multi_inline_kernel, runs.end, runs.shift, hint_shift, line, *tab);
 }
 
-extern "C" int gact_launch_multi(int compress, const gact::TensorArgs* d_table,
+extern "C" int gact_launch_multi(gact::Work work, const gact::TensorArgs* d_table,
                                  const uint32_t* d_first_block, const uint32_t* d_hint,
                                  unsigned hint_shift, const gact::Geometry* geo, unsigned blocks,
                                  void* stream) {

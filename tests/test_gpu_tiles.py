@@ -250,3 +250,38 @@ def test_long_decompressing_launches_against_short_ones(gact, dtype, bits, G):
         alone = gact.gact_decompress(*q, G, bits, dtype=dt).view(torch.uint8)
         assert torch.equal(alone, y[a:a + q[3]].view(torch.uint8)), a
         assert torch.equal(alone, part.view(torch.uint8)), a
+
+
+@pytest.mark.parametrize("blocks", (32767, 32768, 32769 + 130))
+@pytest.mark.parametrize("G,bits,mixed", [(256, 2, False), (96, 4, False), (1024, 1, True), (32, 8, True)])
+def test_long_compressing_launches_in_blocks_of_one_wavefront(gact, G, bits, mixed, blocks):
+    """The longest launch with fp32 in blocks of four wavefronts and the shortest in blocks of one, the last tile
+    cut: one tensor, and a list of four of which two may be bf16, against calls for pieces of the same noise."""
+    tile = 64 // (G // 32) * G
+    n = blocks * 4 * tile - tile // 2 - 5
+    x = torch.randn(n, device="cuda", generator=torch.Generator("cuda").manual_seed(blocks))
+    p, mn, sc = gact.gact_compress(x, G, bits, 3)
+    per = 4001 * 128 * G                               # codes of a piece begin on 16 bytes
+    step = -(-n // per // 4) * per
+    cuts = list(range(0, n, step)) + [n]
+    tensors = [x[a:b] for a, b in zip(cuts, cuts[1:])]
+    L = len(tensors)
+    if mixed:
+        tensors = [t.to(torch.bfloat16) if k % 2 else t for k, t in enumerate(tensors)]
+    bufs = [gact.alloc_compressed(t.numel(), G, bits, x.device) for t in tensors]
+    descs = gact.make_descs(tensors, [b[0] for b in bufs], [b[1] for b in bufs], [b[2] for b in bufs], [None] * L,
+                            [t.numel() for t in tensors], [bits] * L, [3] * L, [t.dtype for t in tensors], cuts[:-1])
+    ws = torch.empty(gact.gact_multi_workspace_bytes(L), dtype=torch.uint8, device="cuda")
+    gact.gact_compress_multi(descs, L, G, ws)
+    for k, (t, a) in enumerate(zip(tensors, cuts)):
+        m = t.numel()
+        alone = gact.alloc_compressed(m, G, bits, x.device)
+        for at in range(0, m, per):                    # short launches
+            part = t[at:at + per]
+            d = gact.make_descs([part], [alone[0][at * bits // 8:]], [alone[1][at // G:]], [alone[2][at // G:]], [None],
+                                [part.numel()], [bits], [3], [t.dtype], [a + at])
+            gact.gact_compress_multi(d, 1, G, ws)
+        assert all(torch.equal(u, v) for u, v in zip(alone, bufs[k])), (k, "list")
+        if t.dtype == torch.float32:
+            whole = (p[a * bits // 8:][:alone[0].numel()], mn[a // G:][:alone[1].numel()], sc[a // G:][:alone[2].numel()])
+            assert all(torch.equal(u, v) for u, v in zip(alone, whole)), (k, "one tensor")
