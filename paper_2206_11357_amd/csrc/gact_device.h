@@ -45,17 +45,30 @@ struct Geometry {
     int32_t pow2;          // lpg is a power of two (DPP reductions, full tiles)
     int32_t groups_per_tile;
     int32_t group_size;
-    int32_t group_shift;   // log2(group_size) when pow2
+    int32_t group_shift;   // element e belongs to group (e >> 4) * group_magic >> 32 >> group_shift
+    uint32_t group_magic;  // (group_divisor)
     int32_t lpg_magic;     // floor(65536 / lpg) + 1: lane / lpg = lane * lpg_magic >> 16 for lane < 64
     int32_t lds_wave_dwords;   // compress: LDS dwords per wavefront (lds_dwords_per_wave of the widest dtype launched)
 };
 // The single-tensor kernels' arguments stay below 112 bytes: from 120 on, the runtime takes the host 0.6 us
 // longer per launch (3.1 -> 3.7 us), which is what bounds small calls.
 static_assert(sizeof(TensorArgs) + sizeof(Geometry) + 16 <= 112, "arguments of the single-tensor kernels");
+// Division of e >> 4 by group_size / 16 = d, for e < 2^35, as a product (Granlund, Montgomery 1994, Thm. 4.2):
+// with 2^(s+1) >= d, m = floor(2^(32+s) / d) + 1 exceeds 2^(32+s) / d by at most 1, so that
+// the product is at most e >> 4 < 2^31 <= 2^(32+s) / d, less than one d-th of 2^(32+s), too large.
+// d is at least 2, so that m fits 32 bits; where d is a power of two, m = 2^31 without the 1 is exact.
+constexpr int64_t kMagicElems = (int64_t)1 << 35;
+inline void group_divisor(Geometry* geo) {
+    const uint32_t d = (uint32_t)geo->group_size / 16;
+    int32_t s = 0;
+    while ((2u << s) < d) ++s;
+    geo->group_shift = s;
+    geo->group_magic = (uint32_t)(((uint64_t)1 << (32 + s)) / d + ((d & (d - 1)) != 0 ? 1 : 0));
+}
 // the geometry in front of a launch table that starts on a 64-byte line, behind three dwords
 struct LineGeometry {
     Geometry geo;
-    int32_t  pad[5];
+    int32_t  pad[4];
 };
 static_assert(12 + sizeof(LineGeometry) == 64, "the launch table starts on a line");
 
@@ -210,6 +223,37 @@ constexpr int dec_units(uint32_t table, int bits) { return (int)(table >> (3 * b
 // elements of a block; bf16_units: the table of bf16 tensors
 constexpr int dec_block_elems(int dtype, int bits, uint32_t bf16_units) {
     return dtype == GACT_DT_F32 ? 4 * 256 * dec_units(kDecUnitsF32, bits) : 4 * 512 * dec_units(bf16_units, bits);
+}
+
+// In what order a decompressing wavefront issues the loads of its units, and how fast.  Back to back they
+// are slower than with pauses in between (s_sleep, of 64 cycles): what a wavefront asks for at once arrives
+// at once and is stored at once, and HBM takes reads and stores that come in such waves worse than a steady
+// mix.  Which order is best depends on the sizes of the loads and was chosen by sweep (us, decompress):
+//                                  bf16, 1.0 G in 400 tensors    bf16, 1.4 G in 96        fp32, 0.7 G in 53
+//   bits                             1      2      4               1      2      4          1      2      4      8
+//   codes, division, group by unit  405    404    414             540    533    555        471    491    532    553
+//   the same without the division   400    405    430             536    528    574        487    542    525    550
+//   groups, pause, codes by unit    384    384    410             515    542    554        623    496    531    565
+//   groups, pause, codes, paused    375    389    415             502    557    563        471    502    514    554
+//   codes, pause, groups            444    --     431             544    543    574        467    490    536    551
+//   as below                        374    384    409             502    533    552        466    494    504    556
+// Launches of mixed widths, division and as below: 400 bf16 tensors, about 3 bits, 829, 813 (0.26 G 109.3, 105.6);
+// groups of 224 422, 400; 53 fp32 tensors 493, 490; 3 fp32 ones of 87 M 72.4, 69.2, groups of 96 74.7, 69.6; 40 of
+// both types, 0.3 G 182, 168.  Short launches of bf16 (us, buffers that are not in the caches): 16 M, 2 bits 8.62,
+// 7.07; 8 M, 1 bit 5.06, 4.48; 12 M, 4 bits 6.79, 6.90; 20 M, 8 bits 12.50, 11.79.
+struct LoadOrder {
+    bool by_unit;          // a unit's codes and its minima and steps together, else those of all units in turn
+    bool groups_first;     // minima and steps before codes
+    int  kinds, units;     // s_sleep between codes and minima, and between units
+};
+constexpr LoadOrder load_order(int dtype, int bits, bool short_launch) {
+    if (dtype == GACT_DT_F32)
+        return bits == 1 ? LoadOrder{false, false, 2, 1} : bits == 2 ? LoadOrder{false, false, 4, 0}
+             : bits == 4 ? LoadOrder{false, true, 1, 0} : LoadOrder{false, true, 1, 1};
+    if (short_launch)
+        return bits <= 2 ? LoadOrder{false, false, 1, 0} : bits == 4 ? LoadOrder{false, false, 0, 0}
+                                                                     : LoadOrder{true, false, 0, 1};
+    return bits == 1 ? LoadOrder{false, true, 1, 1} : LoadOrder{true, true, 1, 0};
 }
 
 // Length of the runs of neighbouring blocks that go to one XCD, as a power of two

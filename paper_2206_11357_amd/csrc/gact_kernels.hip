@@ -721,26 +721,61 @@ __device__ __forceinline__ void load_piece(const TensorArgs& t, int64_t e, Piece
     }
 }
 
-template <int DT, int BITS, bool EDGE, int UNITS>
+// Keeps the wavefront from issuing for about 64 N cycles, and the compiler from moving loads across.
+template <int N>
+__device__ __forceinline__ void pause() {
+    if constexpr (N > 0) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_sleep(N);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+template <int DT, int BITS, bool EDGE, int UNITS, bool SHORT>
 __device__ __forceinline__ void decompress_units(const TensorArgs& t, const Geometry& geo,
-                                                 int64_t block_in_tensor, int wave, int lane) {
+                                                 int64_t block_in_tensor, int64_t first_group, int wave, int lane) {
     constexpr uint32_t B = (1u << BITS) - 1u;
     constexpr int P = DecGeom<DT>::kPiece;
     constexpr int U = DecGeom<DT>::kUnit;
     PieceBits<DT, BITS> pb[UNITS];
     float mn[UNITS], step[UNITS];
     int64_t e[UNITS];
+    const int64_t first_e = first_group * geo.group_size;
 #pragma unroll
     for (int k = 0; k < UNITS; ++k) {
         const int64_t unit = block_in_tensor * (kWavesPerBlk * UNITS) + k * kWavesPerBlk + wave;
         e[k] = unit * U + lane * P;
         mn[k] = 0.0f; step[k] = 0.0f; pb[k].lo = 0u; pb[k].hi = 0u;
-        if (!EDGE || e[k] < t.n) {
-            load_piece<DT, BITS, EDGE>(t, e[k], pb[k]);
-            const int64_t g = geo.pow2 ? (e[k] >> geo.group_shift)
-                                       : (int64_t)((uint64_t)e[k] / (uint32_t)geo.group_size);
-            mn[k] = t.gmin[g];
-            step[k] = t.gscale[g];
+    }
+    const auto load_codes = [&](int k) {
+        if (!EDGE || e[k] < t.n) load_piece<DT, BITS, EDGE>(t, e[k], pb[k]);
+    };
+    const auto load_group = [&](int k) {
+        if (EDGE && e[k] >= t.n) return;
+        const int64_t g = first_group + (int64_t)(__umulhi((uint32_t)((e[k] - first_e) >> 4), geo.group_magic) >> geo.group_shift);
+        mn[k] = t.gmin[g];
+        step[k] = t.gscale[g];
+    };
+    constexpr LoadOrder kOrder = load_order(DT, BITS, SHORT);
+    if constexpr (kOrder.by_unit) {
+#pragma unroll
+        for (int k = 0; k < UNITS; ++k) {
+            if (k) pause<kOrder.units>();
+            if (kOrder.groups_first) load_group(k); else load_codes(k);
+            pause<kOrder.kinds>();
+            if (kOrder.groups_first) load_codes(k); else load_group(k);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < UNITS; ++k) {
+            if (k) pause<kOrder.units>();
+            if (kOrder.groups_first) load_group(k); else load_codes(k);
+        }
+        pause<kOrder.kinds>();
+#pragma unroll
+        for (int k = 0; k < UNITS; ++k) {
+            if (k) pause<kOrder.units>();
+            if (kOrder.groups_first) load_codes(k); else load_group(k);
         }
     }
 #pragma unroll
@@ -852,11 +887,17 @@ __device__ __forceinline__ void decompress_block(const TensorArgs& t, const Geom
                                                  int64_t block_in_tensor, bool full) {
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
+    // A piece's group comes out of a product (group_divisor), in a tensor that is too long for it counted from
+    // the block's first group.  (A division in 64 bits was 110 instructions a unit, with a branch around them for
+    // group sizes that are a power of two; in their place the loads are paced as load_order says.)
+    int64_t first_group = 0;
+    if (t.n > kMagicElems)
+        first_group = (int64_t)((uint64_t)block_in_tensor * (uint32_t)dec_block_elems(t.dtype(), t.bits(), BF16_UNITS) / (uint32_t)geo.group_size);
 #define GACT_D_FULL(DT, BITS) \
-    decompress_units<DT, BITS, false, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS)>(t, geo, block_in_tensor, wave, lane); \
+    decompress_units<DT, BITS, false, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS), BF16_UNITS == kDecUnitsBf16Short>(t, geo, block_in_tensor, first_group, wave, lane); \
     __builtin_amdgcn_endpgm();
 #define GACT_D_EDGE(DT, BITS) \
-    decompress_units<DT, BITS, true, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS)>(t, geo, block_in_tensor, wave, lane); \
+    decompress_units<DT, BITS, true, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS), BF16_UNITS == kDecUnitsBf16Short>(t, geo, block_in_tensor, first_group, wave, lane); \
     __builtin_amdgcn_endpgm();
     if (full) { GACT_DISPATCH(t, true, GACT_D_FULL) } else { GACT_DISPATCH(t, true, GACT_D_EDGE) }
 #undef GACT_D_FULL

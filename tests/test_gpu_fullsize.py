@@ -193,3 +193,23 @@ def test_single_tensor_beyond_32_bit_element_indices(gact):
         assert np.array_equal(host(gmin[g0:g0 + 16]), mn_ref)
         y_ref = oracle.decompress(p_ref, mn_ref, sc_ref, e1 - e0, G, bits, oracle.BF16)
         assert np.array_equal(host(y[e0:e1]), y_ref)
+
+
+@pytest.mark.parametrize("G", (992, 32))
+def test_groups_of_a_tensor_that_is_too_long_for_the_product(gact, G):
+    """Beyond 2^35 elements a piece's group is counted from its block's first group.  One bit, all codes zero, so that
+    the output is the group's minimum; looked at on both sides of 2^35 and at both ends."""
+    n = (1 << 35) + 123_457
+    if torch.cuda.mem_get_info()[0] < 90 << 30:
+        pytest.skip("needs 80 GB of device memory")
+    packed = torch.zeros(gact.gact_packed_bytes(n, 1), dtype=torch.uint8, device="cuda")
+    groups = gact.gact_num_groups(n, G)
+    gmin = (torch.arange(groups, device="cuda", dtype=torch.int32) % 251).float()
+    gscale = torch.ones(groups, device="cuda")
+    y = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    gact.gact_decompress(packed, gmin, gscale, n, G, 1, y=y)
+    for at in (0, (1 << 34) - 70_000, (1 << 35) - 70_000, n - 140_000):
+        i = torch.arange(at, min(at + 140_000, n), device="cuda")
+        assert torch.equal(y[at:at + 140_000].float(), ((i // G) % 251).float()), at
+    del packed, gmin, gscale, y
+    torch.cuda.empty_cache()
