@@ -37,7 +37,6 @@ gact::Geometry make_geometry(int group_size) {
     geo.lanes_used = (64 / geo.lpg) * geo.lpg;
     geo.pow2 = (geo.lpg & (geo.lpg - 1)) == 0 ? 1 : 0;
     geo.groups_per_tile = geo.lanes_used / geo.lpg;
-    geo.group_size = group_size;
     gact::group_divisor(&geo);
     geo.lpg_magic = 65536 / geo.lpg + 1;
     geo.lds_wave_dwords = 0;      // set per launch from the dtypes in it

@@ -44,7 +44,6 @@ struct Geometry {
     int32_t lanes_used;    // (64 / lpg) * lpg
     int32_t pow2;          // lpg is a power of two (DPP reductions, full tiles)
     int32_t groups_per_tile;
-    int32_t group_size;
     int32_t group_shift;   // element e belongs to group (e >> 4) * group_magic >> 32 >> group_shift
     uint32_t group_magic;  // (group_divisor)
     int32_t lpg_magic;     // floor(65536 / lpg) + 1: lane / lpg = lane * lpg_magic >> 16 for lane < 64
@@ -53,13 +52,13 @@ struct Geometry {
 // The single-tensor kernels' arguments stay below 112 bytes: from 120 on, the runtime takes the host 0.6 us
 // longer per launch (3.1 -> 3.7 us), which is what bounds small calls.
 static_assert(sizeof(TensorArgs) + sizeof(Geometry) + 16 <= 112, "arguments of the single-tensor kernels");
-// Division of e >> 4 by group_size / 16 = d, for e < 2^35, as a product (Granlund, Montgomery 1994, Thm. 4.2):
+// Division of e >> 4 by d = 2 lpg, for e < 2^35, as a product (Granlund, Montgomery 1994, Thm. 4.2):
 // with 2^(s+1) >= d, m = floor(2^(32+s) / d) + 1 exceeds 2^(32+s) / d by at most 1, so that
 // the product is at most e >> 4 < 2^31 <= 2^(32+s) / d, less than one d-th of 2^(32+s), too large.
 // d is at least 2, so that m fits 32 bits; where d is a power of two, m = 2^31 without the 1 is exact.
 constexpr int64_t kMagicElems = (int64_t)1 << 35;
 inline void group_divisor(Geometry* geo) {
-    const uint32_t d = (uint32_t)geo->group_size / 16;
+    const uint32_t d = 2u * (uint32_t)geo->lpg;
     int32_t s = 0;
     while ((2u << s) < d) ++s;
     geo->group_shift = s;
@@ -68,7 +67,7 @@ inline void group_divisor(Geometry* geo) {
 // the geometry in front of a launch table that starts on a 64-byte line, behind three dwords
 struct LineGeometry {
     Geometry geo;
-    int32_t  pad[4];
+    int32_t  pad[5];
 };
 static_assert(12 + sizeof(LineGeometry) == 64, "the launch table starts on a line");
 

@@ -740,7 +740,7 @@ __device__ __forceinline__ void decompress_units(const TensorArgs& t, const Geom
     PieceBits<DT, BITS> pb[UNITS];
     float mn[UNITS], step[UNITS];
     int64_t e[UNITS];
-    const int64_t first_e = first_group * geo.group_size;
+    const int64_t first_e = first_group * (geo.lpg * kPerLane);
 #pragma unroll
     for (int k = 0; k < UNITS; ++k) {
         const int64_t unit = block_in_tensor * (kWavesPerBlk * UNITS) + k * kWavesPerBlk + wave;
@@ -892,7 +892,7 @@ __device__ __forceinline__ void decompress_block(const TensorArgs& t, const Geom
     // group sizes that are a power of two; in their place the loads are paced as load_order says.)
     int64_t first_group = 0;
     if (t.n > kMagicElems)
-        first_group = (int64_t)((uint64_t)block_in_tensor * (uint32_t)dec_block_elems(t.dtype(), t.bits(), BF16_UNITS) / (uint32_t)geo.group_size);
+        first_group = (int64_t)((uint64_t)block_in_tensor * (uint32_t)dec_block_elems(t.dtype(), t.bits(), BF16_UNITS) / (uint32_t)(geo.lpg * kPerLane));
 #define GACT_D_FULL(DT, BITS) \
     decompress_units<DT, BITS, false, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS), BF16_UNITS == kDecUnitsBf16Short>(t, geo, block_in_tensor, first_group, wave, lane); \
     __builtin_amdgcn_endpgm();

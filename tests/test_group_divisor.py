@@ -13,7 +13,7 @@ PROGRAM = r"""
 int main() {
     for (int G = 32; G <= 1024; G += 32) {
         gact::Geometry geo{};
-        geo.group_size = G;
+        geo.lpg = G / 32;
         gact::group_divisor(&geo);
         const uint64_t d = (uint64_t)G / 16, end = (uint64_t)gact::kMagicElems / 16;
         const auto bad = [&](uint64_t i) {
