@@ -273,7 +273,9 @@ def main() -> int:
     kernel = "gact::multi_inline_kernel<%s>" if L <= 64 else "gact::multi_kernel<%s>"
     valu = COMPRESS_VALU_PER_ELEMENT[S.specs[0].dtype] * S.n_total / c_avg * 1e3
 
-    roof = {"bound": "hbm", "kernel": kernel % ("kCompressBf16" if all(sp.dtype == "bf16" for sp in S.specs) else "kCompressAny"), "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
+    long_launch = sum(-(-sp.n // 8192) for sp in S.specs) >= 32768       # blocks of four tiles
+    work = "kCompressBf16" if all(sp.dtype == "bf16" for sp in S.specs) else "kCompressLong" if long_launch else "kCompressAny"
+    roof = {"bound": "hbm", "kernel": kernel % work, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
             "traffic": traffic["compress_bytes"] if traffic else None}
     roof_d = {"bound": "hbm", "kernel": kernel % "kDecompress", "achieved": round(achieved_d, 1), "peak": HBM_PEAK_GBPS,
@@ -471,7 +473,7 @@ def live_traffic(workload: str):
                     ref.append(val)
                 elif "gact::multi" in name and ("Work)0>" in name or "Work)3>" in name):      # kDecompress, kDecompressShort
                     dec.append(val)
-                elif "gact::multi" in name:                                # kCompressBf16, kCompressAny
+                elif "gact::multi" in name:                                # kCompressBf16, kCompressAny, kCompressLong
                     comp.append(val)
             if not ref or not comp or not dec:
                 return None
