@@ -236,22 +236,44 @@ constexpr int dec_block_elems(int dtype, int bits, uint32_t bf16_units) {
 //   groups, pause, codes, paused    375    389    415             502    557    563        471    502    514    554
 //   codes, pause, groups            444    --     431             544    543    574        467    490    536    551
 //   as below                        374    384    409             502    533    552        466    494    504    556
-// Launches of mixed widths, division and as below: 400 bf16 tensors, about 3 bits, 829, 813 (0.26 G 109.3, 105.6);
-// groups of 224 422, 400; 53 fp32 tensors 493, 490; 3 fp32 ones of 87 M 72.4, 69.2, groups of 96 74.7, 69.6; 40 of
-// both types, 0.3 G 182, 168.  Short launches of bf16 (us, buffers that are not in the caches): 16 M, 2 bits 8.62,
-// 7.07; 8 M, 1 bit 5.06, 4.48; 12 M, 4 bits 6.79, 6.90; 20 M, 8 bits 12.50, 11.79.
+// At 2 and 8 bits of fp32, taken again in turn, division and as below are equal (492, 493; 555, 555); what differs
+// are launches of mixed widths: 400 bf16 tensors, about 3 bits, 829, 813 (0.26 G 109.3, 105.6); groups of 224 422, 400;
+// 53 fp32 tensors 493, 490; 3 fp32 ones of 87 M 72.4, 69.2, groups of 96 74.7, 69.6; 40 of both types, 0.6 G 361, 336.
+//
+// Launches of fewer than kShortLaunch blocks are over before HBM has settled to any mix, and what waits is the
+// wavefront: they have orders of their own.  The orders of the long launches lose up to 13 % there, and a product for
+// groups that are a power of two (a shift is known three multiplies earlier) up to 4 %, so that these widths choose
+// between the two.  Us, one tensor, buffers that are not in the caches, groups of 256 (of 96), the division in the order
+// by unit | the orders of long launches, for bf16 the product | as below:
+//   M elements            4                      8                    12                     16 (fp32: 15)
+//   fp32  b=1   4.99 | 5.20 | 4.82     7.90 | 7.86 | 7.77    11.02 | 10.66 | 10.57   12.93 | 12.81 | 12.83
+//         b=2   4.31 | 4.25 | 4.26     7.89 | 7.54 | 7.62    11.28 | 10.89 | 10.91   13.67 | 13.26 | 13.27
+//         b=4   4.70 | 5.22 | 4.56     8.26 | 8.60 | 8.00    11.34 | 11.53 | 11.03   13.51 | 13.51 | 13.09
+//         b=8   4.29 | 4.50 | 4.29     8.52 | 7.39 | 7.41    11.94 | 10.22 | 10.24   14.35 | 12.38 | 12.40
+//   bf16  b=1   3.61 | 3.62 | 3.65     5.04 | 4.48 | 4.38     6.68 |  6.60 |  6.56    8.34 |  8.72 |  8.30
+//         b=2   3.65 | 3.60 | 3.68     4.33 | 4.39 | 4.39     6.67 |  5.90 |  5.92    8.64 |  7.17 |  7.19
+//         b=4   3.66 | 3.66 | 3.71     4.32 | 4.38 | 4.40     6.77 |  6.89 |  6.88    8.75 |  9.03 |  8.73
+//         b=8   3.57 | 3.54 | 3.60     6.32 | 5.01 | 4.96     8.45 |  6.50 |  6.45   10.32 |  8.42 |  8.40
+//   (96)  fp32, 8 M, b=1 8.23 | 7.86 | 7.86, b=4 9.09 | 8.61 | 8.60; bf16 b=1 5.61 | 4.56 | 4.96, b=4 5.56 | 4.47 | 4.72
+enum GroupIndex {
+    kByProduct,            // a product (group_divisor) for every group size
+    kByEither,             // a shift for group sizes that are a power of two, chosen at each piece
+    kByBranch              // the same, chosen once around all loads (both of these: codes first, no pauses between units)
+};
 struct LoadOrder {
     bool by_unit;          // a unit's codes and its minima and steps together, else those of all units in turn
     bool groups_first;     // minima and steps before codes
-    int  kinds, units;     // s_sleep between codes and minima, and between units
+    int  kinds, units;     // s_sleep between codes and minima, and between units; -1: in this order, without a pause
+    GroupIndex group = kByProduct;
 };
 constexpr LoadOrder load_order(int dtype, int bits, bool short_launch) {
+    if (short_launch && bits == 1) return LoadOrder{false, false, 1, 0, kByEither};
+    if (short_launch && bits == 4) return LoadOrder{true, false, 0, 0, kByBranch};
+    if (short_launch && dtype == GACT_DT_BF16) return bits == 2 ? LoadOrder{false, false, 1, 0} : LoadOrder{true, false, 0, 1};
+    if (short_launch) return bits == 2 ? LoadOrder{false, false, 4, 0} : LoadOrder{false, false, 1, -1};
     if (dtype == GACT_DT_F32)
         return bits == 1 ? LoadOrder{false, false, 2, 1} : bits == 2 ? LoadOrder{false, false, 4, 0}
              : bits == 4 ? LoadOrder{false, true, 1, 0} : LoadOrder{false, true, 1, 1};
-    if (short_launch)
-        return bits <= 2 ? LoadOrder{false, false, 1, 0} : bits == 4 ? LoadOrder{false, false, 0, 0}
-                                                                     : LoadOrder{true, false, 0, 1};
     return bits == 1 ? LoadOrder{false, true, 1, 1} : LoadOrder{true, true, 1, 0};
 }
 

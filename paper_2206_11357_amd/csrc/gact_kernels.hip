@@ -721,12 +721,12 @@ __device__ __forceinline__ void load_piece(const TensorArgs& t, int64_t e, Piece
     }
 }
 
-// Keeps the wavefront from issuing for about 64 N cycles, and the compiler from moving loads across.
+// Keeps the compiler from moving loads across (N != 0), and the wavefront from issuing for about 64 N cycles (N > 0).
 template <int N>
 __device__ __forceinline__ void pause() {
-    if constexpr (N > 0) {
+    if constexpr (N != 0) {
         __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_sleep(N);
+        if constexpr (N > 0) __builtin_amdgcn_s_sleep(N);
         __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -740,43 +740,74 @@ __device__ __forceinline__ void decompress_units(const TensorArgs& t, const Geom
     PieceBits<DT, BITS> pb[UNITS];
     float mn[UNITS], step[UNITS];
     int64_t e[UNITS];
+    constexpr LoadOrder kOrder = load_order(DT, BITS, SHORT);
     const int64_t first_e = first_group * (geo.lpg * kPerLane);
-#pragma unroll
-    for (int k = 0; k < UNITS; ++k) {
+    const auto begin = [&](int k) {
         const int64_t unit = block_in_tensor * (kWavesPerBlk * UNITS) + k * kWavesPerBlk + wave;
         e[k] = unit * U + lane * P;
         mn[k] = 0.0f; step[k] = 0.0f; pb[k].lo = 0u; pb[k].hi = 0u;
-    }
+    };
     const auto load_codes = [&](int k) {
         if (!EDGE || e[k] < t.n) load_piece<DT, BITS, EDGE>(t, e[k], pb[k]);
     };
-    const auto load_group = [&](int k) {
-        if (EDGE && e[k] >= t.n) return;
-        const int64_t g = first_group + (int64_t)(__umulhi((uint32_t)((e[k] - first_e) >> 4), geo.group_magic) >> geo.group_shift);
-        mn[k] = t.gmin[g];
-        step[k] = t.gscale[g];
+    const auto by_product = [&](int64_t at) {
+        return first_group + (int64_t)(__umulhi((uint32_t)((at - first_e) >> 4), geo.group_magic) >> geo.group_shift);
     };
-    constexpr LoadOrder kOrder = load_order(DT, BITS, SHORT);
-    if constexpr (kOrder.by_unit) {
+    if constexpr (kOrder.group == kByProduct) {
+        const auto load_group = [&](int k) {
+            if (EDGE && e[k] >= t.n) return;
+            const int64_t g = by_product(e[k]);
+            mn[k] = t.gmin[g];
+            step[k] = t.gscale[g];
+        };
 #pragma unroll
-        for (int k = 0; k < UNITS; ++k) {
-            if (k) pause<kOrder.units>();
-            if (kOrder.groups_first) load_group(k); else load_codes(k);
+        for (int k = 0; k < UNITS; ++k) begin(k);
+        if constexpr (kOrder.by_unit) {
+#pragma unroll
+            for (int k = 0; k < UNITS; ++k) {
+                if (k) pause<kOrder.units>();
+                if (kOrder.groups_first) load_group(k); else load_codes(k);
+                pause<kOrder.kinds>();
+                if (kOrder.groups_first) load_codes(k); else load_group(k);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < UNITS; ++k) {
+                if (k) pause<kOrder.units>();
+                if (kOrder.groups_first) load_group(k); else load_codes(k);
+            }
             pause<kOrder.kinds>();
-            if (kOrder.groups_first) load_codes(k); else load_group(k);
+#pragma unroll
+            for (int k = 0; k < UNITS; ++k) {
+                if (k) pause<kOrder.units>();
+                if (kOrder.groups_first) load_codes(k); else load_group(k);
+            }
         }
     } else {
+        // codes first; group_of: the group of an element
+        const auto load = [&](auto group_of) {
+            const auto load_group = [&](int k) {
+                if (EDGE && e[k] >= t.n) return;
+                const int64_t g = group_of(e[k]);
+                mn[k] = t.gmin[g];
+                step[k] = t.gscale[g];
+            };
 #pragma unroll
-        for (int k = 0; k < UNITS; ++k) {
-            if (k) pause<kOrder.units>();
-            if (kOrder.groups_first) load_group(k); else load_codes(k);
-        }
-        pause<kOrder.kinds>();
+            for (int k = 0; k < UNITS; ++k) {
+                begin(k);
+                load_codes(k);
+                if constexpr (kOrder.by_unit) load_group(k);
+            }
+            if constexpr (!kOrder.by_unit) {
+                pause<kOrder.kinds>();
 #pragma unroll
-        for (int k = 0; k < UNITS; ++k) {
-            if (k) pause<kOrder.units>();
-            if (kOrder.groups_first) load_codes(k); else load_group(k);
-        }
+                for (int k = 0; k < UNITS; ++k) load_group(k);
+            }
+        };
+        const auto by_shift = [&](int64_t at) { return at >> (geo.group_shift + 5); };
+        if constexpr (kOrder.group == kByEither) load([&](int64_t at) { return geo.pow2 ? by_shift(at) : by_product(at); });
+        else if (geo.pow2) load(by_shift);
+        else load(by_product);
     }
 #pragma unroll
     for (int k = 0; k < UNITS; ++k) {
