@@ -171,12 +171,16 @@ int gact_decompress_multi(const gact_tensor_desc *h_descs, int L, int group_size
  * compressor, each a list of K parameter buffers; the call computes
  *     c_l = 1/2 * sum_k ||g0_k - g1_k||^2 / S(bits),   S(b) = (2^b-1)^-2,
  * `bits` being the width tensor l was compressed with, accumulated in binary64
- * in a fixed order (the result does not depend on scheduling).
+ * in a fixed order (the result does not depend on scheduling, nor on what other
+ * streams run meanwhile).
  *   h_pairs      host array of K buffer pairs; device pointers inside, 16-byte
  *                aligned, both buffers of a pair have n elements of `dtype`.
  *   d_out        device double[1], receives c_l when the stream reaches it.
  *   d_workspace  device scratch, >= gact_reduce_workspace_bytes(K, sum of n),
  *                16-byte aligned; in use until the enqueued kernels have run.
+ *                Two calls that share a workspace must not overlap in time: their
+ *                results are then unspecified (a sum of either's parts, a NaN),
+ *                but both end.
  * K == 0 or all n == 0 writes 0.
  * HIP graphs: this call and gact_grad_stats_update return GACT_E_CAPTURE, with
  * nothing enqueued, on a stream that is being captured.  A list of more than
@@ -239,6 +243,7 @@ int gact_footprint(const void *d_x, gact_dtype dtype, int64_t n, int n_samples, 
  *                     may differ from gact_footprint's in the last bits)
  *   d_workspace       >= gact_compress_footprint_workspace_bytes(n, group_size)
  *                     bytes, 16-byte aligned, in use until the kernels have run
+ *                     (calls that share one: as for gact_sensitivity)
  * A caller that finds the footprint among tensors it already holds drops the
  * new compressed copy and keeps the old one.  n == 0 writes zeros.
  */

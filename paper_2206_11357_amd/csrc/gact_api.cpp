@@ -379,7 +379,7 @@ int compress_footprint(const void* d_x, gact_dtype dtype, int64_t n, int group_s
     const bool tagged = !limited && workspace_bytes >= 2 * (size_t)blocks * sizeof(double) && blocks < 0x70000000 &&
                         !recorded(stream);
     if (gact_launch_compress_sum(&t, &geo, (unsigned)blocks, (double*)d_workspace, tagged, tag, n_samples, d_footprint,
-                                 stream) != 0)
+                                 stream, nullptr) != 0)
         return GACT_E_HIP;
     if (tagged) return GACT_OK;
     const gact::ReduceArgs r{d_x, nullptr, n, (int32_t)dtype, 0};
@@ -457,7 +457,7 @@ int gact_sensitivity(const gact_grad_pair* h_pairs, int K, int bits, double* d_o
         return gact_launch_zero(d_out, 1, stream) == 0 ? GACT_OK : GACT_E_HIP;
     const double B = (double)((1 << bits) - 1);
     return gact_launch_diff_sq(red.table(), red.d_table, red.d_first, red.K, red.blocks, red.d_partial,
-                               red.tagged, next_tag(), 0.5 * B * B, d_out, stream) == 0 ? GACT_OK : GACT_E_HIP;
+                               red.tagged, next_tag(), 0.5 * B * B, d_out, stream, nullptr) == 0 ? GACT_OK : GACT_E_HIP;
 }
 
 int gact_grad_stats_update(const gact_grad_stat* h_stats, int K, int64_t t, double* d_out,
@@ -493,7 +493,7 @@ int gact_footprint(const void* d_x, gact_dtype dtype, int64_t n, int n_samples, 
         return GACT_E_ARG;
     const gact::ReduceArgs r{d_x, nullptr, n, (int32_t)dtype, 0};
     return gact_launch_footprint(&r, (unsigned)blocks, (double*)d_workspace, next_tag(), n_samples, d_out,
-                                 stream) == 0 ? GACT_OK : GACT_E_HIP;
+                                 stream, nullptr) == 0 ? GACT_OK : GACT_E_HIP;
 }
 
 size_t gact_compress_footprint_workspace_bytes(int64_t n, int group_size) {

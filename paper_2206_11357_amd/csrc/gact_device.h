@@ -315,6 +315,12 @@ inline Runs runs_for(Work w, uint64_t blocks) {
     return Runs{s ? runs_end((uint32_t)blocks, (uint32_t)s) : 0u, (uint32_t)s};
 }
 
+// For tests of the in-launch addition (gact_sum.h): how long its adding blocks wait, in looks, and whether they stand
+// in front of their grid, so that what they wait for comes late.  Null: as the library's own calls.
+struct Late {
+    uint32_t patience, grace, ahead;
+};
+
 }  // namespace gact
 
 extern "C" int gact_launch_single(gact::Work work, const gact::TensorArgs* t,
@@ -322,14 +328,14 @@ extern "C" int gact_launch_single(gact::Work work, const gact::TensorArgs* t,
 // `inline_table` is used when it is not null, else the table in device memory
 extern "C" int gact_launch_diff_sq(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
                                    const uint32_t* d_first, int K, unsigned blocks, double* d_partial, int tagged,
-                                   uint64_t tag, double scale, double* d_out, void* stream);
+                                   uint64_t tag, double scale, double* d_out, void* stream, const gact::Late* late);
 extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::Geometry* geo,
                                         unsigned blocks, double* d_block_sum, int tagged, uint64_t tag,
-                                        int n_samples, double* d_out, void* stream);
+                                        int n_samples, double* d_out, void* stream, const gact::Late* late);
 extern "C" int gact_launch_footprint_finish(const gact::ReduceArgs* r, unsigned count, double* d_partial, uint64_t tag,
                                             int n_samples, double* d_out, void* stream);
 extern "C" int gact_launch_footprint(const gact::ReduceArgs* r, unsigned blocks, double* d_partial, uint64_t tag,
-                                     int n_samples, double* d_out, void* stream);
+                                     int n_samples, double* d_out, void* stream, const gact::Late* late);
 extern "C" int gact_launch_zero(double* d_out, int nout, void* stream);
 extern "C" int gact_launch_grad_stats(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
                                       const uint32_t* d_first, int K, float rt, int bf16_chunks, int wide, unsigned blocks,

@@ -432,15 +432,23 @@ __device__ __forceinline__ uint32_t negate_fields(uint32_t w) {
 }
 
 // ----------------------------------------------------------------- compress
+// What a tile leaves beside its codes (SUM): the sum of its elements; and the word at `look`, if any, as it was when the
+// tile's loads were out (gact_sum.h), for the load to be in nobody's way.
+struct TileOut {
+    const uint64_t* look = nullptr;
+    double   sum = 0.0;
+    uint64_t word = 0;
+};
+
 // One wavefront compresses tile `tile` of tensor `t`.
 //   geo.lpg        lanes per group (G/32)
 //   geo.lanes_used lanes that hold data in a full tile (64 for power-of-two G)
-//   SUM            also return the binary64 sum of the tile's elements in tile_sum (the
+//   SUM            also return the binary64 sum of the tile's elements in out_sum (the
 //                  footprint of Sec. 5.2 from the same read)
 template <int DT, int BITS, TileKind KIND, bool SUM>
 __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometry& geo,
                                               int64_t tile, uint32_t* __restrict__ lds, int lane,
-                                              double& tile_sum) {
+                                              TileOut& out_sum) {
     constexpr uint32_t B = (1u << BITS) - 1u;
     const int tile_elems = geo.lanes_used * kPerLane;
     const int64_t e0 = tile * (int64_t)tile_elems;       // `tile` is uniform over the wavefront
@@ -452,6 +460,7 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
 
     RawTile<DT> raw;
     load_tile<DT, KIND>(t.io, e0, ne, lane, raw);
+    if (SUM && out_sum.look) out_sum.word = load_word(out_sum.look);
 
     uint32_t last_word = 0u;                         // the tile's last valid element
     if (KIND == kEdge) last_word = load_element<DT>(t.io, e0 + ne - 1);
@@ -494,7 +503,7 @@ __device__ __forceinline__ void compress_tile(const TensorArgs& t, const Geometr
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j)
             if (KIND == kFull || j < left_here) acc += (double)v[j];
-        tile_sum = add_lanes(acc);
+        out_sum.sum = add_lanes(acc);
     }
 
     // Places past the end take the last valid element: it belongs to the last group, whose minimum and
@@ -883,7 +892,7 @@ __device__ __forceinline__ uint32_t work_block(uint32_t run_end, uint32_t s) {
 
 template <bool WITH_F32, bool SUM, int WAVES>
 __device__ __forceinline__ void compress_block(const TensorArgs& t, const Geometry& geo,
-                                               int64_t block_in_tensor, double& tile_sum) {
+                                               int64_t block_in_tensor, TileOut& out_sum) {
     // sized by the launcher: geo.lds_wave_dwords per wavefront
     extern __shared__ __attribute__((aligned(16))) uint32_t lds_all[];
     const int wave = threadIdx.x >> 6;
@@ -894,9 +903,9 @@ __device__ __forceinline__ void compress_block(const TensorArgs& t, const Geomet
     // A tile is "full" when all its elements exist.  With other group sizes the last tile is never
     // treated as one: it also zeroes the pad words that lie past its lanes.
     const int64_t end = (tile + 1) * (int64_t)(geo.lanes_used * kPerLane);
-#define GACT_C_FULL(DT, BITS) compress_tile<DT, BITS, kFull, SUM>(t, geo, tile, lds, lane, tile_sum);
-#define GACT_C_ANY(DT, BITS)  compress_tile<DT, BITS, kFullAny, SUM>(t, geo, tile, lds, lane, tile_sum);
-#define GACT_C_EDGE(DT, BITS) compress_tile<DT, BITS, kEdge, SUM>(t, geo, tile, lds, lane, tile_sum);
+#define GACT_C_FULL(DT, BITS) compress_tile<DT, BITS, kFull, SUM>(t, geo, tile, lds, lane, out_sum);
+#define GACT_C_ANY(DT, BITS)  compress_tile<DT, BITS, kFullAny, SUM>(t, geo, tile, lds, lane, out_sum);
+#define GACT_C_EDGE(DT, BITS) compress_tile<DT, BITS, kEdge, SUM>(t, geo, tile, lds, lane, out_sum);
     // A tile in which the low word of the Philox block number wraps is not either (PhiloxUniform).
     const uint32_t blk = (uint32_t)(t.blk_base() + ((uint64_t)tile * (uint32_t)(geo.lanes_used * kPerLane) >> 3));
     if ((geo.pow2 ? end <= t.n : end < t.n) && blk <= 0xFFFFFEFFu) {
@@ -952,7 +961,7 @@ __device__ __forceinline__ void run_block(const TensorArgs& t, const Geometry& g
         const int64_t end = (block_in_tensor + 1) * dec_block_elems(t.dtype(), t.bits(), bf16_units(W));
         decompress_block<bf16_units(W)>(t, geo, block_in_tensor, end <= t.n);
     } else {
-        double unused;
+        TileOut unused;
         compress_block<W != kCompressBf16, false, waves_per_block(W)>(t, geo, block_in_tensor, unused);
     }
 }
@@ -977,22 +986,24 @@ GACT_KERNEL(W) single_kernel(uint32_t run_end, uint32_t shift_or_full, TensorArg
 // nothing, because a block's LDS is not given back before its last wavefront ends.)  Behind fin.blocks
 // blocks come those that take the sample points and add the sums, if these are tagged.
 __global__ __launch_bounds__(kBlockThreads) void compress_sum_kernel(uint32_t run_end, uint32_t run_shift, TensorArgs t,
-                                                                     Geometry geo, double* __restrict__ block_sum,
+                                                                     Geometry geo, double* block_sum,
                                                                      Finish fin, int n_samples) {
     __shared__ double part[kWavesPerBlk];
-    if (blockIdx.x >= fin.blocks) {
-        const uint32_t f = blockIdx.x - fin.blocks, adders = adders_for<kWavesPerBlk>(fin.blocks);
+    const uint32_t place = blockIdx.x - fin.ahead;
+    if (place >= fin.blocks) {
+        const uint32_t f = adding_block(fin, blockIdx.x), adders = adders_for<kWavesPerBlk>(fin.blocks);
         for (int j = (int)(f * kBlockThreads + threadIdx.x); j < n_samples; j += (int)(adders * kBlockThreads))
             sample(t.io, t.dtype(), t.n, j, n_samples, fin.out);
-        finish_block<kWavesPerBlk, true>((uint64_t*)block_sum, fin.blocks, fin.tag, fin.scale, fin.out, f);
+        finish_block<kWavesPerBlk, true>((uint64_t*)block_sum, fin, f);
         return;
     }
-    const uint32_t b = work_block(run_end, run_shift);
-    double sum = 0.0;                                 // stays so for a wavefront past the end
-    compress_block<true, true, kWavesPerBlk>(t, geo, (int64_t)b, sum);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+    const uint32_t b = ordered_block(place, run_end, run_shift);
+    TileOut tile;                                     // its sum stays 0 for a wavefront past the end
+    if (threadIdx.x < 64) tile.look = (const uint64_t*)fin.out;
+    compress_block<true, true, kWavesPerBlk>(t, geo, (int64_t)b, tile);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = tile.sum;
     __syncthreads();
-    if (threadIdx.x == 0) put_result(block_sum, b, (part[0] + part[1]) + (part[2] + part[3]), fin.tag);
+    if (threadIdx.x < 64) put_result<kWavesPerBlk>(block_sum, b, (part[0] + part[1]) + (part[2] + part[3]), fin, tile.word, (int)threadIdx.x);
 }
 
 // Multi-tensor: block b belongs to the tensor l with first_block[l] <= b <
@@ -1062,11 +1073,12 @@ extern "C" int gact_launch_single(gact::Work work, const gact::TensorArgs* t, co
 
 extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::Geometry* geo, unsigned blocks,
                                         double* d_block_sum, int tagged, uint64_t tag, int n_samples, double* d_out,
-                                        void* stream) {
+                                        void* stream, const gact::Late* late) {
     const unsigned lds = 4u * gact::kWavesPerBlk * (unsigned)geo->lds_wave_dwords;
     const gact::Runs runs = gact::runs_for(gact::kCompressAny, blocks);
-    const gact::Finish fin{tagged ? tag : 0, 1.0, d_out, blocks};
-    const dim3 grid(blocks + (tagged ? gact::adders_for<gact::kWavesPerBlk>(blocks) : 0));
+    const uint32_t adders = tagged ? gact::adders_for<gact::kWavesPerBlk>(blocks) : 0;
+    const gact::Finish fin = gact::finish_of(tagged ? tag : 0, 1.0, d_out, blocks, adders, late);
+    const dim3 grid(blocks + adders);
     hipLaunchKernelGGL(gact::compress_sum_kernel, grid, dim3(gact::kBlockThreads), lds,
                        (hipStream_t)stream, runs.end, runs.shift, *t, *geo, d_block_sum, fin, n_samples);
     return hipGetLastError() == hipSuccess ? 0 : -1;

@@ -115,7 +115,7 @@ __device__ __forceinline__ u4r load_piece16(const void* base, int64_t e, int64_t
 // FULL: the whole chunk lies inside the buffer, so all loads are unguarded and
 // issued back to back.
 template <int DT, bool FULL>
-__device__ __forceinline__ double diff_sq_chunk(const ReduceArgs& r, int64_t chunk) {
+__device__ __forceinline__ double diff_sq_chunk(const ReduceArgs& r, int64_t chunk, const Finish& fin, uint64_t& first_word) {
     constexpr int P = DT == GACT_DT_F32 ? 4 : 8;
     const int64_t e0 = chunk * (int64_t)(kRedThreads * kPieces * P) + (int64_t)threadIdx.x * P;
     u4r a[kPieces], b[kPieces];
@@ -125,6 +125,7 @@ __device__ __forceinline__ double diff_sq_chunk(const ReduceArgs& r, int64_t chu
         a[k] = load_piece16<DT, FULL>(r.a, e, r.n);
         b[k] = load_piece16<DT, FULL>(r.b, e, r.n);
     }
+    if (threadIdx.x < 64) first_word = result_word(fin);       // behind the others' loads, in nobody's way
     double acc = 0.0;
 #pragma unroll
     for (int k = 0; k < kPieces; ++k) {
@@ -140,44 +141,47 @@ __device__ __forceinline__ double diff_sq_chunk(const ReduceArgs& r, int64_t chu
     return acc;
 }
 
-__device__ __forceinline__ void diff_sq_block(const ReduceArgs& r, int64_t chunk, double* __restrict__ partial,
-                                              uint64_t tag) {
+__device__ __forceinline__ void diff_sq_block(const ReduceArgs& r, int64_t chunk, uint32_t place, double* partial,
+                                              const Finish& fin) {
+    uint64_t first_word = 0;
     const bool full = (chunk + 1) * reduce_chunk_elems(r.dtype) <= r.n;
     double acc;
     if (r.dtype == GACT_DT_F32)
-        acc = full ? diff_sq_chunk<GACT_DT_F32, true>(r, chunk) : diff_sq_chunk<GACT_DT_F32, false>(r, chunk);
+        acc = full ? diff_sq_chunk<GACT_DT_F32, true>(r, chunk, fin, first_word) : diff_sq_chunk<GACT_DT_F32, false>(r, chunk, fin, first_word);
     else
-        acc = full ? diff_sq_chunk<GACT_DT_BF16, true>(r, chunk) : diff_sq_chunk<GACT_DT_BF16, false>(r, chunk);
+        acc = full ? diff_sq_chunk<GACT_DT_BF16, true>(r, chunk, fin, first_word) : diff_sq_chunk<GACT_DT_BF16, false>(r, chunk, fin, first_word);
     double sum[1] = {acc};
     block_sums<kRedWaves>(sum);
-    if (threadIdx.x == 0) put_result(partial, blockIdx.x, sum[0], tag);
+    if (threadIdx.x < 64) put_result<kRedWaves>(partial, place, sum[0], fin, first_word, (int)threadIdx.x);
 }
 
 // Table in device memory (uploaded to the caller's workspace): any number of buffers.
 __global__ __launch_bounds__(kRedThreads) void diff_sq_kernel(const ReduceArgs* __restrict__ table,
                                                               const uint32_t* __restrict__ first_block,
-                                                              int K, double* __restrict__ partial, Finish fin) {
-    if (blockIdx.x >= fin.blocks) {
-        finish_block<kRedWaves, true>((uint64_t*)partial, fin.blocks, fin.tag, fin.scale, fin.out, blockIdx.x - fin.blocks);
+                                                              int K, double* partial, Finish fin) {
+    const uint32_t place = blockIdx.x - fin.ahead;
+    if (place >= fin.blocks) {
+        finish_block<kRedWaves, true>((uint64_t*)partial, fin, adding_block(fin, blockIdx.x));
         return;
     }
-    const uint32_t b = ordered_block(blockIdx.x, runs_end(fin.blocks, kDiffRunShift), kDiffRunShift);
+    const uint32_t b = ordered_block(place, runs_end(fin.blocks, kDiffRunShift), kDiffRunShift);
     const int k = find_buffer(first_block, K, b);
     const ReduceArgs r = table[k];
-    diff_sq_block(r, (int64_t)(b - first_block[k]), partial, fin.tag);
+    diff_sq_block(r, (int64_t)(b - first_block[k]), place, partial, fin);
 }
 
 // Table by value in the kernel arguments: no upload, which takes the stream 5 us
 // ahead of the kernel (96 bf16 pairs of 101 M elements: 67.8 us with, 65.6 us without).
 __global__ __launch_bounds__(kRedThreads) void diff_sq_inline_kernel(ReduceTable tab, int K,
-                                                                     double* __restrict__ partial, Finish fin) {
-    if (blockIdx.x >= fin.blocks) {
-        finish_block<kRedWaves, true>((uint64_t*)partial, fin.blocks, fin.tag, fin.scale, fin.out, blockIdx.x - fin.blocks);
+                                                                     double* partial, Finish fin) {
+    const uint32_t place = blockIdx.x - fin.ahead;
+    if (place >= fin.blocks) {
+        finish_block<kRedWaves, true>((uint64_t*)partial, fin, adding_block(fin, blockIdx.x));
         return;
     }
-    const uint32_t b = ordered_block(blockIdx.x, runs_end(fin.blocks, kDiffRunShift), kDiffRunShift);
+    const uint32_t b = ordered_block(place, runs_end(fin.blocks, kDiffRunShift), kDiffRunShift);
     const int k = find_buffer(tab.first_block, K, b);
-    diff_sq_block(tab.t[k], (int64_t)(b - tab.first_block[k]), partial, fin.tag);
+    diff_sq_block(tab.t[k], (int64_t)(b - tab.first_block[k]), place, partial, fin);
 }
 
 // ---------------------------------------------------------------- footprint
@@ -350,32 +354,31 @@ __global__ __launch_bounds__(stats_threads(WIDE)) void grad_stats_inline_kernel(
 // fp32 elements.
 constexpr int kFinThreads = 1024, kFinWaves = kFinThreads / 64;
 constexpr uint32_t kFinRows = 4 * kFinWaves;
-__global__ __launch_bounds__(kFinThreads) void finish_kernel(double* __restrict__ partial,
-                                                             uint32_t count, uint32_t adders,
-                                                             size_t out_pitch, uint64_t tag, double scale,
-                                                             double* __restrict__ out, ReduceArgs r, int n_samples) {
+__global__ __launch_bounds__(kFinThreads) void finish_kernel(double* partial, uint32_t adders, size_t out_pitch,
+                                                             Finish fin, ReduceArgs r, int n_samples) {
     __shared__ double lds[kFinRows];
     const uint32_t f = blockIdx.x;
     if (f >= adders) {
         const int j = (int)((f - adders) * kFinThreads + threadIdx.x);
-        if (j < n_samples) sample(r.a, r.dtype, r.n, j, n_samples, out);
+        if (j < n_samples) sample(r.a, r.dtype, r.n, j, n_samples, fin.out);
         return;
     }
     double* p = partial + (size_t)blockIdx.y * out_pitch;
+    fin.out += blockIdx.y;
     if (adders > 1) {
-        finish_block<kFinWaves, false>((uint64_t*)p, count, tag, scale, out + blockIdx.y, f);
+        finish_block<kFinWaves, false>((uint64_t*)p, fin, f);
         return;
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint32_t rows = rows_of(count);
+    const uint32_t rows = rows_of(fin.blocks);
     for (uint32_t row = (uint32_t)wave; row < rows; row += kFinWaves) {
-        const double s = plain_row(p, count, row, lane);
+        const double s = plain_row(p, fin.blocks, row, lane);
         if (lane == 0) lds[row] = s;
     }
     __syncthreads();
     if (wave != 0) return;
     const double total = add_lanes(add_own_rows(0.0, lds, 0, rows, lane));
-    if (lane == 0) out[blockIdx.y] = scale * total;
+    if (lane == 0) *fin.out = fin.scale * total;
 }
 
 // out[0 .. nout) = 0
@@ -386,21 +389,23 @@ __global__ void zero_kernel(double* __restrict__ out, int nout) {
 
 // Enqueues the final addition of `count` terms for each of `nout` outputs, and the sample points of r.
 static void launch_finish(double* d_partial, unsigned count, int nout, uint64_t tag, double scale, double* d_out,
-                          hipStream_t s, const ReduceArgs& r = ReduceArgs{}, int n_samples = 0) {
+                          hipStream_t s, const ReduceArgs& r = ReduceArgs{}, int n_samples = 0,
+                          const Late* late = nullptr) {
     const uint32_t adders = rows_of(count) <= kFinRows ? 1u : adders_for<kFinWaves>(count);
     const dim3 grid(adders + (n_samples + kFinThreads - 1) / kFinThreads, nout);
-    hipLaunchKernelGGL(finish_kernel, grid, dim3(kFinThreads), 0, s, d_partial, count, adders, (size_t)count, tag,
-                       scale, d_out, r, n_samples);
+    hipLaunchKernelGGL(finish_kernel, grid, dim3(kFinThreads), 0, s, d_partial, adders, (size_t)count,
+                       finish_of(tag, scale, d_out, count, 0, late), r, n_samples);
 }
 
 }  // namespace gact
 
 extern "C" int gact_launch_diff_sq(const gact::ReduceTable* inline_table, const gact::ReduceArgs* d_table,
                                    const uint32_t* d_first, int K, unsigned blocks, double* d_partial, int tagged,
-                                   uint64_t tag, double scale, double* d_out, void* stream) {
+                                   uint64_t tag, double scale, double* d_out, void* stream, const gact::Late* late) {
     hipStream_t s = (hipStream_t)stream;
-    const gact::Finish fin{tagged ? tag : 0, scale, d_out, blocks};
-    const dim3 grid(blocks + (tagged ? gact::adders_for<gact::kRedWaves>(blocks) : 0));
+    const uint32_t adders = tagged ? gact::adders_for<gact::kRedWaves>(blocks) : 0;
+    const gact::Finish fin = gact::finish_of(tagged ? tag : 0, scale, d_out, blocks, adders, late);
+    const dim3 grid(blocks + adders);
     if (inline_table)
         hipLaunchKernelGGL(gact::diff_sq_inline_kernel, grid, dim3(gact::kRedThreads), 0, s, *inline_table,
                            K, d_partial, fin);
@@ -447,9 +452,9 @@ extern "C" int gact_launch_footprint_finish(const gact::ReduceArgs* r, unsigned 
 }
 
 extern "C" int gact_launch_footprint(const gact::ReduceArgs* r, unsigned blocks, double* d_partial, uint64_t tag,
-                                     int n_samples, double* d_out, void* stream) {
+                                     int n_samples, double* d_out, void* stream, const gact::Late* late) {
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(gact::sum_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, *r, d_partial);
-    gact::launch_finish(d_partial, blocks, 1, tag, 1.0, d_out, s, *r, n_samples);
+    gact::launch_finish(d_partial, blocks, 1, tag, 1.0, d_out, s, *r, n_samples, late);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
