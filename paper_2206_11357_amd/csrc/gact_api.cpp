@@ -313,9 +313,10 @@ int stage_reduction(const std::vector<gact::ReduceArgs>& bufs, bool statistics, 
     red->K = K;
     red->blocks = (unsigned)blocks;
     red->d_partial = (double*)((unsigned char*)d_workspace + tb);
-    red->wide = statistics && blocks >= gact::kWideStats &&
+    red->wide = statistics && gact::wide_stats(blocks) &&
                 std::all_of(live.begin(), live.end(), [](const gact::ReduceArgs& r) { return r.dtype == GACT_F32 && aligned(r.b, 128); });
-    red->tagged = !statistics && workspace_bytes >= tb + 2 * blocks * sizeof(double) && blocks < 0x70000000u;
+    red->tagged = !statistics && workspace_bytes >= tb + 2 * blocks * sizeof(double) &&
+                  gact::room_for_adders<gact::kReduceWaves>(blocks);
     if (K <= gact::kInlineBuffers) {
         std::memcpy(red->inline_table.t, live.data(), (size_t)K * sizeof(gact::ReduceArgs));
         std::memcpy(red->inline_table.first_block, first.data(), first.size() * sizeof(uint32_t));
@@ -376,8 +377,8 @@ int compress_footprint(const void* d_x, gact_dtype dtype, int64_t n, int group_s
     // have from two tiles on) and the tag is this call's alone: not in a graph, whose replays share one, nor in
     // the library's scratch area, which calls that overlap in time may overwrite under each other.
     const uint64_t tag = next_tag();
-    const bool tagged = !limited && workspace_bytes >= 2 * (size_t)blocks * sizeof(double) && blocks < 0x70000000 &&
-                        !recorded(stream);
+    const bool tagged = !limited && workspace_bytes >= 2 * (size_t)blocks * sizeof(double) &&
+                        gact::room_for_adders<gact::waves_per_block(gact::kCompressAny)>((uint64_t)blocks) && !recorded(stream);
     if (gact_launch_compress_sum(&t, &geo, (unsigned)blocks, (double*)d_workspace, tagged, tag, n_samples, d_footprint,
                                  stream, nullptr) != 0)
         return GACT_E_HIP;

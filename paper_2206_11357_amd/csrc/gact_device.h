@@ -104,6 +104,7 @@ __device__ __forceinline__ uint32_t ordered_block(uint32_t b, uint32_t run_end, 
 enum Work { kDecompress, kCompressBf16, kCompressAny, kDecompressShort, kCompressLong };
 constexpr bool decompresses(Work w) { return w == kDecompress || w == kDecompressShort; }
 constexpr int waves_per_block(Work w) { return w == kCompressLong ? 1 : 4; }
+constexpr int kReduceWaves = 8;
 constexpr uint64_t kLongCompress = 32768;
 
 // LDS one compressing wavefront stages its tile in: 64 rows of 32 elements in
@@ -184,9 +185,14 @@ constexpr int64_t stats_block_elems(int dtype, int bf16_chunks) {
 static_assert(stats_block_elems(GACT_DT_BF16, 2) == reduce_chunk_elems(GACT_DT_BF16) &&
               stats_block_elems(GACT_DT_F32, 2) == reduce_chunk_elems(GACT_DT_F32), "the least workspace");
 
+// Threads of a launch: the runtime takes fewer than 2^32.
+constexpr bool launchable(uint64_t blocks, uint32_t threads) { return blocks * threads < 1ull << 32; }
+
 // A statistics launch of this many blocks and more, all of whose buffers are fp32 with a mean that starts
-// on a line, is one of wide blocks (stats_chunk).
+// on a line, is one of wide blocks (stats_chunk), up to what the runtime takes of those (17 G elements).
 constexpr uint64_t kWideStats = 8192;
+constexpr int stats_threads(bool wide) { return wide ? 1024 : 512; }
+constexpr bool wide_stats(uint64_t blocks) { return blocks >= kWideStats && launchable(blocks, stats_threads(true)); }
 
 // Decompress launch shape.  A unit is the 1 KB of output one coalesced
 // wavefront store covers (256 fp32 or 512 bf16 elements); a block of four

@@ -23,13 +23,11 @@ typedef uint32_t u4r __attribute__((ext_vector_type(4)));
 typedef uint32_t u2r __attribute__((ext_vector_type(2)));
 typedef float    f4r __attribute__((ext_vector_type(4)));
 
-constexpr int kRedThreads = 512;
+constexpr int kRedWaves = kReduceWaves, kRedThreads = 64 * kRedWaves;
 constexpr int kPieces = 2;              // per thread and buffer
-constexpr int kRedWaves = kRedThreads / 64;
 // A statistics chunk is two pieces of four elements per thread, or one of twice as many threads (stats_chunk).
-constexpr int stats_threads(bool wide) { return wide ? 1024 : kRedThreads; }
 constexpr int stats_pieces(bool wide) { return wide ? 1 : kPieces; }
-static_assert(kStatsChunkElems == stats_threads(false) * stats_pieces(false) * 4 &&
+static_assert(stats_threads(false) == kRedThreads && kStatsChunkElems == stats_threads(false) * stats_pieces(false) * 4 &&
               kStatsChunkElems == stats_threads(true) * stats_pieces(true) * 4, "the elements of a statistics chunk");
 static_assert(reduce_chunk_elems(GACT_DT_F32) == kRedThreads * kPieces * 4 &&
               reduce_chunk_elems(GACT_DT_BF16) == kRedThreads * kPieces * 8, "two pieces of 16 bytes per thread");
@@ -412,6 +410,7 @@ extern "C" int gact_launch_diff_sq(const gact::ReduceTable* inline_table, const 
     else
         hipLaunchKernelGGL(gact::diff_sq_kernel, grid, dim3(gact::kRedThreads), 0, s, d_table, d_first,
                            K, d_partial, fin);
+    if (hipGetLastError() != hipSuccess) return -1;       // no addition of what nothing leaves
     if (!tagged) gact::launch_finish(d_partial, blocks, 1, tag, scale, d_out, s);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -434,6 +433,7 @@ extern "C" int gact_launch_grad_stats(const gact::ReduceTable* inline_table, con
     hipStream_t s = (hipStream_t)stream;
     if (wide) launch_stats<true>(inline_table, d_table, d_first, K, rt, bf16_chunks, blocks, d_partial, s);
     else launch_stats<false>(inline_table, d_table, d_first, K, rt, bf16_chunks, blocks, d_partial, s);
+    if (hipGetLastError() != hipSuccess) return -1;
     gact::launch_finish(d_partial, blocks, 2, tag, 1.0, d_out, s);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -455,6 +455,7 @@ extern "C" int gact_launch_footprint(const gact::ReduceArgs* r, unsigned blocks,
                                      int n_samples, double* d_out, void* stream, const gact::Late* late) {
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(gact::sum_kernel, dim3(blocks), dim3(gact::kRedThreads), 0, s, *r, d_partial);
+    if (hipGetLastError() != hipSuccess) return -1;
     gact::launch_finish(d_partial, blocks, 1, tag, 1.0, d_out, s, *r, n_samples, late);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }

@@ -53,6 +53,14 @@ constexpr uint32_t kPatience = 1u << 14;          // looks, at about a microseco
 constexpr uint32_t kGrace = 1u << 20;
 
 __host__ __device__ constexpr uint32_t rows_of(uint32_t count) { return (count + kRowTerms - 1) / kRowTerms; }
+// Adding blocks of WAVES wavefronts, a row each.
+template <int WAVES>
+__host__ __device__ constexpr uint32_t adders_for(uint32_t count) { return (rows_of(count) + WAVES - 1) / WAVES; }
+// Whether a launch of `blocks` such blocks has room for them.
+template <int WAVES>
+constexpr bool room_for_adders(uint64_t blocks) {
+    return launchable(blocks, 64 * WAVES) && launchable(blocks + adders_for<WAVES>((uint32_t)blocks), 64 * WAVES);
+}
 
 // What a reducing launch needs to add its results itself.  tag 0: they stay as they are, one word each.
 struct Finish {
@@ -194,8 +202,6 @@ __device__ __forceinline__ double add_own_rows(double acc, const double* mine, u
 // Adding block f of adders_for<WAVES>(count): a wavefront adds one row; all blocks but the last leave
 // the row's sum behind, the last adds them up.  PAIRS: the results are tagged (else each is one word, and all
 // are there), so that a row has twice as many words.
-template <int WAVES>
-__host__ __device__ constexpr uint32_t adders_for(uint32_t count) { return (rows_of(count) + WAVES - 1) / WAVES; }
 template <bool PAIRS>
 __host__ __device__ constexpr size_t row_words() { return (PAIRS ? 2 : 1) * (size_t)kRowTerms; }
 

@@ -1,0 +1,51 @@
+"""The choices that a launch's size makes, on the host, at the sizes where the runtime takes no more threads (2^32) and
+where one form gives way to the next."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2206_11357_amd", "csrc")
+
+PROGRAM = r"""
+#include <cstdint>
+#include <cstdio>
+#include <initializer_list>
+#include "gact_device.h"
+#include "gact_sum.h"
+static int failed = 0;
+#define CHECK(X) do { if (!(X)) { std::printf("line %d: %s\n", __LINE__, #X); failed = 1; } } while (0)
+template <int WAVES>
+void adders() {
+    const uint64_t end = (1ull << 32) / (64 * WAVES);              // blocks that the runtime does not take
+    uint64_t most = 0;
+    for (uint64_t b = end - 5000; b <= end + 5000; ++b) {
+        const uint64_t with = b + ((b + 511) / 512 + WAVES - 1) / WAVES;
+        CHECK(gact::room_for_adders<WAVES>(b) == (with < end));
+        if (gact::room_for_adders<WAVES>(b)) most = b;
+    }
+    CHECK(most < end && most + most / (512 * WAVES) + 2 >= end);
+    for (uint64_t b : {1ull, 511ull, 100000ull}) CHECK(gact::room_for_adders<WAVES>(b));
+    for (uint64_t b : {end, 0x70000000ull, 0x7FFFFFFFull, 1ull << 32, (1ull << 32) + 1}) CHECK(!gact::room_for_adders<WAVES>(b));
+}
+int main() {
+    const uint64_t least = gact::kWideStats, end = 1ull << 22;     // 2^32 threads in blocks of 1024
+    CHECK(!gact::wide_stats(1) && !gact::wide_stats(least - 1) && gact::wide_stats(least));
+    CHECK(gact::wide_stats(end - 1) && !gact::wide_stats(end) && !gact::wide_stats((1ull << 23) - 1) && !gact::wide_stats(0x7FFFFFFFull));
+    for (uint64_t b = 1; b < 1ull << 31; b += 4093)
+        CHECK(!gact::wide_stats(b) || b * gact::stats_threads(true) < 1ull << 32);
+    CHECK(gact::launchable((1ull << 23) - 1, gact::stats_threads(false)));
+    adders<gact::kReduceWaves>();
+    adders<gact::waves_per_block(gact::kCompressAny)>();
+    // the compressor of long launches takes at most four blocks of 64 threads for each of 256
+    CHECK(4 * 64 * gact::waves_per_block(gact::kCompressLong) == 64 * gact::waves_per_block(gact::kCompressAny));
+    return failed;
+}
+"""
+
+
+def test_launches_keep_to_what_the_runtime_takes(tmp_path):
+    src, exe = tmp_path / "limits.cpp", tmp_path / "limits"
+    src.write_text(PROGRAM)
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)])
+    done = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert done.returncode == 0, done.stdout
