@@ -18,14 +18,14 @@ template <int WAVES>
 void adders() {
     const uint64_t end = (1ull << 32) / (64 * WAVES);              // blocks that the runtime does not take
     uint64_t most = 0;
-    for (uint64_t b = end - 5000; b <= end + 5000; ++b) {
+    for (uint64_t b = end - 20000; b <= end + 20000; ++b) {
         const uint64_t with = b + ((b + 511) / 512 + WAVES - 1) / WAVES;
         CHECK(gact::room_for_adders<WAVES>(b) == (with < end));
         if (gact::room_for_adders<WAVES>(b)) most = b;
     }
     CHECK(most < end && most + most / (512 * WAVES) + 2 >= end);
-    for (uint64_t b : {1ull, 511ull, 100000ull}) CHECK(gact::room_for_adders<WAVES>(b));
-    for (uint64_t b : {end, 0x70000000ull, 0x7FFFFFFFull, 1ull << 32, (1ull << 32) + 1}) CHECK(!gact::room_for_adders<WAVES>(b));
+    for (uint64_t b : {(uint64_t)1, (uint64_t)511, (uint64_t)100000}) CHECK(gact::room_for_adders<WAVES>(b));
+    for (uint64_t b : {end, (uint64_t)0x70000000, (uint64_t)0x7FFFFFFF, (uint64_t)1 << 32, ((uint64_t)1 << 32) + 1}) CHECK(!gact::room_for_adders<WAVES>(b));
 }
 int main() {
     const uint64_t least = gact::kWideStats, end = 1ull << 22;     // 2^32 threads in blocks of 1024
