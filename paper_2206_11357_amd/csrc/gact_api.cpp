@@ -313,7 +313,7 @@ int stage_reduction(const std::vector<gact::ReduceArgs>& bufs, bool statistics, 
     red->K = K;
     red->blocks = (unsigned)blocks;
     red->d_partial = (double*)((unsigned char*)d_workspace + tb);
-    red->wide = statistics && gact::wide_stats(blocks) &&
+    red->wide = statistics && gact::wide_stats(blocks, (uint64_t)K) &&
                 std::all_of(live.begin(), live.end(), [](const gact::ReduceArgs& r) { return r.dtype == GACT_F32 && aligned(r.b, 128); });
     red->tagged = !statistics && workspace_bytes >= tb + 2 * blocks * sizeof(double) &&
                   gact::room_for_adders<gact::kReduceWaves>(blocks);

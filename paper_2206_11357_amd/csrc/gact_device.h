@@ -189,10 +189,20 @@ static_assert(stats_block_elems(GACT_DT_BF16, 2) == reduce_chunk_elems(GACT_DT_B
 constexpr bool launchable(uint64_t blocks, uint32_t threads) { return blocks * threads < 1ull << 32; }
 
 // A statistics launch of this many blocks and more, all of whose buffers are fp32 with a mean that starts
-// on a line, is one of wide blocks (stats_chunk), up to what the runtime takes of those (17 G elements).
-constexpr uint64_t kWideStats = 8192;
+// on a line, is one of wide blocks (stats_chunk), up to what the runtime takes of those (17 G elements); but
+// not where a buffer has fewer than kWideBlocks blocks on average: a block first finds its buffer, log2 of their
+// number of loads one after the other, then often cut short by the buffer's end, and half as many blocks are
+// there to hide that.  Us, narrow | wide blocks, buffers of equal size:
+//   M elements, buffers   100         312         600         1000        2000        4000        8000
+//        40            79.6 | 80   83.0 | 84   86.2 | 89   89.1 | 92    101 | 110   106 | 120   127 | 161
+//        80             159 | 152   159 | 154   166 | 160   170 | 166   175 | 188   181 | 198   191 | 217
+//       160             319 | 292   315 | 298   319 | 304   349 | 307   337 | 335   323 | 350   334 | 370
+//       300             587 | 544   611 | 547   645 | 561   623 | 562   625 | 586   574 | 612   602 | 655
+constexpr uint64_t kWideStats = 8192, kWideBlocks = 24;
 constexpr int stats_threads(bool wide) { return wide ? 1024 : 512; }
-constexpr bool wide_stats(uint64_t blocks) { return blocks >= kWideStats && launchable(blocks, stats_threads(true)); }
+constexpr bool wide_stats(uint64_t blocks, uint64_t buffers) {
+    return blocks >= kWideStats && blocks >= kWideBlocks * buffers && launchable(blocks, stats_threads(true));
+}
 
 // Decompress launch shape.  A unit is the 1 KB of output one coalesced
 // wavefront store covers (256 fp32 or 512 bf16 elements); a block of four

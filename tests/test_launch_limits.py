@@ -29,10 +29,13 @@ void adders() {
 }
 int main() {
     const uint64_t least = gact::kWideStats, end = 1ull << 22;     // 2^32 threads in blocks of 1024
-    CHECK(!gact::wide_stats(1) && !gact::wide_stats(least - 1) && gact::wide_stats(least));
-    CHECK(gact::wide_stats(end - 1) && !gact::wide_stats(end) && !gact::wide_stats((1ull << 23) - 1) && !gact::wide_stats(0x7FFFFFFFull));
+    CHECK(!gact::wide_stats(1, 1) && !gact::wide_stats(least - 1, 1) && gact::wide_stats(least, 1));
+    CHECK(gact::wide_stats(end - 1, 1) && !gact::wide_stats(end, 1) && !gact::wide_stats((1ull << 23) - 1, 1) && !gact::wide_stats(0x7FFFFFFFull, 1));
     for (uint64_t b = 1; b < 1ull << 31; b += 4093)
-        CHECK(!gact::wide_stats(b) || b * gact::stats_threads(true) < 1ull << 32);
+        CHECK(!gact::wide_stats(b, 1) || b * gact::stats_threads(true) < 1ull << 32);
+    // many small buffers: a block that is short of its buffer's search
+    CHECK(gact::wide_stats(24 * 1000, 1000) && !gact::wide_stats(24 * 1000 - 1, 1000) && !gact::wide_stats(9000, 9000));
+    CHECK(!gact::wide_stats(least, least) && gact::wide_stats(least, 312));
     CHECK(gact::launchable((1ull << 23) - 1, gact::stats_threads(false)));
     adders<gact::kReduceWaves>();
     adders<gact::waves_per_block(gact::kCompressAny)>();
