@@ -48,10 +48,10 @@ int64_t tiles_for(int64_t n, const gact::Geometry& geo) {
     return (n + te - 1) / te;
 }
 
-// Fills `out`; returns GACT_OK or the error for this tensor.
+// Fills `out` and the tensor's tiles; returns GACT_OK or the error for this tensor.
 int make_args(bool compress, const void* x, void* packed, float* gmin, float* gscale, void* y,
               int64_t n, uint64_t seed, int64_t index_base, int bits, int dtype,
-              const gact::Geometry& geo, gact::TensorArgs* out) {
+              const gact::Geometry& geo, gact::TensorArgs* out, uint32_t* out_tiles) {
     if (!bits_ok(bits)) return GACT_E_BITS;
     if (n < 0 || !dtype_ok(dtype)) return GACT_E_ARG;
     // noise is drawn per block of 8 elements: a shard starts on a block boundary
@@ -64,6 +64,7 @@ int make_args(bool compress, const void* x, void* packed, float* gmin, float* gs
     }
     const int64_t tiles = tiles_for(n, geo);
     if (tiles > 0xFFFFFFFFll) return GACT_E_ARG;
+    *out_tiles = (uint32_t)tiles;
     out->io = compress ? const_cast<void*>(x) : y;
     out->packed = packed;
     out->gmin = gmin;
@@ -78,10 +79,11 @@ int make_args(bool compress, const void* x, void* packed, float* gmin, float* gs
 }
 
 // blocks a tensor needs: compress takes a wavefront per tile, decompress
-// a fixed span of elements per block
-int64_t blocks_for(gact::Work work, const gact::TensorArgs& t, const gact::Geometry& geo) {
-    const int waves = gact::waves_per_block(work);
-    if (!decompresses(work)) return (tiles_for(t.n, geo) + waves - 1) / waves;
+// a fixed span of elements per block.  (The tiles are passed on and not counted anew: the division, once more for
+// each of 40,000 tensors where a launch turned out to be long, took the host 100 us beside 355.)
+int64_t blocks_for(gact::Work work, const gact::TensorArgs& t, uint32_t tiles) {
+    const uint32_t waves = gact::waves_per_block(work);
+    if (!decompresses(work)) return ((int64_t)tiles + waves - 1) / waves;
     const int64_t span = gact::dec_block_elems(t.dtype(), t.bits(), work == gact::kDecompressShort ? gact::kDecUnitsBf16Short : gact::kDecUnitsBf16);
     return (t.n + span - 1) / span;
 }
@@ -98,13 +100,13 @@ gact::Work work_of_length(gact::Work work, uint64_t blocks) {
     return work;
 }
 
-int run_single(bool compress, const gact::TensorArgs& t, const gact::Geometry& geo, void* stream) {
+int run_single(bool compress, const gact::TensorArgs& t, uint32_t tiles, const gact::Geometry& geo, void* stream) {
     if (t.n == 0) return GACT_OK;
     const gact::Work work = work_for(compress, geo);
-    int64_t blocks = blocks_for(work, t, geo);
+    int64_t blocks = blocks_for(work, t, tiles);
     if (blocks > 0x7FFFFFFFll) return GACT_E_ARG;
     const gact::Work final_work = work_of_length(work, (uint64_t)blocks);
-    if (final_work != work) blocks = blocks_for(final_work, t, geo);
+    if (final_work != work) blocks = blocks_for(final_work, t, tiles);
     return gact_launch_single(final_work, &t, &geo, (unsigned)blocks, stream) == 0
                ? GACT_OK : GACT_E_HIP;
 }
@@ -176,9 +178,10 @@ int run_multi(bool compress, const gact_tensor_desc* descs, int L, int group_siz
     // one contiguous staging image: table of the non-empty tensors, then the
     // first block of each, then the total
     std::vector<gact::TensorArgs> table;
-    std::vector<uint32_t> first;
+    std::vector<uint32_t> first, tiles;
     table.reserve(L);
     first.reserve(L + 1);
+    if (compress) tiles.reserve(L);
     uint64_t blocks = 0;
     for (int l = 0; l < L; ++l) {
         const gact_tensor_desc& d = descs[l];
@@ -187,14 +190,16 @@ int run_multi(bool compress, const gact_tensor_desc* descs, int L, int group_siz
             continue;
         }
         gact::TensorArgs t;
+        uint32_t its_tiles;
         const int rc = make_args(compress, d.x, d.packed, d.gmin, d.gscale, d.y, d.n, d.seed,
-                                 compress ? d.index_base : 0, d.bits, d.dtype, geo, &t);
+                                 compress ? d.index_base : 0, d.bits, d.dtype, geo, &t, &its_tiles);
         if (rc != GACT_OK) return rc;
         if (d.n == 0) continue;
         first.push_back((uint32_t)blocks);
         table.push_back(t);
+        if (compress) tiles.push_back(its_tiles);
         geo.lds_wave_dwords = std::max(geo.lds_wave_dwords, gact::lds_dwords_per_wave(d.dtype));
-        blocks += (uint64_t)blocks_for(compress ? gact::kCompressAny : gact::kDecompress, t, geo);
+        blocks += (uint64_t)blocks_for(compress ? gact::kCompressAny : gact::kDecompress, t, its_tiles);
         if (blocks > 0x7FFFFFFFull) return GACT_E_ARG;
     }
     const int live = (int)table.size();
@@ -205,7 +210,7 @@ int run_multi(bool compress, const gact_tensor_desc* descs, int L, int group_siz
         blocks = 0;
         for (int l = 0; l < live; ++l) {
             first[l] = (uint32_t)blocks;
-            blocks += (uint64_t)blocks_for(work, table[l], geo);
+            blocks += (uint64_t)blocks_for(work, table[l], compress ? tiles[l] : 0);
         }
     }
     first.push_back((uint32_t)blocks);
@@ -362,16 +367,17 @@ int compress_footprint(const void* d_x, gact_dtype dtype, int64_t n, int group_s
     gact::Geometry geo = make_geometry(group_size);
     geo.lds_wave_dwords = gact::lds_dwords_per_wave((int)dtype);
     gact::TensorArgs t;
+    uint32_t tiles;
     const int rc = make_args(true, d_x, d_packed, d_gmin, d_gscale, nullptr, n, seed, 0, bits,
-                             (int)dtype, geo, &t);
+                             (int)dtype, geo, &t, &tiles);
     if (rc != GACT_OK) return rc;
     if (n == 0)
         return gact_launch_zero(d_footprint, 1 + n_samples, stream) == 0 ? GACT_OK : GACT_E_HIP;
     // The documented size, a sum per tile; one per block of four tiles is used.
-    const size_t need = (size_t)tiles_for(n, geo) * sizeof(double);
+    const size_t need = (size_t)tiles * sizeof(double);
     if (!d_workspace || !aligned(d_workspace, 16) || workspace_bytes < need)
         return limited ? GACT_E_SCRATCH : GACT_E_ARG;
-    const int64_t blocks = blocks_for(gact::kCompressAny, t, geo);
+    const int64_t blocks = blocks_for(gact::kCompressAny, t, tiles);
     if (blocks > 0x7FFFFFFFll) return GACT_E_ARG;
     // The launch adds its sums itself where the workspace has two words for each (all of the documented size
     // have from two tiles on) and the tag is this call's alone: not in a graph, whose replays share one, nor in
@@ -399,10 +405,11 @@ int gact_compress(const void* d_x, gact_dtype dtype, int64_t n, int group_size, 
     gact::Geometry geo = make_geometry(group_size);
     geo.lds_wave_dwords = gact::lds_dwords_per_wave((int)dtype);
     gact::TensorArgs t;
+    uint32_t tiles;
     const int rc = make_args(true, d_x, d_packed, d_gmin, d_gscale, nullptr, n, seed, 0, bits,
-                             (int)dtype, geo, &t);
+                             (int)dtype, geo, &t, &tiles);
     if (rc != GACT_OK) return rc;
-    return run_single(true, t, geo, stream);
+    return run_single(true, t, tiles, geo, stream);
 }
 
 int gact_decompress(const void* d_packed, const float* d_gmin, const float* d_gscale, int64_t n,
@@ -411,11 +418,12 @@ int gact_decompress(const void* d_packed, const float* d_gmin, const float* d_gs
     if (!group_ok(group_size)) return GACT_E_GROUP;
     const gact::Geometry geo = make_geometry(group_size);
     gact::TensorArgs t;
+    uint32_t tiles;
     const int rc = make_args(false, nullptr, const_cast<void*>(d_packed),
                              const_cast<float*>(d_gmin), const_cast<float*>(d_gscale), d_y, n, 0, 0,
-                             bits, (int)dtype, geo, &t);
+                             bits, (int)dtype, geo, &t, &tiles);
     if (rc != GACT_OK) return rc;
-    return run_single(false, t, geo, stream);
+    return run_single(false, t, tiles, geo, stream);
 }
 
 size_t gact_multi_workspace_bytes(int L) {
