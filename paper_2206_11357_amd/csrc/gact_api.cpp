@@ -384,7 +384,7 @@ int compress_footprint(const void* d_x, gact_dtype dtype, int64_t n, int group_s
     // the library's scratch area, which calls that overlap in time may overwrite under each other.
     const uint64_t tag = next_tag();
     const bool tagged = !limited && workspace_bytes >= 2 * (size_t)blocks * sizeof(double) &&
-                        gact::room_for_adders<gact::waves_per_block(gact::kCompressAny)>((uint64_t)blocks) && !recorded(stream);
+                        gact::room_for_adders<gact::waves_per_block(gact::kCompressAny)>((uint64_t)blocks, n_samples) && !recorded(stream);
     if (gact_launch_compress_sum(&t, &geo, (unsigned)blocks, (double*)d_workspace, tagged, tag, n_samples, d_footprint,
                                  stream, nullptr) != 0)
         return GACT_E_HIP;

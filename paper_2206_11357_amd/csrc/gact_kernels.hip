@@ -984,17 +984,25 @@ GACT_KERNEL(W) single_kernel(uint32_t run_end, uint32_t shift_or_full, TensorArg
 // One tensor, compressed, with the sum of every block's elements as a by-product.  (One sum per block
 // and not per tile: the addition that follows reads a quarter of the terms, and the barrier costs
 // nothing, because a block's LDS is not given back before its last wavefront ends.)  Behind fin.blocks
-// blocks come those that take the sample points and add the sums, if these are tagged.
+// blocks come, if the sums are tagged, those that take the sample points and those that add the sums.
+// The former are blocks of their own because there may be more sample points than the adding blocks, one for 16.8 M
+// elements, have threads.  Us a call with 8, 1,024 and 32,768 points, points taken by the adding blocks (with a division
+// in 128 bits) and as now: 1 M elements 6.0, 11.7, 340 and 6.0, 6.1, 6.0; 17 M 14.9, 24.7, 425 and 15.0, 15.3, 15.4; 51 M
+// 37.8, 38.9, 143 and 37.9, 38.1, 38.1.  (With a launch behind for both: 1 M 9.3, 10.2, 11.3; 51 M 40.8, 44.1, 44.8.)
+// The arguments pass the 112 bytes that cost the host 0.6 us (gact_device.h); the launch saved was 3.7 us.
 __global__ __launch_bounds__(kBlockThreads) void compress_sum_kernel(uint32_t run_end, uint32_t run_shift, TensorArgs t,
                                                                      Geometry geo, double* block_sum,
                                                                      Finish fin, int n_samples) {
     __shared__ double part[kWavesPerBlk];
     const uint32_t place = blockIdx.x - fin.ahead;
     if (place >= fin.blocks) {
-        const uint32_t f = adding_block(fin, blockIdx.x), adders = adders_for<kWavesPerBlk>(fin.blocks);
-        for (int j = (int)(f * kBlockThreads + threadIdx.x); j < n_samples; j += (int)(adders * kBlockThreads))
-            sample(t.io, t.dtype(), t.n, j, n_samples, fin.out);
-        finish_block<kWavesPerBlk, true>((uint64_t*)block_sum, fin, f);
+        const uint32_t past = place - fin.blocks, samplers = samplers_for<kWavesPerBlk>(n_samples);
+        if (past < samplers) {
+            const int j = (int)(past * kBlockThreads + threadIdx.x);
+            if (j < n_samples) sample(t.io, t.dtype(), t.n, j, n_samples, fin.out);
+            return;
+        }
+        finish_block<kWavesPerBlk, true>((uint64_t*)block_sum, fin, fin.ahead ? blockIdx.x : past - samplers);
         return;
     }
     const uint32_t b = ordered_block(place, run_end, run_shift);
@@ -1078,7 +1086,7 @@ extern "C" int gact_launch_compress_sum(const gact::TensorArgs* t, const gact::G
     const gact::Runs runs = gact::runs_for(gact::kCompressAny, blocks);
     const uint32_t adders = tagged ? gact::adders_for<gact::kWavesPerBlk>(blocks) : 0;
     const gact::Finish fin = gact::finish_of(tagged ? tag : 0, 1.0, d_out, blocks, adders, late);
-    const dim3 grid(blocks + adders);
+    const dim3 grid(blocks + adders + (tagged ? gact::samplers_for<gact::kWavesPerBlk>(n_samples) : 0));
     hipLaunchKernelGGL(gact::compress_sum_kernel, grid, dim3(gact::kBlockThreads), lds,
                        (hipStream_t)stream, runs.end, runs.shift, *t, *geo, d_block_sum, fin, n_samples);
     return hipGetLastError() == hipSuccess ? 0 : -1;

@@ -56,10 +56,14 @@ __host__ __device__ constexpr uint32_t rows_of(uint32_t count) { return (count +
 // Adding blocks of WAVES wavefronts, a row each.
 template <int WAVES>
 __host__ __device__ constexpr uint32_t adders_for(uint32_t count) { return (rows_of(count) + WAVES - 1) / WAVES; }
+// Blocks that take a footprint's sample points, one a thread.
+template <int WAVES>
+__host__ __device__ constexpr uint32_t samplers_for(int n_samples) { return ((uint32_t)n_samples + 64 * WAVES - 1) / (64 * WAVES); }
 // Whether a launch of `blocks` such blocks has room for them.
 template <int WAVES>
-constexpr bool room_for_adders(uint64_t blocks) {
-    return launchable(blocks, 64 * WAVES) && launchable(blocks + adders_for<WAVES>((uint32_t)blocks), 64 * WAVES);
+constexpr bool room_for_adders(uint64_t blocks, int n_samples = 0) {
+    return launchable(blocks, 64 * WAVES) &&
+           launchable(blocks + adders_for<WAVES>((uint32_t)blocks) + samplers_for<WAVES>(n_samples), 64 * WAVES);
 }
 
 // What a reducing launch needs to add its results itself.  tag 0: they stay as they are, one word each.
@@ -292,9 +296,10 @@ __device__ __forceinline__ void finish_block(uint64_t* words, const Finish& fin,
     try_finish<WAVES, PAIRS>(words, fin, 0, lane);
 }
 
-// A footprint's sample point: out[1 + j] = element floor(j * n / n_samples) as binary64
+// A footprint's sample point: out[1 + j] = element floor(j * n / n_samples) as binary64.  (j < 2^15, and n at most
+// 2^44, from the number of blocks that a launch may have.)
 __device__ __forceinline__ void sample(const void* x, int dtype, int64_t n, int j, int n_samples, double* __restrict__ out) {
-    const int64_t i = (int64_t)(((unsigned __int128)(uint64_t)j * (uint64_t)n) / (uint64_t)n_samples);
+    const int64_t i = (int64_t)((uint64_t)j * (uint64_t)n / (uint32_t)n_samples);
     float v;
     if (dtype == GACT_DT_F32) v = ((const float*)x)[i];
     else v = __builtin_bit_cast(float, (uint32_t)((const uint16_t*)x)[i] << 16);

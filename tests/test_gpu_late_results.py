@@ -60,12 +60,13 @@ def test_sensitivity(gact, blocks, late):
 
 
 @pytest.mark.parametrize("late", LATE)
-@pytest.mark.parametrize("blocks", (2, 513, 2049, 40001))
-def test_compressor_with_a_footprint(gact, blocks, late):
-    G, bits, ns = 256, 2, 3
+@pytest.mark.parametrize("blocks,ns", [(2, 3), (2, 257), (513, 0), (513, 256), (2049, 1), (2049, 32768), (40001, 3)])
+def test_compressor_with_a_footprint(gact, blocks, ns, late):
+    G, bits = 256, 2
     n = blocks * 8192 - 77
     x = counted(251, n).float()
     want = gact.gact_compress_footprint(x, G, bits, 5, ns)
+    assert want[3][1:].cpu().tolist() == [float(j * n // ns % 251) for j in range(ns)]
     p, mn, sc = gact.alloc_compressed(n, G, bits, x.device)
     t = TensorArgs(x.data_ptr(), p.data_ptr(), mn.data_ptr(), sc.data_ptr(), n, 5, 0, 0, bits | gact.GACT_F32 << 8)
     lpg, lds = G // 32, 64 * 32

@@ -22,6 +22,7 @@ void adders() {
         const uint64_t with = b + ((b + 511) / 512 + WAVES - 1) / WAVES;
         CHECK(gact::room_for_adders<WAVES>(b) == (with < end));
         if (gact::room_for_adders<WAVES>(b)) most = b;
+        CHECK(gact::room_for_adders<WAVES>(b, 1000) == (with + (1000 + 64 * WAVES - 1) / (64 * WAVES) < end));
     }
     CHECK(most < end && most + most / (512 * WAVES) + 2 >= end);
     for (uint64_t b : {(uint64_t)1, (uint64_t)511, (uint64_t)100000}) CHECK(gact::room_for_adders<WAVES>(b));
@@ -37,6 +38,9 @@ int main() {
     CHECK(gact::wide_stats(24 * 1000, 1000) && !gact::wide_stats(24 * 1000 - 1, 1000) && !gact::wide_stats(9000, 9000));
     CHECK(!gact::wide_stats(least, least) && gact::wide_stats(least, 312));
     CHECK(gact::launchable((1ull << 23) - 1, gact::stats_threads(false)));
+    // a sample point a thread, whatever the number of sums
+    CHECK(gact::samplers_for<4>(0) == 0 && gact::samplers_for<4>(1) == 1 && gact::samplers_for<4>(256) == 1);
+    CHECK(gact::samplers_for<4>(257) == 2 && gact::samplers_for<4>(32768) == 128);
     adders<gact::kReduceWaves>();
     adders<gact::waves_per_block(gact::kCompressAny)>();
     // the compressor of long launches takes at most four blocks of 64 threads for each of 256
