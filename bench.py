@@ -273,7 +273,8 @@ def main() -> int:
     kernel = "gact::multi_inline_kernel<%s>" if L <= 64 else "gact::multi_kernel<%s>"
     valu = COMPRESS_VALU_PER_ELEMENT[S.specs[0].dtype] * S.n_total / c_avg * 1e3
 
-    long_launch = sum(-(-sp.numel // 8192) for sp in S.specs) >= 32768       # blocks of four tiles
+    block = 4 * (64 // (G // 32)) * G                                        # elements of four wavefront tiles
+    long_launch = sum(-(-sp.numel // block) for sp in S.specs) >= 32768
     work = "kCompressBf16" if all(sp.dtype == "bf16" for sp in S.specs) else "kCompressLong" if long_launch else "kCompressAny"
     roof = {"bound": "hbm", "kernel": kernel % work, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
