@@ -94,9 +94,9 @@ gact::Work work_for(bool compress, const gact::Geometry& geo) {
     if (!compress) return gact::kDecompress;
     return geo.lds_wave_dwords == gact::lds_dwords_per_wave(GACT_BF16) ? gact::kCompressBf16 : gact::kCompressAny;
 }
-gact::Work work_of_length(gact::Work work, uint64_t blocks) {
+gact::Work work_of_length(gact::Work work, uint64_t blocks, uint64_t bf16_blocks, const gact::Geometry& geo) {
     if (work == gact::kDecompress && blocks < gact::kShortLaunch) return gact::kDecompressShort;
-    if (work == gact::kCompressAny && blocks >= gact::kLongCompress && blocks <= 0x7FFFFFFFull / 4) return gact::kCompressLong;
+    if (work == gact::kCompressAny && gact::long_compress(blocks, bf16_blocks, geo.lanes_used)) return gact::kCompressLong;
     return work;
 }
 
@@ -105,7 +105,7 @@ int run_single(bool compress, const gact::TensorArgs& t, uint32_t tiles, const g
     const gact::Work work = work_for(compress, geo);
     int64_t blocks = blocks_for(work, t, tiles);
     if (blocks > 0x7FFFFFFFll) return GACT_E_ARG;
-    const gact::Work final_work = work_of_length(work, (uint64_t)blocks);
+    const gact::Work final_work = work_of_length(work, (uint64_t)blocks, 0, geo);
     if (final_work != work) blocks = blocks_for(final_work, t, tiles);
     return gact_launch_single(final_work, &t, &geo, (unsigned)blocks, stream) == 0
                ? GACT_OK : GACT_E_HIP;
@@ -182,7 +182,7 @@ int run_multi(bool compress, const gact_tensor_desc* descs, int L, int group_siz
     table.reserve(L);
     first.reserve(L + 1);
     if (compress) tiles.reserve(L);
-    uint64_t blocks = 0;
+    uint64_t blocks = 0, bf16_blocks = 0;
     for (int l = 0; l < L; ++l) {
         const gact_tensor_desc& d = descs[l];
         if (d.bits == GACT_BITS_UNCOMPRESSED) {          // left uncompressed by the allocator
@@ -199,13 +199,15 @@ int run_multi(bool compress, const gact_tensor_desc* descs, int L, int group_siz
         table.push_back(t);
         if (compress) tiles.push_back(its_tiles);
         geo.lds_wave_dwords = std::max(geo.lds_wave_dwords, gact::lds_dwords_per_wave(d.dtype));
-        blocks += (uint64_t)blocks_for(compress ? gact::kCompressAny : gact::kDecompress, t, its_tiles);
+        const uint64_t its_blocks = (uint64_t)blocks_for(compress ? gact::kCompressAny : gact::kDecompress, t, its_tiles);
+        blocks += its_blocks;
+        if (d.dtype == GACT_BF16) bf16_blocks += its_blocks;
         if (blocks > 0x7FFFFFFFull) return GACT_E_ARG;
     }
     const int live = (int)table.size();
     if (live == 0) return GACT_OK;
     gact::Work work = work_for(compress, geo);
-    if (const gact::Work w = work_of_length(work, blocks); w != work) {
+    if (const gact::Work w = work_of_length(work, blocks, bf16_blocks, geo); w != work) {
         work = w;
         blocks = 0;
         for (int l = 0; l < live; ++l) {

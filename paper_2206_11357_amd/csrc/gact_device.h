@@ -94,9 +94,10 @@ __device__ __forceinline__ uint32_t ordered_block(uint32_t b, uint32_t run_end, 
 //                  of these more are resident (a block of four needs 32 KB of the 160 at once) and each
 //                  leaves by itself.  Us, blocks of four | of one: 53 fp32 tensors of 0.7 G elements 479 | 469,
 //                  4 bits 520 | 507, groups of 1024 490 | 480, one of 0.42 G, 4 bits 307 | 294; 40 of both types,
-//                  0.9 G 504 | 505.  Shorter launches gain nothing for sure, or lose (89 M elements 59.4 | 59.7,
-//                  87 M 69.3 | 69.0, 67 M 45.8 | 46.5, 7 M 6.3 | 6.6), and bf16 gains 1 % on some sets
-//                  and loses 2 % on others (400 tensors of 2 G elements 829 | 843).
+//                  0.9 G 504 | 505.  Shorter launches gain nothing for sure, or lose (53 fp32 tensors, 2 bits, 89 M
+//                  elements 59.0 | 59.1, 0.18 G 119 | 120, 0.27 G 176 | 180), and bf16 gains 1 % on some sets
+//                  and loses 2 % on others (400 tensors of 2 G elements 829 | 843).  Nor is it for tiles that leave
+//                  1 to 9 lanes without data (long_compress).
 // A decompressing launch of fewer than kShortLaunch blocks is a kernel of its own, for
 // its units per wavefront and because such a launch has no block order.  (As a branch
 // in one kernel it gave back half of what the other units gain: one bf16 tensor of
@@ -106,6 +107,18 @@ constexpr bool decompresses(Work w) { return w == kDecompress || w == kDecompres
 constexpr int waves_per_block(Work w) { return w == kCompressLong ? 1 : 4; }
 constexpr int kReduceWaves = 8;
 constexpr uint64_t kLongCompress = 32768;
+// Whether `blocks` of kCompressAny, among them bf16_blocks of bf16 tensors, are launched as kCompressLong (whose grid has
+// four times as many).  The time of blocks of four wavefronts over that of blocks of one, lists of 15 and 80 fp32 tensors of
+// unequal sizes and widths, 0.3 to 0.7 G elements, by the lanes that hold data in a tile, which are whole groups:
+//   lanes        64          63          62         60         58    57    56    55    54    52    51   44-50
+//          1.010-1.018  0.991-1.003  0.977  0.969-0.980  0.980 0.988 0.995 1.003 1.009 1.019 1.017  1.020
+// (Tiles of the 64 are 8 KB and begin on 8 KB; those that leave 10 lanes and more idle issue so much more per element that
+// the resident wavefronts count.)  bf16 beside it, as a share of the elements, 63 lanes: none 0.980-0.991, 0.1 0.980-0.991,
+// 0.2 0.994-1.000, 0.3 1.002-1.004, 0.4 1.007-1.011, 0.6 1.018, 0.8 1.021-1.025.
+constexpr bool long_compress(uint64_t blocks, uint64_t bf16_blocks, int lanes_used) {
+    return blocks >= kLongCompress && blocks <= 0x7FFFFFFFull / 4 &&
+           (lanes_used == 64 || lanes_used <= 54 || 4 * bf16_blocks >= blocks);
+}
 
 // LDS one compressing wavefront stages its tile in: 64 rows of 32 elements in
 // the input's own format.

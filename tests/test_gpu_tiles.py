@@ -253,10 +253,10 @@ def test_long_decompressing_launches_against_short_ones(gact, dtype, bits, G):
 
 
 @pytest.mark.parametrize("blocks", (32767, 32768, 32769 + 130))
-@pytest.mark.parametrize("G,bits,mixed", [(256, 2, False), (96, 4, False), (1024, 1, True), (32, 8, True)])
+@pytest.mark.parametrize("G,bits,mixed", [(256, 2, False), (96, 4, False), (96, 4, True), (416, 2, False), (1024, 1, True), (32, 8, True)])
 def test_long_compressing_launches_in_blocks_of_one_wavefront(gact, G, bits, mixed, blocks):
-    """The longest launch with fp32 in blocks of four wavefronts and the shortest in blocks of one, the last tile
-    cut: one tensor, and a list of four of which two may be bf16, against calls for pieces of the same noise."""
+    """The longest launch with fp32 in blocks of four wavefronts and the shortest in blocks of one (groups of 96 only
+    beside bf16), the last tile cut: one tensor, and a list of four of which two may be bf16, against calls for pieces of the same noise."""
     tile = 64 // (G // 32) * G
     n = blocks * 4 * tile - tile // 2 - 5
     x = torch.randn(n, device="cuda", generator=torch.Generator("cuda").manual_seed(blocks))

@@ -43,6 +43,15 @@ int main() {
     CHECK(gact::samplers_for<4>(257) == 2 && gact::samplers_for<4>(32768) == 128);
     adders<gact::kReduceWaves>();
     adders<gact::waves_per_block(gact::kCompressAny)>();
+    // long compressing launches: of fp32 alone, or nearly so, not in tiles of 55 to 63 lanes
+    for (uint64_t b : {gact::kLongCompress, (uint64_t)1000000, (uint64_t)0x7FFFFFFF / 4})
+        for (int lanes = 44; lanes <= 64; ++lanes) {
+            CHECK(gact::long_compress(b, 0, lanes) == (lanes < 55 || lanes == 64));
+            CHECK(gact::long_compress(b, (b + 3) / 4 - 1, lanes) == (lanes < 55 || lanes == 64));
+            CHECK(gact::long_compress(b, (b + 3) / 4, lanes) && gact::long_compress(b, b - 1, lanes));
+        }
+    for (uint64_t b : {(uint64_t)0, gact::kLongCompress - 1, (uint64_t)0x7FFFFFFF / 4 + 1})
+        CHECK(!gact::long_compress(b, b / 2, 64) && !gact::long_compress(b, 0, 64) && !gact::long_compress(b, 0, 52));
     // the compressor of long launches takes at most four blocks of 64 threads for each of 256
     CHECK(4 * 64 * gact::waves_per_block(gact::kCompressLong) == 64 * gact::waves_per_block(gact::kCompressAny));
     return failed;
