@@ -268,6 +268,9 @@ constexpr int dec_block_elems(int dtype, int bits, uint32_t bf16_units) {
 // At 2 and 8 bits of fp32, taken again in turn, division and as below are equal (492, 493; 555, 555); what differs
 // are launches of mixed widths: 400 bf16 tensors, about 3 bits, 829, 813 (0.26 G 109.3, 105.6); groups of 224 422, 400;
 // 53 fp32 tensors 493, 490; 3 fp32 ones of 87 M 72.4, 69.2, groups of 96 74.7, 69.6; 40 of both types, 0.6 G 361, 336.
+// One long tensor of bf16 at 4 bits lost by the order that is best for lists (division, that order, codes first): 34 M
+// 15.72, 15.93, 15.86; 80 M 32.2, 32.6, 32.2; 150 M 59.2, 59.3, 58.3; 220 M 84.5, 85.5, 84.3; 290 M 110.9, 112.6, 110.8;
+// but 400 of 1.0 G 402, 403, 420, 96 of 1.4 G 558, 557, 579.  Single tensors have a kernel of their own, and this order.
 //
 // Launches of fewer than kShortLaunch blocks are over before HBM has settled to any mix, and what waits is the
 // wavefront: they have orders of their own.  The orders of the long launches lose up to 13 % there, and a product for
@@ -295,7 +298,9 @@ struct LoadOrder {
     int  kinds, units;     // s_sleep between codes and minima, and between units; -1: in this order, without a pause
     GroupIndex group = kByProduct;
 };
-constexpr LoadOrder load_order(int dtype, int bits, bool short_launch) {
+enum Launch { kLongList, kLongSingle, kShort };
+constexpr LoadOrder load_order(int dtype, int bits, Launch launch) {
+    const bool short_launch = launch == kShort;
     if (short_launch && bits == 1) return LoadOrder{false, false, 1, 0, kByEither};
     if (short_launch && bits == 4) return LoadOrder{true, false, 0, 0, kByBranch};
     if (short_launch && dtype == GACT_DT_BF16) return bits == 2 ? LoadOrder{false, false, 1, 0} : LoadOrder{true, false, 0, 1};
@@ -303,6 +308,7 @@ constexpr LoadOrder load_order(int dtype, int bits, bool short_launch) {
     if (dtype == GACT_DT_F32)
         return bits == 1 ? LoadOrder{false, false, 2, 1} : bits == 2 ? LoadOrder{false, false, 4, 0}
              : bits == 4 ? LoadOrder{false, true, 1, 0} : LoadOrder{false, true, 1, 1};
+    if (bits == 4 && launch == kLongSingle) return LoadOrder{true, false, 1, 0};
     return bits == 1 ? LoadOrder{false, true, 1, 1} : LoadOrder{true, true, 1, 0};
 }
 

@@ -740,7 +740,7 @@ __device__ __forceinline__ void pause() {
     }
 }
 
-template <int DT, int BITS, bool EDGE, int UNITS, bool SHORT>
+template <int DT, int BITS, bool EDGE, int UNITS, Launch LAUNCH>
 __device__ __forceinline__ void decompress_units(const TensorArgs& t, const Geometry& geo,
                                                  int64_t block_in_tensor, int64_t first_group, int wave, int lane) {
     constexpr uint32_t B = (1u << BITS) - 1u;
@@ -749,7 +749,7 @@ __device__ __forceinline__ void decompress_units(const TensorArgs& t, const Geom
     PieceBits<DT, BITS> pb[UNITS];
     float mn[UNITS], step[UNITS];
     int64_t e[UNITS];
-    constexpr LoadOrder kOrder = load_order(DT, BITS, SHORT);
+    constexpr LoadOrder kOrder = load_order(DT, BITS, LAUNCH);
     const int64_t first_e = first_group * (geo.lpg * kPerLane);
     const auto begin = [&](int k) {
         const int64_t unit = block_in_tensor * (kWavesPerBlk * UNITS) + k * kWavesPerBlk + wave;
@@ -922,7 +922,7 @@ __device__ __forceinline__ void compress_block(const TensorArgs& t, const Geomet
 // A wavefront ends where its stores are out and not behind the dispatch: otherwise it takes four more jumps,
 // each to a line of instructions of its own, which a launch between a model's kernels fetches anew (bf16,
 // 4 bits, between the kernels of a training step: 16.8 M elements 11.7 -> 11.3 us, 50 M 24.7 -> 24.1).
-template <uint32_t BF16_UNITS>
+template <uint32_t BF16_UNITS, Launch LAUNCH>
 __device__ __forceinline__ void decompress_block(const TensorArgs& t, const Geometry& geo,
                                                  int64_t block_in_tensor, bool full) {
     const int wave = threadIdx.x >> 6;
@@ -934,10 +934,10 @@ __device__ __forceinline__ void decompress_block(const TensorArgs& t, const Geom
     if (t.n > kMagicElems)
         first_group = (int64_t)((uint64_t)block_in_tensor * (uint32_t)dec_block_elems(t.dtype(), t.bits(), BF16_UNITS) / (uint32_t)(geo.lpg * kPerLane));
 #define GACT_D_FULL(DT, BITS) \
-    decompress_units<DT, BITS, false, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS), BF16_UNITS == kDecUnitsBf16Short>(t, geo, block_in_tensor, first_group, wave, lane); \
+    decompress_units<DT, BITS, false, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS), LAUNCH>(t, geo, block_in_tensor, first_group, wave, lane); \
     __builtin_amdgcn_endpgm();
 #define GACT_D_EDGE(DT, BITS) \
-    decompress_units<DT, BITS, true, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS), BF16_UNITS == kDecUnitsBf16Short>(t, geo, block_in_tensor, first_group, wave, lane); \
+    decompress_units<DT, BITS, true, dec_units(DT == GACT_DT_F32 ? kDecUnitsF32 : BF16_UNITS, BITS), LAUNCH>(t, geo, block_in_tensor, first_group, wave, lane); \
     __builtin_amdgcn_endpgm();
     if (full) { GACT_DISPATCH(t, true, GACT_D_FULL) } else { GACT_DISPATCH(t, true, GACT_D_EDGE) }
 #undef GACT_D_FULL
@@ -959,7 +959,7 @@ __device__ __forceinline__ void run_block(const TensorArgs& t, const Geometry& g
                                           int64_t block_in_tensor) {
     if constexpr (decompresses(W)) {
         const int64_t end = (block_in_tensor + 1) * dec_block_elems(t.dtype(), t.bits(), bf16_units(W));
-        decompress_block<bf16_units(W)>(t, geo, block_in_tensor, end <= t.n);
+        decompress_block<bf16_units(W), W == kDecompressShort ? kShort : kLongList>(t, geo, block_in_tensor, end <= t.n);
     } else {
         TileOut unused;
         compress_block<W != kCompressBf16, false, waves_per_block(W)>(t, geo, block_in_tensor, unused);
@@ -977,7 +977,7 @@ __device__ __forceinline__ void run_block(const TensorArgs& t, const Geometry& g
 template <Work W>
 GACT_KERNEL(W) single_kernel(uint32_t run_end, uint32_t shift_or_full, TensorArgs t, Geometry geo) {
     const uint32_t b = work_block_of<W>(run_end, shift_or_full);
-    if constexpr (decompresses(W)) decompress_block<bf16_units(W)>(t, geo, (int64_t)b, b < shift_or_full);
+    if constexpr (decompresses(W)) decompress_block<bf16_units(W), W == kDecompressShort ? kShort : kLongSingle>(t, geo, (int64_t)b, b < shift_or_full);
     else run_block<W>(t, geo, (int64_t)b);
 }
 
