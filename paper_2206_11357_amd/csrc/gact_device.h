@@ -164,8 +164,8 @@ struct ReduceArgs {
     int32_t     dtype;     // of a (and of b for sensitivity)
     int32_t     pad;
 };
-// A buffer table small enough to travel in the kernel arguments: 36 bytes a buffer, so that up to 111 would
-// fit beside the 48 bytes of the sensitivity kernel's other arguments; eight buffers' room is left.
+// A buffer table small enough to travel in the kernel arguments: 36 bytes a buffer, so that up to 112 would
+// fit beside the 56 bytes of the sensitivity kernel's other arguments; eight buffers' room is left.
 constexpr int kInlineBuffers = 104;
 struct ReduceTable {
     ReduceArgs t[kInlineBuffers];

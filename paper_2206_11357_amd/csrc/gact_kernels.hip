@@ -990,6 +990,8 @@ GACT_KERNEL(W) single_kernel(uint32_t run_end, uint32_t shift_or_full, TensorArg
 // in 128 bits) and as now: 1 M elements 6.0, 11.7, 340 and 6.0, 6.1, 6.0; 17 M 14.9, 24.7, 425 and 15.0, 15.3, 15.4; 51 M
 // 37.8, 38.9, 143 and 37.9, 38.1, 38.1.  (With a launch behind for both: 1 M 9.3, 10.2, 11.3; 51 M 40.8, 44.1, 44.8.)
 // The arguments pass the 112 bytes that cost the host 0.6 us (gact_device.h); the launch saved was 3.7 us.
+// Blocks of four wavefronts at any length, because a block leaves one sum (537 M fp32 elements: 362 us, the compressor
+// alone, in blocks of one, 350).
 __global__ __launch_bounds__(kBlockThreads) void compress_sum_kernel(uint32_t run_end, uint32_t run_shift, TensorArgs t,
                                                                      Geometry geo, double* block_sum,
                                                                      Finish fin, int n_samples) {
