@@ -287,6 +287,11 @@ constexpr int dec_block_elems(int dtype, int bits, uint32_t bf16_units) {
 //         b=4   3.66 | 3.66 | 3.71     4.32 | 4.38 | 4.40     6.77 |  6.89 |  6.88    8.75 |  9.03 |  8.73
 //         b=8   3.57 | 3.54 | 3.60     6.32 | 5.01 | 4.96     8.45 |  6.50 |  6.45   10.32 |  8.42 |  8.40
 //   (96)  fp32, 8 M, b=1 8.23 | 7.86 | 7.86, b=4 9.09 | 8.61 | 8.60; bf16 b=1 5.61 | 4.56 | 4.96, b=4 5.56 | 4.47 | 4.72
+// At 8 bits the last column is the lists' order.  What it gains where the codes were written long ago it loses right behind
+// their compressor, 4 % on average; single calls, which come like that, load by unit without a pause.  Us, one tensor
+// compressed and decompressed in turn, groups of 256, the division by unit | the lists' order | by unit: bf16, 9.4 M 15.2 |
+// 15.5 | 15.3, 13 M 17.6 | 18.5 | 17.7, 16 M 20.0 | 22.0 | 20.1, 19 M 23.3 | 26.1 | 23.4; fp32, 6 M 13.7 | 14.3 | 13.6, 9.4 M
+// 19.2 | 20.5 | 19.2, 13 M 25.3 | 26.9 | 25.2, 16 M 28.8 | 31.5 | 28.8.
 enum GroupIndex {
     kByProduct,            // a product (group_divisor) for every group size
     kByEither,             // a shift for group sizes that are a power of two, chosen at each piece
@@ -298,11 +303,12 @@ struct LoadOrder {
     int  kinds, units;     // s_sleep between codes and minima, and between units; -1: in this order, without a pause
     GroupIndex group = kByProduct;
 };
-enum Launch { kLongList, kLongSingle, kShort };
+enum Launch { kLongList, kLongSingle, kShortList, kShortSingle };
 constexpr LoadOrder load_order(int dtype, int bits, Launch launch) {
-    const bool short_launch = launch == kShort;
+    const bool short_launch = launch == kShortList || launch == kShortSingle;
     if (short_launch && bits == 1) return LoadOrder{false, false, 1, 0, kByEither};
     if (short_launch && bits == 4) return LoadOrder{true, false, 0, 0, kByBranch};
+    if (launch == kShortSingle && bits == 8) return LoadOrder{true, false, 0, 0, kByEither};
     if (short_launch && dtype == GACT_DT_BF16) return bits == 2 ? LoadOrder{false, false, 1, 0} : LoadOrder{true, false, 0, 1};
     if (short_launch) return bits == 2 ? LoadOrder{false, false, 4, 0} : LoadOrder{false, false, 1, -1};
     if (dtype == GACT_DT_F32)

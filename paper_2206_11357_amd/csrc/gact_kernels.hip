@@ -959,7 +959,7 @@ __device__ __forceinline__ void run_block(const TensorArgs& t, const Geometry& g
                                           int64_t block_in_tensor) {
     if constexpr (decompresses(W)) {
         const int64_t end = (block_in_tensor + 1) * dec_block_elems(t.dtype(), t.bits(), bf16_units(W));
-        decompress_block<bf16_units(W), W == kDecompressShort ? kShort : kLongList>(t, geo, block_in_tensor, end <= t.n);
+        decompress_block<bf16_units(W), W == kDecompressShort ? kShortList : kLongList>(t, geo, block_in_tensor, end <= t.n);
     } else {
         TileOut unused;
         compress_block<W != kCompressBf16, false, waves_per_block(W)>(t, geo, block_in_tensor, unused);
@@ -977,7 +977,7 @@ __device__ __forceinline__ void run_block(const TensorArgs& t, const Geometry& g
 template <Work W>
 GACT_KERNEL(W) single_kernel(uint32_t run_end, uint32_t shift_or_full, TensorArgs t, Geometry geo) {
     const uint32_t b = work_block_of<W>(run_end, shift_or_full);
-    if constexpr (decompresses(W)) decompress_block<bf16_units(W), W == kDecompressShort ? kShort : kLongSingle>(t, geo, (int64_t)b, b < shift_or_full);
+    if constexpr (decompresses(W)) decompress_block<bf16_units(W), W == kDecompressShort ? kShortSingle : kLongSingle>(t, geo, (int64_t)b, b < shift_or_full);
     else run_block<W>(t, geo, (int64_t)b);
 }
 
