@@ -184,6 +184,11 @@ static_assert(sizeof(ReduceTable) + 64 <= kKernelArguments, "a buffer table and 
 // Launches below one window of eight runs keep plain order.
 constexpr uint32_t kDiffRunShift = 3, kStatsRunShift = 5;
 constexpr uint32_t runs_end(uint32_t blocks, uint32_t s) { return blocks >> (3 + s) << (3 + s); }
+// A statistics launch of fewer blocks is in memory at once, or nearly so: plain order, and a block does not wait for its
+// stores before it adds up.  Us, plain order and no wait | runs and a wait, an encoder's buffers: fp32, 6.3 M elements 15.9 |
+// 16.6, 12.6 M 27.6 | 28.3, 25 M 50.4 | 50.5, 32 M 64.6 | 64.1; bf16, 6.3 M 13.7 | 14.1, 12.6 M 23.9 | 24.3, 25 M 42.5 | 42.6.
+constexpr uint32_t kShortStats = 4096;
+constexpr uint32_t stats_runs_end(uint32_t blocks) { return blocks < kShortStats ? 0 : runs_end(blocks, kStatsRunShift); }
 
 // Elements of one buffer a block covers: 512 threads x 2 pieces, of 16 bytes where the buffers are only
 // read, of 4 elements in a statistics step (16 bytes of the fp32 mean, whatever the gradient's type).

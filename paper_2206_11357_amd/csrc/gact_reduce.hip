@@ -315,8 +315,8 @@ __device__ __forceinline__ void grad_stats_block(const ReduceArgs& r, int64_t bl
     }
     // The block keeps its place until its stores are acknowledged: the fewer are under way, the better the
     // memory takes them beside the reads (us, 302 M parameters: fp32 589 without, 580 with; bf16 478, 468;
-    // WIDE 552 without, 571 with).
-    if (!WIDE) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // WIDE 552 without, 571 with).  Not in short launches (kShortStats).
+    if (!WIDE && blocks >= kShortStats) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     double sum[2] = {sg2, sm2};
     block_sums<stats_threads(WIDE) / 64>(sum);
     if (threadIdx.x == 0) { partial[b] = sum[0]; partial[blocks + b] = sum[1]; }
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(stats_threads(WIDE)) void grad_stats_kernel(const R
                                                                          const uint32_t* __restrict__ first_block,
                                                                          int K, float rt, int bf16_chunks, uint32_t blocks,
                                                                          double* __restrict__ partial) {
-    const uint32_t b = ordered_block(blockIdx.x, runs_end(blocks, kStatsRunShift), kStatsRunShift);
+    const uint32_t b = ordered_block(blockIdx.x, stats_runs_end(blocks), kStatsRunShift);
     const int k = find_buffer(first_block, K, b);
     const ReduceArgs r = table[k];
     grad_stats_block<WIDE>(r, (int64_t)(b - first_block[k]), rt, bf16_chunks, blocks, partial);
@@ -337,7 +337,7 @@ template <bool WIDE>
 __global__ __launch_bounds__(stats_threads(WIDE)) void grad_stats_inline_kernel(ReduceTable tab, int K, float rt,
                                                                                 int bf16_chunks, uint32_t blocks,
                                                                                 double* __restrict__ partial) {
-    const uint32_t b = ordered_block(blockIdx.x, runs_end(blocks, kStatsRunShift), kStatsRunShift);
+    const uint32_t b = ordered_block(blockIdx.x, stats_runs_end(blocks), kStatsRunShift);
     const int k = find_buffer(tab.first_block, K, b);
     grad_stats_block<WIDE>(tab.t[k], (int64_t)(b - tab.first_block[k]), rt, bf16_chunks, blocks, partial);
 }

@@ -114,10 +114,10 @@ def test_statistics_in_the_least_workspace(gact, sizes, dtypes):
 
 
 @pytest.mark.parametrize("dtype", ("f32", "bf16"))
-@pytest.mark.parametrize("blocks", (1, 63, 64, 65, 129, 255, 256, 257, 700))
+@pytest.mark.parametrize("blocks", (1, 63, 64, 65, 129, 255, 256, 257, 700, 4095, 4096, 4097 + 256))
 def test_every_block_is_taken_once_in_any_order(gact, dtype, blocks):
     """Launches of no, one and several whole windows of eight runs (64 blocks of a sensitivity, 256 of a statistics
-    step), with and without blocks behind them, in one buffer and in three.  Small whole numbers, a sum of which
+    step, which has them from 4,096 blocks on), with and without blocks behind them, in one buffer and in three.  Small whole numbers, a sum of which
     is exact; every chunk of a buffer has a value of its own, so that none can stand for another."""
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
     for lists in (1, 3):
