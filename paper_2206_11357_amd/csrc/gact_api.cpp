@@ -84,8 +84,7 @@ int make_args(bool compress, const void* x, void* packed, float* gmin, float* gs
 int64_t blocks_for(gact::Work work, const gact::TensorArgs& t, uint32_t tiles) {
     const uint32_t waves = gact::waves_per_block(work);
     if (!decompresses(work)) return ((int64_t)tiles + waves - 1) / waves;
-    const int64_t span = gact::dec_block_elems(t.dtype(), t.bits(), work == gact::kDecompressShort ? gact::kDecUnitsBf16Short : gact::kDecUnitsBf16);
-    return (t.n + span - 1) / span;
+    return gact::dec_blocks(t.n, t.dtype(), t.bits(), work == gact::kDecompressShort ? gact::kDecUnitsBf16Short : gact::kDecUnitsBf16);
 }
 
 // The kind of a launch, from the LDS its widest dtype needs; then, its blocks counted as those of that kind,

@@ -52,6 +52,14 @@ int main() {
         }
     for (uint64_t b : {(uint64_t)0, gact::kLongCompress - 1, (uint64_t)0x7FFFFFFF / 4 + 1})
         CHECK(!gact::long_compress(b, b / 2, 64) && !gact::long_compress(b, 0, 64) && !gact::long_compress(b, 0, 52));
+    // blocks of a decompressed tensor: as by a division
+    for (int dtype : {GACT_DT_F32, GACT_DT_BF16})
+        for (int bits : {1, 2, 4, 8})
+            for (uint32_t table : {gact::kDecUnitsBf16, gact::kDecUnitsBf16Short}) {
+                const int64_t span = gact::dec_block_elems(dtype, bits, table);
+                for (int64_t base : {(int64_t)0, 3 * span, 1000003 * span, ((int64_t)1 << 42) / span * span})
+                    for (int64_t n = base > 9 ? base - 9 : 1; n < base + 9000; ++n) CHECK(gact::dec_blocks(n, dtype, bits, table) == (n + span - 1) / span);
+            }
     // the compressor of long launches takes at most four blocks of 64 threads for each of 256
     CHECK(4 * 64 * gact::waves_per_block(gact::kCompressLong) == 64 * gact::waves_per_block(gact::kCompressAny));
     return failed;
