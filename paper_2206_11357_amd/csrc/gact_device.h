@@ -188,7 +188,8 @@ constexpr uint32_t runs_end(uint32_t blocks, uint32_t s) { return blocks >> (3 +
 // stores before it adds up.  Us, plain order and no wait | runs and a wait, an encoder's buffers: fp32, 6.3 M elements 15.9 |
 // 16.6, 12.6 M 27.6 | 28.3, 25 M 50.4 | 50.5, 32 M 64.6 | 64.1; bf16, 6.3 M 13.7 | 14.1, 12.6 M 23.9 | 24.3, 25 M 42.5 | 42.6.
 constexpr uint32_t kShortStats = 4096;
-constexpr uint32_t stats_runs_end(uint32_t blocks) { return blocks < kShortStats ? 0 : runs_end(blocks, kStatsRunShift); }
+// (Wide blocks are more than that; asked for it all the same, a block of theirs starts later: 302 M fp32 0.4 %.)
+constexpr uint32_t stats_runs_end(uint32_t blocks, bool wide) { return !wide && blocks < kShortStats ? 0 : runs_end(blocks, kStatsRunShift); }
 
 // Elements of one buffer a block covers: 512 threads x 2 pieces, of 16 bytes where the buffers are only
 // read, of 4 elements in a statistics step (16 bytes of the fp32 mean, whatever the gradient's type).

@@ -327,7 +327,7 @@ __global__ __launch_bounds__(stats_threads(WIDE)) void grad_stats_kernel(const R
                                                                          const uint32_t* __restrict__ first_block,
                                                                          int K, float rt, int bf16_chunks, uint32_t blocks,
                                                                          double* __restrict__ partial) {
-    const uint32_t b = ordered_block(blockIdx.x, stats_runs_end(blocks), kStatsRunShift);
+    const uint32_t b = ordered_block(blockIdx.x, stats_runs_end(blocks, WIDE), kStatsRunShift);
     const int k = find_buffer(first_block, K, b);
     const ReduceArgs r = table[k];
     grad_stats_block<WIDE>(r, (int64_t)(b - first_block[k]), rt, bf16_chunks, blocks, partial);
@@ -337,7 +337,7 @@ template <bool WIDE>
 __global__ __launch_bounds__(stats_threads(WIDE)) void grad_stats_inline_kernel(ReduceTable tab, int K, float rt,
                                                                                 int bf16_chunks, uint32_t blocks,
                                                                                 double* __restrict__ partial) {
-    const uint32_t b = ordered_block(blockIdx.x, stats_runs_end(blocks), kStatsRunShift);
+    const uint32_t b = ordered_block(blockIdx.x, stats_runs_end(blocks, WIDE), kStatsRunShift);
     const int k = find_buffer(tab.first_block, K, b);
     grad_stats_block<WIDE>(tab.t[k], (int64_t)(b - tab.first_block[k]), rt, bf16_chunks, blocks, partial);
 }
